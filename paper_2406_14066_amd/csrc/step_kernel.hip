@@ -252,11 +252,57 @@ struct RejectShared {
     float seg_off[2 * SPEC_K_MAX + 1][kMaxStatSegments];
 };
 
+// Streams one segment of a logit row through the block: `use(batch, x)` is called for each batch of
+// kBatch vectors per thread, the vectors of thread t of batch i being (i * kBatch + u) * kThreads + t.
+// DEPTH batches are in flight per thread: as soon as one is used its registers are refilled, so
+// the memory system stays busy during the arithmetic (a pass that loads a whole batch of rows, waits
+// and then computes leaves it idle in between, all blocks of a rejection-only launch in step: greedy
+// acceptance of 256 requests, k = 3, V = 32000, 131 MB: 44.9 -> 35.7 us with the arg-max below).
+// Vectors past the end read as zeros without touching memory (the descriptor ends with the segment).
+constexpr int kBatch = 4;
+template <int DEPTH, int POLICY, typename F>
+__device__ __forceinline__ void stream_segment(const float *seg, int nvec, F use)
+{
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(seg), 0, (uint32_t)nvec * 16u, kBufferFlags);
+    f32x4 ring[DEPTH][kBatch];
+    auto fetch = [&](int batch, f32x4(&x)[kBatch]) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            x[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                rsrc, (int)(((uint32_t)(batch * kBatch + u) * kThreads + threadIdx.x) * 16u), 0, POLICY));
+    };
+    const int nbatch = (nvec + kBatch * kThreads - 1) / (kBatch * kThreads);
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        fetch(d, ring[d]);
+        __builtin_amdgcn_sched_barrier(0);   // the loads stay in ring order: a wait for one batch is not a wait for later ones
+    }
+    for (int i = 0; i < nbatch; i += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (i + d < nbatch) use(i + d, ring[d]);
+            fetch(i + d + DEPTH, ring[d]);
+        }
+    }
+}
+
+// Sets what a batch holds past the end of the segment (zeros) to -inf.
+__device__ __forceinline__ void mask_past_end(int batch, int nvec, f32x4 (&x)[kBatch])
+{
+    if ((batch + 1) * kBatch * kThreads <= nvec) return;   // the same for the whole block
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+        if ((batch * kBatch + u) * kThreads + (int)threadIdx.x >= nvec) x[u] = (f32x4){-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+}
+
+__device__ __forceinline__ float max_of(const f32x4 &x) { return fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])); }
+
 // One (row, segment): offset and sum of 2^(x*log2e - offset) over the segment.
 // The running offset is integer-valued in base-2 units, so every rescale is an
 // exact power of two and x*log2(e) - offset is rounded once (log2 e enters as an
 // fp32 hi/lo pair inside fused multiply-adds).
-template <int UNROLL>   // vectors of 16 bytes in flight per thread (these blocks share the attention role's register budget)
+template <int DEPTH>   // batches in flight per thread (these blocks share the attention role's register budget)
 __device__ __forceinline__ void stats_block(const RejectParams &p, int row, int seg, RejectShared &sh)
 {
     const int tid = threadIdx.x;
@@ -264,22 +310,16 @@ __device__ __forceinline__ void stats_block(const RejectParams &p, int row, int 
                                   : p.draft_logits + (size_t)(row - p.T) * p.V;
     const int v0 = seg * p.stat_seg_len;
     const int v1 = min(p.V, v0 + p.stat_seg_len);
-    const float4 *vec = reinterpret_cast<const float4 *>(base + v0);
     const int nvec = (v1 - v0) >> 2;
 
     float m = -FLT_MAX;   // largest logit seen
     float off = kEmptyMax;
     float s = 0.0f;
-    for (int i = tid; i < nvec; i += kThreads * UNROLL) {
-        float4 x[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int idx = i + u * kThreads;
-            x[u] = idx < nvec ? vec[idx] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        }
+    stream_segment<DEPTH, 0>(base + v0, nvec, [&](int batch, f32x4(&x)[kBatch]) {
+        mask_past_end(batch, nvec, x);
         float cm = m;
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) cm = fmaxf(cm, fmaxf(fmaxf(x[u].x, x[u].y), fmaxf(x[u].z, x[u].w)));
+        for (int u = 0; u < kBatch; ++u) cm = fmaxf(cm, max_of(x[u]));
         if (cm > m) {
             const float new_off = ceilf(cm * kLog2eHi);
             s *= fast_exp2(off - new_off);
@@ -288,13 +328,11 @@ __device__ __forceinline__ void stats_block(const RejectParams &p, int row, int 
         }
         const float noff = -off;
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            s += fast_exp2(fmaf(x[u].x, kLog2eHi, fmaf(x[u].x, kLog2eLo, noff)));
-            s += fast_exp2(fmaf(x[u].y, kLog2eHi, fmaf(x[u].y, kLog2eLo, noff)));
-            s += fast_exp2(fmaf(x[u].z, kLog2eHi, fmaf(x[u].z, kLog2eLo, noff)));
-            s += fast_exp2(fmaf(x[u].w, kLog2eHi, fmaf(x[u].w, kLog2eLo, noff)));
+        for (int u = 0; u < kBatch; ++u) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s += fast_exp2(fmaf(x[u][e], kLog2eHi, fmaf(x[u][e], kLog2eLo, noff)));
         }
-    }
+    });
 
     const int wave = tid / kWave, lane = tid % kWave;
     float wm = off;
@@ -325,35 +363,35 @@ __device__ __forceinline__ void stats_block(const RejectParams &p, int row, int 
 }
 
 // Greedy mode: one (target row, segment): the largest logit and the lowest id that has it.
+template <int DEPTH>
 __device__ __forceinline__ void argmax_block(const RejectParams &p, int row, int seg, RejectShared &sh)
 {
-    constexpr int UNROLL = 16;
     const int tid = threadIdx.x;
     const float *base = p.target_logits + (size_t)row * p.V;
     const int v0 = seg * p.stat_seg_len;
     const int v1 = min(p.V, v0 + p.stat_seg_len);
-    const float4 *vec = reinterpret_cast<const float4 *>(base + v0);
     const int nvec = (v1 - v0) >> 2;
+    // Per element only a maximum is taken (of three operands per instruction); the id is looked up when a
+    // batch raises a thread's maximum, which gets rare after the first few.  Ids rise from batch to
+    // batch and within one, so the first batch with the maximum and its lowest match are the answer.
+    // (Nothing but -inf: the lowest id.)
     float best = -INFINITY;
-    int best_id = 0x7FFFFFFF;
-    for (int i = tid; i < nvec; i += kThreads * UNROLL) {
-        float4 x[UNROLL];
+    int best_id = tid < nvec ? v0 + 4 * tid : 0x7FFFFFFF;
+    stream_segment<DEPTH, kStreamPolicy>(base + v0, nvec, [&](int batch, f32x4(&x)[kBatch]) {
+        mask_past_end(batch, nvec, x);
+        float cm = best;
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int idx = i + u * kThreads;
-            x[u] = idx < nvec ? vec[idx] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        }
+        for (int u = 0; u < kBatch; ++u) cm = fmaxf(cm, max_of(x[u]));
+        if (cm > best) {
+            best = cm;
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            // vectors past the end were filled with -inf and ids that only grow: they change
-            // nothing unless the whole row is -inf, and then the lowest id still wins
-            const int id0 = v0 + 4 * (i + u * kThreads);
-            if (x[u].x > best || (x[u].x == best && id0 + 0 < best_id)) { best = x[u].x; best_id = id0 + 0; }
-            if (x[u].y > best || (x[u].y == best && id0 + 1 < best_id)) { best = x[u].y; best_id = id0 + 1; }
-            if (x[u].z > best || (x[u].z == best && id0 + 2 < best_id)) { best = x[u].z; best_id = id0 + 2; }
-            if (x[u].w > best || (x[u].w == best && id0 + 3 < best_id)) { best = x[u].w; best_id = id0 + 3; }
+            for (int u = kBatch - 1; u >= 0; --u) {
+                const int id0 = v0 + 4 * ((batch * kBatch + u) * kThreads + tid);
+#pragma unroll
+                for (int e = 3; e >= 0; --e) best_id = x[u][e] == cm ? id0 + e : best_id;
+            }
         }
-    }
+    });
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
         const float ov = __shfl_xor(best, o);
@@ -623,7 +661,7 @@ __device__ __forceinline__ bool greedy_prefix(const RejectParams &p, int b, int 
 // Statistics items are ordered by request (its target rows, then its draft rows), so that
 // the first requests' statistics are complete early and their races can start while
 // later requests' rows are still being read.
-template <int UNROLL>
+template <int DEPTH>
 __device__ __forceinline__ void stats_role(const RejectParams &p, int item, RejectShared &sh)
 {
     const int rec = item / p.stat_segments;          // (request, row of the request)
@@ -669,13 +707,13 @@ __device__ __forceinline__ void stats_role(const RejectParams &p, int item, Reje
             }
             return;
         }
-        if (greedy) argmax_block(p, row, seg, sh);
-        else stats_block<UNROLL>(p, row, seg, sh);
+        if (greedy) argmax_block<DEPTH>(p, row, seg, sh);
+        else stats_block<DEPTH>(p, row, seg, sh);
         return;
     }
     if (p.mode != SPEC_ACCEPT_SAMPLE) {   // target rows only: rec is the row
-        if (p.mode == SPEC_ACCEPT_GREEDY) argmax_block(p, rec, seg, sh);
-        else stats_block<UNROLL>(p, rec, seg, sh);
+        if (p.mode == SPEC_ACCEPT_GREEDY) argmax_block<DEPTH>(p, rec, seg, sh);
+        else stats_block<DEPTH>(p, rec, seg, sh);
         return;
     }
     // largest b with 2 * cu_q_len[b] - b <= rec (rows of the requests before b).  Start from
@@ -691,7 +729,7 @@ __device__ __forceinline__ void stats_role(const RejectParams &p, int item, Reje
     const int k = uniform_load(p.cu_q_len, b + 1) - row_t0 - 1;
     const int ri = rec - (2 * row_t0 - b);
     const int row = ri <= k ? row_t0 + ri : p.T + (row_t0 - b) + (ri - k - 1);
-    stats_block<UNROLL>(p, row, seg, sh);
+    stats_block<DEPTH>(p, row, seg, sh);
 }
 
 // A request whose bounded wait ran out (never in a healthy launch): every output gets its
@@ -1580,7 +1618,7 @@ __global__ __launch_bounds__(kThreads, 2) void spec_step_kernel(StepArgs args)
             __shared__ RejectShared rsh;
             if (item < gs.n_stat) {
                 // a whole 32000-entry row per round trip where the registers allow it
-                stats_role<(HAS_ATTN && NT >= 2) ? 32 : 16>(rp, item, rsh);
+                stats_role<(HAS_ATTN && NT >= 2) ? 8 : 4>(rp, item, rsh);
             } else {
                 const int after = item - gs.n_stat;
                 const int n_race = rp.B * rp.race_segments;

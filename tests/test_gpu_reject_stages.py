@@ -1,0 +1,55 @@
+"""Sizes at which the rejection half's stages can go wrong, against the CPU oracle: the edges of the
+batches in which a block streams a logit row, and equal maxima wherever they can sit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2406_14066_amd import workloads as W
+from paper_2406_14066_amd import spec_verify as sv
+from parity_utils import check_reject
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def harness():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2406_14066_amd import harness as H
+    return H
+
+
+def _logits_only(B, V, k, seed):
+    w = W.make_workload("stages", B=B, Hq=1, Hkv=1, d=64, V=V, dtype="f32", kv_len=[16] * B, k=k, draft_std=3.0,
+                        sigma=0.8, data_seed=seed, philox_seed=99 + seed, with_kv=False)
+    w.k_pages = w.v_pages = np.zeros((1, 1, 16, 64), np.float32)
+    w.q = np.zeros((w.T, 1, 64), np.float32)
+    return w
+
+
+# a batch of the streaming pass is 4096 logits, a ring of them 16384; a row is cut into segments of 8192 or more
+@pytest.mark.parametrize("V", [4, 1020, 4092, 4096, 4100, 16380, 16388, 20484, 65540], ids=lambda v: "V%d" % v)
+def test_streamed_rows_at_batch_edges(harness, V):
+    print("case stream edges", V, flush=True)
+    k = [3, 0, 5, 1]
+    w = _logits_only(4, V, k, seed=V)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    ds.run_reject()
+    check_reject(w, ds.results())
+
+    # greedy: integer logits (many equal maxima), a maximum in the last and in a middle place, a row of -inf
+    w.target_logits = np.round(np.clip(w.target_logits, -6, 6)).astype(np.float32)
+    w.target_logits[1, [V - 1, V // 2]] = 9.0
+    w.target_logits[2] = -np.inf
+    w.target_logits[3, V - 1] = 9.0
+    for b in range(w.B):
+        t0 = int(w.cu_q_len[b])
+        for i in range(k[b]):
+            w.draft_tokens[t0 - b + i] = int(np.argmax(w.target_logits[t0 + i]))   # (the first of equal maxima)
+    ref = oracle.reject_greedy(w.target_logits, w.draft_tokens, w.cu_q_len)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=sv.ACCEPT_GREEDY)
+    ds.run_reject()
+    res = ds.results()
+    for name in ("accepted_len", "next_token", "out_tokens", "counters"):
+        np.testing.assert_array_equal(res[name], getattr(ref, name))
+    assert (ref.accepted_len == k).all()
