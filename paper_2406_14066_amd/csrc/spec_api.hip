@@ -97,7 +97,7 @@ struct Tuning {
     int force_generic = 0;        // SPEC_VERIFY_FORCE_GENERIC=1: every shape through the generic attention kernels
     long target_blocks = 0;       // SPEC_VERIFY_TARGET_BLOCKS: attention blocks to aim for when splitting requests (0: automatic)
     long chunk = 0;               // SPEC_VERIFY_CHUNK: tokens per chunk, multiple of 16 (0: automatic)
-    int race_blocks = 512;        // SPEC_VERIFY_RACE_BLOCKS: race blocks to aim for
+    int race_blocks = 0;          // SPEC_VERIFY_RACE_BLOCKS: race blocks to aim for (0: automatic)
     int early_stop = -1;          // SPEC_VERIFY_EARLY_STOP=0/1: statistics in position order (-1: automatic)
     float reject_span = 0.5f;     // SPEC_VERIFY_REJECT_SPAN: fraction of the attention items among which the rejection items are spread
     long attn_first_limit = -1;   // SPEC_VERIFY_ATTN_FIRST_LIMIT: attention blocks up to which they all precede the rejection blocks (-1: automatic)
@@ -415,14 +415,19 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     seg_len = (seg_len + 3) / 4 * 4;
     pl.stat_seg_len = seg_len;
     pl.stat_segments = (r->V + seg_len - 1) / seg_len;
-    // race: about 512 blocks in all, segments of >= 2048 vocabulary ids, at most 64 per request
-    int rsegs = (tu.race_blocks + r->B - 1) / r->B;
+    // race: segments of >= 2048 vocabulary ids, at most 64 per request; about 1024 blocks in all when the
+    // rejection half runs alone (what 4 blocks per compute unit hold: 256 / 512 / 1024 / 1536 blocks 59.3 / 53.8 /
+    // 51.4 / 52.4 us for 256 requests, k = 2, V = 32000), about 256 beside an attention half, where every block
+    // holds a slot of the attention's while it waits (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
+    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7)
+    const int race_blocks = tu.race_blocks > 0 ? tu.race_blocks : (attn_us < 0.0 ? 1024 : 256);
+    int rsegs = (race_blocks + r->B - 1) / r->B;
     const int rmax_by_len = (r->V + 2047) / 2048;
     if (rsegs > rmax_by_len) rsegs = rmax_by_len;
     if (rsegs > 64) rsegs = 64;
     if (rsegs < 1) rsegs = 1;
     int rlen = (r->V + rsegs - 1) / rsegs;
-    rlen = (rlen + 3) / 4 * 4;
+    rlen = (rlen + 1023) / 1024 * 1024;   // a block takes 1024 ids at a time
     pl.race_seg_len = rlen;
     pl.race_segments = (r->V + rlen - 1) / rlen;
 

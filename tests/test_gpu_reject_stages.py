@@ -53,3 +53,19 @@ def test_streamed_rows_at_batch_edges(harness, V):
     for name in ("accepted_len", "next_token", "out_tokens", "counters"):
         np.testing.assert_array_equal(res[name], getattr(ref, name))
     assert (ref.accepted_len == k).all()
+
+
+# a race block takes 1024 ids at a time and parts of 8192; one segment per request makes the last part ragged
+@pytest.mark.parametrize("mode", [sv.ACCEPT_SAMPLE, sv.ACCEPT_POINT_DRAFT], ids=["sample", "point"])
+@pytest.mark.parametrize("V", [4, 1024, 1028, 8188, 8196, 20484], ids=lambda v: "V%d" % v)
+def test_race_of_one_segment_at_part_edges(harness, tuning, V, mode):
+    print("case race parts", V, mode, flush=True)
+    tuning("SPEC_VERIFY_RACE_BLOCKS", 1)
+    w = _logits_only(5, V, [2, 0, 8, 1, 4], seed=V + 1)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=mode)
+    assert ds.plan()["race_segments"] == 1
+    ds.run_reject()
+    ref = None
+    if mode == sv.ACCEPT_POINT_DRAFT:
+        ref = oracle.reject_onehot(w.target_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
+    check_reject(w, ds.results(), ref=ref)
