@@ -85,7 +85,7 @@ __host__ __device__ inline bool request_lengths_ok(int kv_len, int q_len, int ca
 //     sum_v 2^(x_v*log2(e) - off2) as fp64, and off2 (integer-valued base-2 offset) as fp32
 //     (greedy mode: the segment's largest logit as fp32 and its lowest id, third word unused)
 //   race partial of one (request, segment): 2 words: best score (fp32), its id
-//   race info of one request: m | k << 8 | near ties << 16
+//   race info of one request: m | near ties << 16
 constexpr int kStatWords = 3;
 
 struct RejectPlan {
@@ -95,7 +95,9 @@ struct RejectPlan {
     size_t partial_off, partial_bytes;     // race partials [B][race_segments][2], then race info [B]
     size_t total_bytes;
     int32_t early_stop, uniform_k;         // see RejectParams
+    int32_t final_shift;                   // log2 of the requests per item of the final stage
 };
+constexpr int kMaxFinalShift = 4;
 
 struct RejectParams {
     // (4-byte scalars first, an even number of them: no padding holes, see AttnParams)
@@ -109,7 +111,7 @@ struct RejectParams {
     int32_t early_stop;                  // statistics in position order, rows after a request's first rejection are not read (see stats_role)
     int32_t uniform_k;                   // with early_stop: every request's draft length
     int32_t short_naps;                  // a small launch: the bounded waits poll at short intervals at first
-    int32_t reserved;
+    int32_t final_shift;                 // log2 of the requests per item of the final stage (0..kMaxFinalShift)
     const float *target_logits, *draft_logits;
     const int32_t *draft_tokens, *cu_q_len;
     int32_t *accepted_len, *next_token, *out_tokens;
@@ -123,6 +125,7 @@ struct RejectParams {
     const unsigned long long *step_device;   // if not null: the Philox step counter, read when the kernel runs
 };
 static_assert(sizeof(RejectParams) == 18 * 4 + 16 * 8, "RejectParams has padding");
+inline int final_items(const RejectParams &p) { return (p.B + (1 << p.final_shift) - 1) >> p.final_shift; }
 
 // Order in which the attention items take the requests (longest first), passed as a
 // kernel argument.  n == 0: the given order.

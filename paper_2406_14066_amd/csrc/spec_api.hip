@@ -430,6 +430,10 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     rlen = (rlen + 1023) / 1024 * 1024;   // a block takes 1024 ids at a time
     pl.race_seg_len = rlen;
     pl.race_segments = (r->V + rlen - 1) / rlen;
+    // requests per item of the final stage: as many as leave 8 items (the kernel says why they are grouped)
+    pl.final_shift = 0;
+    while (pl.final_shift < kMaxFinalShift && (16 << pl.final_shift) <= r->B && (pl.stat_segments << (pl.final_shift + 1)) <= 32)
+        ++pl.final_shift;
 
     // Early stop: with one draft length for all requests the statistics items can be taken in
     // position order and the rows after a request's first rejection left unread.  That turns the
@@ -653,11 +657,12 @@ RejectParams reject_params(const spec_reject_args *r, const RejectPlan &pl, char
     p.stat_segments = pl.stat_segments; p.stat_seg_len = pl.stat_seg_len;
     p.race_segments = pl.race_segments; p.race_seg_len = pl.race_seg_len;
     p.early_stop = pl.early_stop; p.uniform_k = pl.uniform_k;
+    p.final_shift = pl.final_shift;
     p.spin_limit = tuning().spin_limit;
     {
         // (a launch of at most one rejection block per compute unit counts as small)
         const int64_t rows = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * (int64_t)r->T - r->B : r->T;
-        p.short_naps = rows * pl.stat_segments + (int64_t)r->B * (pl.race_segments + 1) <= compute_units() ? 1 : 0;
+        p.short_naps = rows * pl.stat_segments + (int64_t)r->B * pl.race_segments + final_items(p) <= compute_units() ? 1 : 0;
     }
     p.stats = reinterpret_cast<unsigned long long *>(ws + pl.stats_off);
     p.race_partial = reinterpret_cast<unsigned long long *>(ws + pl.partial_off);
@@ -782,7 +787,8 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
         info->stat_segments = pl.stat_segments;
         info->race_segments = reject->accept_mode == SPEC_ACCEPT_GREEDY ? 0 : pl.race_segments;
         const int rows = reject->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * reject->T - reject->B : reject->T;
-        info->reject_blocks = rows * pl.stat_segments + reject->B * info->race_segments + reject->B;
+        info->reject_blocks = rows * pl.stat_segments + reject->B * info->race_segments +
+                              ((reject->B + (1 << pl.final_shift) - 1) >> pl.final_shift);
         if (attn == nullptr || info->attn_path != SPEC_PATH_MFMA) info->launches += 1;
         info->workspace_bytes += pl.total_bytes;
     }

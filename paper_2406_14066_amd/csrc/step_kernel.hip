@@ -236,6 +236,7 @@ __device__ __forceinline__ StepWords philox_step_words(const RejectParams &p)
 }
 
 constexpr int kMaxStatSegments = 32;
+constexpr int kMaxFinalGroup = 1 << kMaxFinalShift;
 constexpr int kRaceVec = 8;                      // see the race
 constexpr int kRacePart = kRaceVec * kThreads;   // vectors of 4 ids per part of the race
 constexpr float kLog2eHi = 1.4426950216293335f;     // fp32(log2 e)
@@ -252,6 +253,9 @@ struct RejectShared {
     int best_id[kWaves];
     double seg_sum[2 * SPEC_K_MAX + 1][kMaxStatSegments];
     float seg_off[2 * SPEC_K_MAX + 1][kMaxStatSegments];
+    // final stage: per request of the block
+    int fin_ready[kMaxFinalGroup], fin_need[kMaxFinalGroup], fin_id[kMaxFinalGroup];
+    uint32_t fin_count[2];
     f32x4 variates[kRaceVec][kThreads];   // 1 / e_v of a race block's part, each thread its own
 };
 
@@ -754,29 +758,6 @@ __device__ __forceinline__ void stats_role(const RejectParams &p, int item, Reje
     stats_block<DEPTH>(p, row, seg, sh);
 }
 
-// A request whose bounded wait ran out (never in a healthy launch): every output gets its
-// sentinel and the request is counted in counters[7] only.
-__device__ __forceinline__ void abandon_request(const RejectParams &p, int b)
-{
-    const int tid = threadIdx.x;
-    if (p.out_tokens != nullptr && tid <= SPEC_K_MAX) p.out_tokens[(size_t)b * (SPEC_K_MAX + 1) + tid] = -1;
-    if (tid != 0) return;
-    p.accepted_len[b] = -1;
-    p.next_token[b] = -1;
-    if (p.new_kv_len != nullptr) p.new_kv_len[b] = -1;
-    if (p.draft_next_len != nullptr) p.draft_next_len[b] = -1;
-    atomicAdd(&p.counters[7], 1ull);
-}
-
-// Draft tokens of request b outside [0, V): counted among the input errors (counters[6]).
-__device__ __forceinline__ void count_bad_draft_tokens(const RejectParams &p, int row_d0, int k)
-{
-    int bad = 0;
-    for (int i = 0; i < k; ++i)
-        if ((unsigned)p.draft_tokens[row_d0 + i] >= (unsigned)p.V) ++bad;
-    if (bad) atomicAdd(&p.counters[6], (unsigned long long)bad);
-}
-
 __device__ __forceinline__ RaceRows race_rows(const RejectParams &p, int b, const RejectShared &sh)
 {
     RaceRows rr;
@@ -818,7 +799,6 @@ __device__ __forceinline__ void race_role(const RejectParams &p, int item, Rejec
     race_variates(p, step, b, g_begin, g_end, sh);
     if (!accept_phase(p, b, sh, seg == 0)) return;
     const RaceRows rr = race_rows(p, b, sh);
-    const int k = uniform_load(p.cu_q_len, b + 1) - uniform_load(p.cu_q_len, b) - 1;
     float win_score = -1.0f;
     int win_id = 0x7FFFFFFF;
     race_part(rr, g_begin, g_end, sh, win_score, win_id);
@@ -832,175 +812,185 @@ __device__ __forceinline__ void race_role(const RejectParams &p, int item, Rejec
         publish_tagged(dst + 0, __float_as_uint(win_score), p.generation);
         publish_tagged(dst + 1, (uint32_t)win_id, p.generation);
         if (seg == 0)   // the accept chain's result, for the final stage
-            publish_tagged(p.race_info + b, (uint32_t)rr.m | ((uint32_t)k << 8) | ((uint32_t)sh.near << 16), p.generation);
+            publish_tagged(p.race_info + b, (uint32_t)rr.m | ((uint32_t)sh.near << 16), p.generation);
     }
 }
 
-// Greedy mode, last stage of request b (there is no race): waits (bounded) for the
-// arg-max records of the request's k+1 target rows, accepts the leading run of draft
-// tokens that equal their row's arg-max, and emits the arg-max of the row after it.
-__device__ __forceinline__ void greedy_final(const RejectParams &p, int b, RejectShared &sh)
+// Last stage: one item per group of 2^final_shift requests (after all race items), 2^(8 - final_shift)
+// threads each.  Waits (bounded) for what the group's requests need, writes their outputs, adds up
+// their counters, and clears their tags so that a replay of the same launch (HIP graph) starts
+// clean.  Requests are grouped because of the counters: all blocks add to the same few words, and
+// such adds are taken one after the other, some 14 ns each (one block per request and seven adds: the last
+// of 256 blocks ended 10 us after the race; the adds of a block of 16 requests are made once:
+// greedy acceptance of 256 requests, k = 3: 35.1 -> 29.0 us; a 70B-shaped step of 256: 155.6 -> 150.3 us).
+//   Sampling: the requests' race segments and accept results; the best segment wins.
+//   Greedy acceptance (there is no race): the arg-max records of the k+1 target rows; the leading run
+//   of draft tokens that equal their row's arg-max is accepted, the arg-max after it emitted.
+__device__ __forceinline__ void final_role(const RejectParams &p, int item, RejectShared &sh)
 {
     const int tid = threadIdx.x;
-    const int row_t0 = uniform_load(p.cu_q_len, b);
-    const int k = uniform_load(p.cu_q_len, b + 1) - row_t0 - 1;
+    const int group = kThreads >> p.final_shift;   // threads per request
+    const int local = tid / group;                 // request of the block
+    const int li = tid % group;
+    const int b = (item << p.final_shift) + local;
+    const bool valid = b < p.B;
+    const bool greedy = p.mode == SPEC_ACCEPT_GREEDY;
+    const int segs = p.stat_segments;
+
+    // what does not depend on the other stages is fetched before the wait
+    const int row_t0 = valid ? p.cu_q_len[b] : 0;
+    const int k = valid ? p.cu_q_len[b + 1] - row_t0 - 1 : 0;
     const int row_d0 = row_t0 - b;
-    const int nstat = (k + 1) * p.stat_segments;
-    const bool ok = wait_all(p, [&] {
-        bool mine = true;
-        for (int i = tid; i < nstat; i += kThreads) {
-            const int ri = i / p.stat_segments;
-            const int sg = i - ri * p.stat_segments;
-            const unsigned long long *st = p.stats + 3 * ((size_t)(row_t0 + ri) * p.stat_segments + sg);
-            const unsigned long long w0 = fetch_u64(st), w1 = fetch_u64(st + 1);
-            mine = mine && tagged_ok(w0, p.generation) && tagged_ok(w1, p.generation);
-            sh.seg_off[ri][sg] = __uint_as_float((uint32_t)w0);
-            sh.seg_sum[ri][sg] = (double)(uint32_t)w1;   // the id, exactly
-        }
-        return mine;
-    });
-    if (!ok) {
-        abandon_request(p, b);
-        return;
+    const int token = li < k ? p.draft_tokens[row_d0 + li] : 0;
+    const int kv_len = (valid && li == 0 && p.new_kv_len != nullptr) ? p.kv_len[b] : 0;
+    if (tid < kMaxFinalGroup) {
+        sh.fin_ready[tid] = 1;
+        sh.fin_need[tid] = 0;
     }
-    if (tid <= k) {
-        float best = -INFINITY;
-        int best_id = 0x7FFFFFFF;
-        for (int sg = 0; sg < p.stat_segments; ++sg) {   // segments in rising id order: > keeps the lowest id
-            const float v = sh.seg_off[tid][sg];
-            const int id = (int)sh.seg_sum[tid][sg];
-            if (v > best || (v == best && id < best_id)) { best = v; best_id = id; }
-        }
-        sh.lse2[tid] = (double)(best_id == 0x7FFFFFFF ? 0 : best_id);
-    }
+    if (tid < 2) sh.fin_count[tid] = 0;
     __syncthreads();
-    if (tid == 0) {
-        int m = 0;
-        while (m < k && p.draft_tokens[row_d0 + m] == (int)sh.lse2[m]) ++m;
-        const int next = (int)sh.lse2[m];
-        p.accepted_len[b] = m;
-        p.next_token[b] = next;
-        if (p.new_kv_len != nullptr) p.new_kv_len[b] = p.kv_len[b] - (k - m);
-        if (p.draft_next_len != nullptr) p.draft_next_len[b] = (k > 0 && m == k) ? 2 : 1;
-        if (p.out_tokens != nullptr) {
-            int32_t *row = p.out_tokens + (size_t)b * (SPEC_K_MAX + 1);
-            for (int i = 0; i <= SPEC_K_MAX; ++i)
-                row[i] = i < m ? p.draft_tokens[row_d0 + i] : (i == m ? next : -1);
-        }
-        atomicAdd(&p.counters[0], (unsigned long long)k);
-        atomicAdd(&p.counters[1], (unsigned long long)m);
-        atomicAdd(&p.counters[2], (unsigned long long)(m + 1 < k ? m + 1 : k));
-        atomicAdd(&p.counters[3], (unsigned long long)(m + 1));
-        atomicAdd(&p.counters[5], 1ull);
-        count_bad_draft_tokens(p, row_d0, k);
-    }
-    // clear this request's tags
-    for (int i = tid; i < 2 * nstat; i += kThreads) {
-        const int rec = i >> 1;
-        publish_u64(p.stats + 3 * ((size_t)row_t0 * p.stat_segments + rec) + (i & 1), 0ull);
-    }
-}
 
-// Last stage of request b (one item per request, after all race items):
-// waits (bounded) for the request's race segments, picks the winner, writes the
-// outputs and counters, and clears the request's tags so that a replay of the
-// same launch (HIP graph) starts clean.
-__device__ __forceinline__ void final_role(const RejectParams &p, int b, RejectShared &sh)
-{
-    if (p.mode == SPEC_ACCEPT_GREEDY) {
-        greedy_final(p, b, sh);
-        return;
-    }
-    const int tid = threadIdx.x;
+    // poll and fetch in one: every word carries its own tag
     unsigned long long *part = p.race_partial + 2 * (size_t)b * p.race_segments;
-    // poll and fetch in one: the race partials (race_segments <= 64: wavefront 0 holds
-    // them all) and the accept chain's result
+    unsigned long long *rec_t = p.stats + kStatWords * ((size_t)row_t0 * segs);   // target rows, then (sampling) draft rows
     float best_score = -1.0f;
     int best_id = 0x7FFFFFFF;
     uint32_t info = 0;
+    float *rec_value = &sh.seg_off[0][0] + local * (SPEC_K_MAX + 1) * segs;   // (2^final_shift * segs <= kMaxStatSegments)
+    double *rec_id = &sh.seg_sum[0][0] + local * (SPEC_K_MAX + 1) * segs;
+    bool mine = true;
     const bool ok = wait_all(p, [&] {
-        bool mine = true;
-        if (tid < p.race_segments) {
-            const unsigned long long w0 = fetch_u64(part + 2 * tid), w1 = fetch_u64(part + 2 * tid + 1);
-            mine = tagged_ok(w0, p.generation) && tagged_ok(w1, p.generation);
-            best_score = __uint_as_float((uint32_t)w0);
-            best_id = (int)(uint32_t)w1;
+        mine = true;
+        if (!valid) return true;
+        if (greedy) {
+            for (int i = li; i < (k + 1) * segs; i += group) {
+                const unsigned long long w0 = fetch_u64(rec_t + kStatWords * i), w1 = fetch_u64(rec_t + kStatWords * i + 1);
+                mine = mine && tagged_ok(w0, p.generation) && tagged_ok(w1, p.generation);
+                rec_value[i] = __uint_as_float((uint32_t)w0);
+                rec_id[i] = (double)(uint32_t)w1;   // the id, exactly
+            }
+            return mine;
         }
-        if (tid == 0) {
+        best_score = -1.0f;
+        best_id = 0x7FFFFFFF;
+        for (int i = li; i < p.race_segments; i += group) {   // segments in rising id order: > keeps the lowest id
+            const unsigned long long w0 = fetch_u64(part + 2 * i), w1 = fetch_u64(part + 2 * i + 1);
+            mine = mine && tagged_ok(w0, p.generation) && tagged_ok(w1, p.generation);
+            const float score = __uint_as_float((uint32_t)w0);
+            if (score > best_score) {
+                best_score = score;
+                best_id = (int)(uint32_t)w1;
+            }
+        }
+        if (li <= SPEC_K_MAX) {
             const unsigned long long wi = fetch_u64(p.race_info + b);
             mine = mine && tagged_ok(wi, p.generation);
             info = (uint32_t)wi;
         }
         return mine;
     });
-    if (!ok) {
-        abandon_request(p, b);
-        return;
+    if (!ok) {   // the same for the whole block: find the requests that are complete all the same
+        if (!mine) sh.fin_ready[local] = 0;
+        __syncthreads();
     }
-    if (tid == 0) sh.m = (int)info;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const float os = __shfl_xor(best_score, o);
-        const int oi = __shfl_xor(best_id, o);
-        if (os > best_score || (os == best_score && oi < best_id)) { best_score = os; best_id = oi; }
-    }
-    if (tid == 0) { sh.best_score[0] = best_score; sh.best_id[0] = best_id; }
-    __syncthreads();
-    float win_score = sh.best_score[0];
-    int win_id = sh.best_id[0];
-    info = (uint32_t)sh.m;
-    __syncthreads();
-    const int m = (int)(info & 0xFFu), k = (int)((info >> 8) & 0xFFu), near = (int)(info >> 16);
-    const int row_t0 = uniform_load(p.cu_q_len, b);
-    const int row_d0 = row_t0 - b;
-    if (!(win_score > 0.0f)) {
+
+    // the first lanes of a request's threads (all in one wavefront) hold its result
+    const int lane = tid % kWave;
+    int m, near = 0, win_id;
+    if (greedy) {
+        int id = 0;
+        if (valid && li <= k) {
+            float best = -INFINITY;
+            id = 0x7FFFFFFF;
+            for (int sg = 0; sg < segs; ++sg) {   // segments in rising id order: > keeps the lowest id
+                const float v = rec_value[li * segs + sg];
+                const int vid = (int)rec_id[li * segs + sg];
+                if (v > best || (v == best && vid < id)) { best = v; id = vid; }
+            }
+            if (id == 0x7FFFFFFF) id = 0;
+        }
+        const int first = lane - li;   // (meaningful in the wavefront that holds li = 0 .. k)
+        const unsigned long long equal = __builtin_amdgcn_ballot_w64(li < k && token == id);
+        m = __builtin_ctzll(~(equal >> (first & (kWave - 1))));   // (bit k of the request is clear)
+        win_id = __shfl(id, (first + m) & (kWave - 1));
+    } else {
+        const int width = group < kWave ? group : kWave;
+        for (int o = width / 2; o > 0; o >>= 1) {
+            const float os = __shfl_xor(best_score, o);
+            const int oi = __shfl_xor(best_id, o);
+            if (os > best_score || (os == best_score && oi < best_id)) { best_score = os; best_id = oi; }
+        }
+        m = (int)(info & 0xFFu);
+        near = (int)(info >> 16);
+        win_id = best_id;
         // p - q has no positive entry (p == q to rounding): draw from p instead
-        if (!accept_phase(p, b, sh, false)) {
-            abandon_request(p, b);
-            return;
+        const bool need = valid && li == 0 && sh.fin_ready[local] && !(best_score > 0.0f);
+        if (need) sh.fin_need[local] = 1;
+        if (__syncthreads_or(need ? 1 : 0)) {
+            for (int r = 0; r < (1 << p.final_shift); ++r) {
+                if (!sh.fin_need[r]) continue;   // (the same for the whole block)
+                const int rb = (item << p.final_shift) + r;
+                if (!accept_phase(p, rb, sh, false)) {
+                    if (tid == 0) sh.fin_ready[r] = 0;
+                    __syncthreads();
+                    continue;
+                }
+                RaceRows rr = race_rows(p, rb, sh);
+                rr.drow = nullptr;
+                rr.corr_d = rr.off_d = 0.0f;
+                rr.exclude = -1;
+                const StepWords step = philox_step_words(p);
+                float score = -1.0f;
+                int id = 0x7FFFFFFF;
+                for (int g0 = 0; g0 < p.V >> 2; g0 += kRacePart) {
+                    race_variates(p, step, rb, g0, p.V >> 2, sh);
+                    race_part(rr, g0, p.V >> 2, sh, score, id);
+                }
+                race_winner(score, id, sh);
+                if (tid == 0) sh.fin_id[r] = id;
+                __syncthreads();
+            }
+            if (sh.fin_need[local]) win_id = sh.fin_id[local];
         }
-        RaceRows rr = race_rows(p, b, sh);
-        rr.drow = nullptr;
-        rr.corr_d = rr.off_d = 0.0f;
-        rr.exclude = -1;
-        const StepWords step = philox_step_words(p);
-        win_score = -1.0f;
-        win_id = 0x7FFFFFFF;
-        for (int g0 = 0; g0 < p.V >> 2; g0 += kRacePart) {
-            race_variates(p, step, b, g0, p.V >> 2, sh);
-            race_part(rr, g0, p.V >> 2, sh, win_score, win_id);
+    }
+
+    const bool ready = sh.fin_ready[local] != 0;
+    if (valid && li <= SPEC_K_MAX) {
+        if (p.out_tokens != nullptr)
+            p.out_tokens[(size_t)b * (SPEC_K_MAX + 1) + li] = !ready ? -1 : (li < m ? token : (li == m ? win_id : -1));
+        if (ready && li < k && (unsigned)token >= (unsigned)p.V) atomicAdd(&sh.fin_count[1], 1u << 8);   // an input error
+        if (li == 0) {
+            p.accepted_len[b] = ready ? m : -1;
+            p.next_token[b] = ready ? win_id : -1;
+            if (p.new_kv_len != nullptr) p.new_kv_len[b] = ready ? kv_len - (k - m) : -1;
+            if (p.draft_next_len != nullptr) p.draft_next_len[b] = !ready ? -1 : ((k > 0 && m == k) ? 2 : 1);
+            if (ready) {   // four sums of at most 16 * 8 in one word
+                atomicAdd(&sh.fin_count[0], (uint32_t)k | (uint32_t)m << 8 | (uint32_t)(m + 1 < k ? m + 1 : k) << 16 | (uint32_t)near << 24);
+                atomicAdd(&sh.fin_count[1], 1u);
+            } else {       // a wait ran out (never in a healthy launch): the request is counted here only
+                atomicAdd(&p.counters[7], 1ull);
+            }
         }
-        race_winner(win_score, win_id, sh);
     }
-    if (tid == 0) {
-        p.accepted_len[b] = m;
-        p.next_token[b] = win_id;
-        if (p.new_kv_len != nullptr) p.new_kv_len[b] = p.kv_len[b] - (k - m);
-        if (p.draft_next_len != nullptr) p.draft_next_len[b] = (k > 0 && m == k) ? 2 : 1;
-        if (p.out_tokens != nullptr) {
-            int32_t *row = p.out_tokens + (size_t)b * (SPEC_K_MAX + 1);
-            for (int i = 0; i <= SPEC_K_MAX; ++i)
-                row[i] = i < m ? p.draft_tokens[row_d0 + i] : (i == m ? win_id : -1);
-        }
-        atomicAdd(&p.counters[0], (unsigned long long)k);
-        atomicAdd(&p.counters[1], (unsigned long long)m);
-        atomicAdd(&p.counters[2], (unsigned long long)(m + 1 < k ? m + 1 : k));
-        atomicAdd(&p.counters[3], (unsigned long long)(m + 1));
-        atomicAdd(&p.counters[4], (unsigned long long)near);
-        atomicAdd(&p.counters[5], 1ull);
-        count_bad_draft_tokens(p, row_d0, k);
+    __syncthreads();
+    if (tid < 7) {
+        const uint32_t sums = sh.fin_count[0], n = sh.fin_count[1] & 0xFFu;
+        uint32_t add = tid == 5 ? n : sh.fin_count[1] >> 8;
+        if (tid < 3) add = (sums >> (8 * tid)) & 0xFFu;
+        if (tid == 3) add = ((sums >> 8) & 0xFFu) + n;
+        if (tid == 4) add = sums >> 24;
+        if (add != 0) atomicAdd(&p.counters[tid], (unsigned long long)add);
     }
-    // clear this request's tags
-    const int nstat = (p.mode == SPEC_ACCEPT_SAMPLE ? 2 * k + 1 : k + 1) * p.stat_segments;
-    for (int i = tid; i < 3 * nstat; i += kThreads) {
-        const int rec = i / 3;
-        const int ri = rec / p.stat_segments;
-        const int sg = rec - ri * p.stat_segments;
-        const int row = ri <= k ? row_t0 + ri : p.T + row_d0 + (ri - k - 1);
-        publish_u64(p.stats + 3 * ((size_t)row * p.stat_segments + sg) + (i - 3 * rec), 0ull);
+    if (!valid || !ready) return;
+    // clear the request's tags
+    for (int i = li; i < kStatWords * (k + 1) * segs; i += group) publish_u64(rec_t + i, 0ull);
+    if (greedy) return;
+    if (p.mode == SPEC_ACCEPT_SAMPLE) {
+        unsigned long long *rec_d = p.stats + kStatWords * ((size_t)(p.T + row_d0) * segs);
+        for (int i = li; i < kStatWords * k * segs; i += group) publish_u64(rec_d + i, 0ull);
     }
-    if (tid < 2 * p.race_segments) publish_u64(part + tid, 0ull);
-    if (tid == 0) publish_u64(p.race_info + b, 0ull);
+    for (int i = li; i < 2 * p.race_segments; i += group) publish_u64(part + i, 0ull);
+    if (li == 0) publish_u64(p.race_info + b, 0ull);
 }
 
 // ===========================================================================
@@ -1808,11 +1798,12 @@ hipError_t launch_step_fused(const AttnParams *attn, int row_tiles, const Reject
     int n_stat = 0, n_attn = 0, n_race = 0;
     if (reject != nullptr) {
         rp = *reject;
-        if (rp.stat_segments > kMaxStatSegments || rp.race_segments > kWave || rp.spin_limit < 1)
+        if (rp.stat_segments > kMaxStatSegments || rp.race_segments > kWave || rp.spin_limit < 1 ||
+            rp.final_shift < 0 || rp.final_shift > kMaxFinalShift || (rp.stat_segments << rp.final_shift) > kMaxStatSegments)
             return hipErrorInvalidValue;
         if (rp.mode == SPEC_ACCEPT_GREEDY) rp.race_segments = 0;   // no race stage
         n_stat = (rp.mode == SPEC_ACCEPT_SAMPLE ? 2 * rp.T - rp.B : rp.T) * rp.stat_segments;
-        n_race = rp.B * rp.race_segments + rp.B;   // race segments, then one final item per request
+        n_race = rp.B * rp.race_segments + final_items(rp);   // race segments, then the final items
     }
     if (attn != nullptr) {
         ap = *attn;

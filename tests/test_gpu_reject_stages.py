@@ -69,3 +69,31 @@ def test_race_of_one_segment_at_part_edges(harness, tuning, V, mode):
     if mode == sv.ACCEPT_POINT_DRAFT:
         ref = oracle.reject_onehot(w.target_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
     check_reject(w, ds.results(), ref=ref)
+
+
+# the final stage takes 1, 2, 4, 8 or 16 requests per block, depending on their number
+@pytest.mark.parametrize("mode", [sv.ACCEPT_SAMPLE, sv.ACCEPT_GREEDY, sv.ACCEPT_POINT_DRAFT], ids=["sample", "greedy", "point"])
+@pytest.mark.parametrize("B", [1, 15, 16, 33, 67, 131], ids=lambda b: "B%d" % b)
+def test_requests_grouped_in_the_final_stage(harness, B, mode):
+    print("case final groups", B, mode, flush=True)
+    rng = np.random.default_rng(B)
+    w = _logits_only(B, 2052, rng.integers(0, 9, size=B), seed=B)
+    if mode == sv.ACCEPT_GREEDY:
+        hit = rng.random(w.T - B) < 0.7
+        rows = np.concatenate([np.arange(w.cu_q_len[b], w.cu_q_len[b + 1] - 1) for b in range(B)])
+        w.draft_tokens = np.where(hit, w.target_logits[rows].argmax(1), w.draft_tokens).astype(np.int32)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=mode)
+    for _ in range(2):   # the second call finds the first one's records cleared or out of date
+        ds.counters.zero_()
+        ds.out_tokens.fill_(-7)
+        ds.run_reject()
+        res = ds.results()
+        if mode == sv.ACCEPT_GREEDY:
+            ref = oracle.reject_greedy(w.target_logits, w.draft_tokens, w.cu_q_len)
+            for name in ("accepted_len", "next_token", "out_tokens", "counters"):
+                np.testing.assert_array_equal(res[name], getattr(ref, name))
+        else:
+            ref = None
+            if mode == sv.ACCEPT_POINT_DRAFT:
+                ref = oracle.reject_onehot(w.target_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
+            check_reject(w, res, ref=ref, max_excluded=1)
