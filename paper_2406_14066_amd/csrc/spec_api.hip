@@ -502,6 +502,7 @@ struct StepPlan {
     AttnPlan apl;
     RejectPlan rpl;
     UnitOrder order;
+    size_t workspace_bytes = 0;     // what callers are told: enough for this call and for its rejection half alone
     // (for telling a hash collision from a hit)
     int32_t B = 0, T = 0, V = 0;
 };
@@ -587,6 +588,9 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     }
     if (r != nullptr)
         e.rpl = plan_reject(r, base, tu, (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0);
+    e.workspace_bytes = base + (r != nullptr ? e.rpl.total_bytes : 0);
+    // (a workspace made for the step also serves its rejection half alone, which may race in more segments)
+    if (a != nullptr && r != nullptr) e.workspace_bytes = std::max(e.workspace_bytes, plan_reject(r, 0, tu).total_bytes);
     return e;
 }
 
@@ -748,7 +752,7 @@ size_t spec_verify_workspace_bytes(const spec_attn_args *attn, const spec_reject
     if (attn != nullptr && reject != nullptr && (attn->B != reject->B || attn->T != reject->T)) return 0;
     const StepPlan &plan = plan_for(attn, reject);
     if (plan.status != SPEC_OK) return 0;
-    return (attn != nullptr ? plan.apl.total_bytes : 0) + (reject != nullptr ? plan.rpl.total_bytes : 0);
+    return plan.workspace_bytes;
 }
 
 spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args *reject, spec_plan_info *info)
@@ -779,7 +783,6 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
             info->attn_blocks = pl.max_chunks * attn->Hq * attn->T;
             info->launches = pl.max_chunks > 1 ? 2 : 1;
         }
-        info->workspace_bytes += pl.total_bytes;
     }
     if (reject != nullptr) {
         const RejectPlan &pl = plan.rpl;
@@ -790,8 +793,8 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
         info->reject_blocks = rows * pl.stat_segments + reject->B * info->race_segments +
                               ((reject->B + (1 << pl.final_shift) - 1) >> pl.final_shift);
         if (attn == nullptr || info->attn_path != SPEC_PATH_MFMA) info->launches += 1;
-        info->workspace_bytes += pl.total_bytes;
     }
+    info->workspace_bytes = plan.workspace_bytes;
     return SPEC_OK;
 }
 

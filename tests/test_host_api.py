@@ -406,3 +406,14 @@ def test_plan_is_reused_for_an_unchanged_shape_and_follows_a_changed_one():
     bad = np.array([100, 200, 300, 400, 500, 2], dtype=np.int32)          # kv_len < q_len: the cached plan must not hide it
     a.host_kv_len = bad.ctypes.data
     assert sv.lib().spec_verify_step(C.byref(a), C.byref(r), FAKE, 1 << 30, None) == sv.SPEC_EINVAL
+
+
+@pytest.mark.parametrize("B", [1, 4, 17, 48, 96, 256, 600])
+@pytest.mark.parametrize("V", [1024, 32000, 128256])
+def test_a_workspace_for_the_step_serves_either_half_alone(B, V):
+    q_len = (3,) * B
+    a = _attn(B=B, Hq=8, Hkv=2, kv_len=(300,) * B, q_len=q_len, max_blocks=32)
+    r = _reject(B=B, V=V, q_len=q_len)
+    step = sv.spec_verify_workspace_bytes(a, r)
+    assert step >= sv.spec_verify_workspace_bytes(a, None) and step >= sv.spec_verify_workspace_bytes(None, r)
+    assert sv.spec_verify_plan(a, r)["workspace_bytes"] == step
