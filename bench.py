@@ -207,7 +207,7 @@ def measure(w, args, mode, with_graph, token_major=False):
 
     kernel_us = {k: (1e3 * ms / n if n else None) for k, (ms, n) in kt.items()}
     # the step is the one launch of the step kernel (plus a merge launch only when a request has more than 64
-    # chunks); on the generic path (fp32) it is two or three launches: attention, a merge if a request is split,
+    # chunks); with the scalar kernels (a test switch) it is two or three launches: attention, a merge if a request is split,
     # rejection sampling
     step_us = sum(kernel_us[k] or 0.0 for k in ("step", "attn_generic", "attn_combine", "reject"))
     achieved = step_bytes / (step_us * 1e-6) / 1e9
@@ -236,7 +236,7 @@ def brief(mm, traffic):
         "achieved_GBps": mm["achieved"],
         "frac": mm["achieved"] / HBM_PEAK_GBS,
         "traffic": traffic,
-        "attention_path": {1: "matrix instructions", 2: "generic"}[mm["plan"]["attn_path"]],
+        "attention_path": {1: "matrix instructions", 2: "fp32"}[mm["plan"]["attn_path"]],
         "kv_layout": "token-major pages" if mm["layout"] == 0 else "matrix-operand tiles",
         "row_tiles": mm["plan"]["row_tiles"], "row_groups": mm["plan"]["row_groups"],
         "chunk_tokens": mm["plan"]["chunk_tokens"], "launches": mm["plan"]["launches"],

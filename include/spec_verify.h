@@ -39,8 +39,8 @@
  *     9 * 16 fused rows per KV head) and both head dims: fastest with pages in
  *     the SPEC_KV_MFMA layout; token-major pages take the same kernel, 3 to 8%
  *     slower up to 48 fused rows and about 20% slower beyond (V is transposed
- *     through LDS inside the kernel).  fp32 runs on plain, untuned kernels (two
- *     or three launches).  spec_verify_plan tells which path a call takes.
+ *     through LDS inside the kernel).  fp32 (token-major pages) has a one-launch
+ *     kernel of its own.  spec_verify_plan tells which path a call takes.
  */
 #ifndef SPEC_VERIFY_H
 #define SPEC_VERIFY_H
@@ -252,13 +252,14 @@ spec_status spec_verify_step_static(const spec_attn_args *attn, const spec_rejec
  * callers and tests that want to know which kernel a shape takes.
  */
 #define SPEC_PATH_NONE 0
-#define SPEC_PATH_MFMA 1     /* matrix-instruction attention inside the one-launch step kernel */
-#define SPEC_PATH_GENERIC 2  /* scalar attention kernel, plus a merge kernel when a request is split (fp32) */
+#define SPEC_PATH_MFMA 1     /* bf16: matrix-instruction attention inside the one-launch step kernel */
+#define SPEC_PATH_GENERIC 2  /* fp32, in a one-launch kernel too; either type with SPEC_VERIFY_FORCE_GENERIC=1: the scalar
+                                attention kernel, plus a merge kernel when a request is split (launches tells them apart) */
 typedef struct {
     int32_t attn_path;       /* SPEC_PATH_* */
-    int32_t row_tiles;       /* 16-row tiles of query rows per wavefront (matrix path, 1..3) */
+    int32_t row_tiles;       /* 16-row tiles of query rows per wavefront (1..3) */
     int32_t row_groups;      /* groups of wavefronts inside an attention block (1, 2 or 4): with more than
-                                48 fused rows per KV head the block's wavefronts split the rows instead of
+                                48 (fp32: 32) fused rows per KV head the block's wavefronts split the rows instead of
                                 the pages and read every page side by side, so K and V still cross the
                                 memory interface once */
     int32_t chunk_tokens;    /* bound of the tokens per chunk of the split over the KV length */
@@ -393,7 +394,7 @@ int32_t spec_argmax_goodput(const spec_goodput_args *args, double *goodput_per_k
 #define SPEC_NUM_KERNELS 5
 #define SPEC_KERNEL_STEP 0          /* the whole step in one launch (attention + rejection sampling) */
 #define SPEC_KERNEL_ATTN 1          /* attention-only launch of the matrix-instruction kernel */
-#define SPEC_KERNEL_ATTN_GENERIC 2  /* generic attention over one KV chunk (fp32 / token-major path) */
+#define SPEC_KERNEL_ATTN_GENERIC 2  /* scalar attention over one KV chunk (SPEC_VERIFY_FORCE_GENERIC=1) */
 #define SPEC_KERNEL_ATTN_COMBINE 3  /* merge of the generic kernel's chunk partials */
 #define SPEC_KERNEL_REJECT 4        /* rejection-sampling-only launch */
 spec_status spec_profile_begin(int32_t max_launches);

@@ -4,9 +4,10 @@
 //
 //   attn_generic_kernel   any dtype (fp32, bf16) and page layout, scalar fp32
 //                         arithmetic: one block per (KV chunk, query head,
-//                         query row), one thread per key of the chunk.  This is
-//                         the fp32 path and the fallback for shapes the
-//                         matrix-instruction kernel does not take.
+//                         query row), one thread per key of the chunk.  Every
+//                         shape has a matrix-instruction kernel; this one is the
+//                         plain implementation that SPEC_VERIFY_FORCE_GENERIC=1
+//                         selects, which the tests compare those with.
 //   attn_combine_kernel   merges the per-chunk partial results of either
 //                         attention kernel: out = sum_c w_c acc_c / sum_c w_c l_c,
 //                         w_c = 2^(m_c - max_c m_c).  Requests with one chunk are

@@ -31,7 +31,7 @@ struct AttnPlan {
     int32_t chunk_tokens;
     int32_t max_chunks;
     int32_t max_q_len;
-    int32_t use_mfma;      // 1: bf16 matrix-instruction kernel, 0: generic kernel
+    int32_t use_mfma;      // 1: matrix-instruction kernels (one launch for the step), 0: generic kernel
     int32_t row_tiles;     // 16-row tiles of query rows per wave group (mfma kernel, 1..3)
     int32_t row_groups;    // wave groups per attention block (1, 2 or 4): row_groups * row_tiles tiles cover max_q_len * (Hq/Hkv) rows
     int32_t capacity_tokens;  // longest kv_len the plan allows for (chunk_tokens * max_chunks, capped by the bucket)
@@ -55,12 +55,14 @@ struct AttnParams {
     int32_t attn_first_limit;     // attention blocks go first in the grid when there are at most this many
     float reject_span;            // fraction of the attention items among which the rejection items are spread in the grid
     int32_t split_p;              // feed the softmax weights to the PV product as bf16 high + low parts
-    int32_t reserved;
+    int32_t f32;                  // fp32 queries and cache (token-major pages)
     int32_t reject_even_xcds;     // fused step: rejection blocks only at even positions of the grid's rows of 8 (see GridSplit)
     int32_t reject_even_limit;    // ... when there are at most this many attention blocks (the number of compute units)
     int32_t capacity_tokens;      // a request whose device-side kv_len exceeds this is skipped and counted in *errors
     int32_t row_groups;           // see AttnPlan
     int32_t reject_first_limit;   // fused step: up to this many rejection items go first in the grid (0: never)
+    int32_t row_tiles;            // see AttnPlan
+    int32_t reserved;
     const void *q, *k_cache, *v_cache;
     const int32_t *block_table, *kv_len, *cu_q_len;
     float *out;
@@ -69,7 +71,7 @@ struct AttnParams {
     unsigned long long *tickets;  // [B * Hkv]
     unsigned long long *errors;   // findings of the device-side input checks are added here (may be null)
 };
-static_assert(sizeof(AttnParams) == 22 * 4 + 11 * 8, "AttnParams has padding");
+static_assert(sizeof(AttnParams) == 24 * 4 + 11 * 8, "AttnParams has padding");
 
 // What the kernels check of a request before they use its lengths as loop bounds and indices.
 __host__ __device__ inline bool request_lengths_ok(int kv_len, int q_len, int capacity_tokens, int max_blocks_per_req)
@@ -143,7 +145,7 @@ struct LaunchEvents {
 };
 
 // One launch for the whole step (either half may be absent).  `attn` needs the
-// matrix-instruction path (bf16, either page layout, d = 128 or 64; row_tiles tiles per wave
+// matrix-instruction path (bf16 with either page layout or fp32, d = 128 or 64; row_tiles tiles per wave
 // group, ap.row_groups wave groups per block).  `order` may be null.
 int step_attn_items(const AttnParams &ap);   // attention blocks of the launch
 // attention items per chunk index: one per (request, KV head), padded to whole rows of 8 blocks (one per XCD) when requests are split

@@ -324,9 +324,9 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
     pl.max_q_len = max_q;
     const int group = a->Hq / a->Hkv;
     const int tiles = (max_q * group + 15) / 16;
-    // bf16 runs on the matrix-instruction kernel, in either page layout (token-major pages have
-    // their V transposed through LDS)
-    pl.use_mfma = (a->qkv_dtype == SPEC_BF16 && !tu.force_generic) ? 1 : 0;
+    // both types run on matrix-instruction kernels, bf16 in either page layout (token-major pages have
+    // their V transposed through LDS), fp32 on token-major pages, the only ones it has
+    pl.use_mfma = tu.force_generic ? 0 : 1;
     pl.row_groups = 1;
     pl.row_tiles = tiles;
     if (pl.use_mfma) {
@@ -334,7 +334,8 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
         // per KV head the block's four wavefronts share the pages between them; with more (long
         // drafts on wide query groups) they form 2 or 4 groups that each own a share of the rows and
         // walk all pages, reading them side by side.
-        pl.row_groups = tiles <= 3 ? 1 : (tiles <= 6 ? 2 : 4);
+        const bool f32 = a->qkv_dtype == SPEC_F32;   // (twice the registers per tile: two tiles per wavefront)
+        pl.row_groups = tiles <= (f32 ? 2 : 3) ? 1 : (tiles <= (f32 ? 4 : 6) ? 2 : 4);
         pl.row_tiles = (tiles + pl.row_groups - 1) / pl.row_groups;
         if (pl.row_groups > 1 && pl.row_tiles < 2) pl.row_tiles = 2;
         // Splitting costs (partials, a merge, more block start-ups), so the longest request is split
@@ -620,6 +621,8 @@ AttnParams attn_params(const spec_attn_args *a, const AttnPlan &pl, char *ws, in
     p.chunk_tokens = pl.chunk_tokens; p.max_chunks = pl.max_chunks;
     p.capacity_tokens = pl.capacity_tokens;
     p.row_groups = pl.row_groups;
+    p.row_tiles = pl.row_tiles;
+    p.f32 = a->qkv_dtype == SPEC_F32 ? 1 : 0;
     const double scale = a->softmax_scale > 0.0f ? (double)a->softmax_scale : 1.0 / sqrt((double)a->d);
     p.scale_log2 = (float)(scale * kLog2eD);
     p.q = a->q; p.k_cache = a->k_cache; p.v_cache = a->v_cache;
@@ -768,7 +771,7 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
     if (plan.status != SPEC_OK) return plan.status;
     if (attn != nullptr) {
         const AttnPlan &pl = plan.apl;
-        info->attn_path = pl.use_mfma ? SPEC_PATH_MFMA : SPEC_PATH_GENERIC;
+        info->attn_path = pl.use_mfma && attn->qkv_dtype == SPEC_BF16 ? SPEC_PATH_MFMA : SPEC_PATH_GENERIC;
         info->row_tiles = pl.row_tiles;
         info->row_groups = pl.row_groups;
         info->chunk_tokens = pl.chunk_tokens;
@@ -792,7 +795,7 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
         const int rows = reject->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * reject->T - reject->B : reject->T;
         info->reject_blocks = rows * pl.stat_segments + reject->B * info->race_segments +
                               ((reject->B + (1 << pl.final_shift) - 1) >> pl.final_shift);
-        if (attn == nullptr || info->attn_path != SPEC_PATH_MFMA) info->launches += 1;
+        if (attn == nullptr || !plan.apl.use_mfma) info->launches += 1;
     }
     info->workspace_bytes = plan.workspace_bytes;
     return SPEC_OK;

@@ -46,6 +46,8 @@
 //   that its rounding does not limit the result.  All q_len * (Hq/Hkv) query rows
 //   sharing a KV head are fused into the N dimension: K and V are read once.
 //
+// fp32 caches take a kernel of their own with the same grid (f32_step_kernel, attn_f32_role).
+//
 // Rejection arithmetic: the streaming part is fp32; what happens once per row or
 // per decision (segment sums, log-sum-exp, p/q of the draft token, the comparison
 // with u) is fp64.
@@ -1058,20 +1060,22 @@ struct OrderTable {
 constexpr int head_dim_of(int VAR) { return (VAR == 3 || VAR == 4) ? 64 : kD; }
 constexpr bool token_major_of(int VAR) { return VAR == 2 || VAR == 4; }
 
-template <int NT, int WG, int VAR>
-__device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order, int item,
-                                          AttnShared<NT, WG, token_major_of(VAR), head_dim_of(VAR)> &sh)
+// What one attention block works on, and each thread's place in it (see attn_begin).
+struct AttnWork {
+    int tid, wave, lane, n16, g;   // lane = 16 g + n16
+    int grp, pw;                   // this wavefront's row group, and its place in the page walk of the group
+    int kvh, unit, chunk, nchunks;
+    int L, row0, q_len, group;     // group: query heads per KV head
+    int rows, row_lo, grp_rows;    // fused query rows of the block; first row and number of rows of this wavefront's group
+    int tok0, npages;
+    int bt;                        // block-table entries of this wavefront's pages, one per lane (-1: outside the pool)
+    int my_pages;
+};
+
+// The block's place in the work: request, KV head, chunk, rows, pages.  False: nothing to do.
+template <int NT, int WG>
+__device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order, int item, AttnWork &w)
 {
-    constexpr bool SPLIT_P = VAR != 1;
-    constexpr bool TM = token_major_of(VAR);
-    constexpr int D = head_dim_of(VAR);
-    constexpr int KK = D / 32;                        // 32-dim steps of the score product = 1 KB loads per K or V page
-    constexpr int MT = D / 16;                        // 16-dim slices of the output
-    constexpr int kQStride = q_stride(D), kOStride = o_stride(D);
-    constexpr int kPageHeadBytes = SPEC_BLOCK_SIZE * D * 2;   // one (page, KV head) of K or of V: 4096 at D = 128
-    constexpr int QP = D / 8;                         // 16-byte pieces of a bf16 query row
-    constexpr int QI = (NT * WG * 16 * QP + kThreads - 1) / kThreads;   // ... of all the block's rows, per thread
-    constexpr int kVtRowBytes = vt_row_bytes(D), kVtWaveBytes = vt_wave_bytes(D);
     constexpr int PW = kWaves / WG;   // wavefronts that share the pages of a group between them
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1093,7 +1097,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     const int row_items = attn_row_items(p);
     const int chunk = item / row_items;
     const int place = item - chunk * row_items;
-    if (place >= n_units) return;   // padding
+    if (place >= n_units) return false;   // padding
     const int kvh = place % p.Hkv;
     int b = place / p.Hkv;   // rank in the order of the attention items
     if (order.n > 0) {
@@ -1115,10 +1119,10 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     // shorter than its own query rows) is left out and reported.
     if (!request_lengths_ok(L, q_len, p.capacity_tokens, p.max_blocks_per_req)) {
         if (chunk == 0 && kvh == 0 && tid == 0 && p.errors != nullptr) atomicAdd(p.errors, 1ull);
-        return;
+        return false;
     }
     const int nchunks = (L + p.chunk_tokens - 1) / p.chunk_tokens;   // <= max_chunks, since L <= capacity_tokens
-    if (chunk >= nchunks) return;
+    if (chunk >= nchunks) return false;
     // even chunks per request, page aligned (never longer than chunk_tokens)
     const int C = ((L + nchunks - 1) / nchunks + SPEC_BLOCK_SIZE - 1) & ~(SPEC_BLOCK_SIZE - 1);
     const int group = p.Hq / p.Hkv;
@@ -1143,6 +1147,229 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         if (bad_lanes != 0 && kvh == 0 && grp == 0 && p.errors != nullptr && lane == 0)
             atomicAdd(p.errors, (unsigned long long)__builtin_popcountll(bad_lanes));
     }
+
+    w.tid = tid; w.wave = wave; w.lane = lane; w.n16 = n16; w.g = g; w.grp = grp; w.pw = pw;
+    w.kvh = kvh; w.unit = unit; w.chunk = chunk; w.nchunks = nchunks;
+    w.L = L; w.row0 = row0; w.q_len = q_len; w.group = group;
+    w.rows = rows; w.row_lo = row_lo; w.grp_rows = grp_rows; w.tok0 = tok0; w.npages = npages; w.bt = bt;
+    // pages pw, pw + PW, ... (none for a group that has no rows of this request)
+    w.my_pages = (npages > pw && grp_rows > 0) ? (npages - pw + PW - 1) / PW : 0;
+    return true;
+}
+
+// The end of an attention block: merges its wavefronts, and writes the output rows (a request that is not
+// split) or publishes the chunk's partial results and, as the last chunk to finish, merges all of them.
+// acc[nt][mt] holds, per lane, four consecutive head dims of query row n16 of tile nt, the first of which
+// is dim_base(mt, g).
+template <int NT, int WG, int D, typename Shared, typename DimBase>
+__device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w, f32x4 (&acc)[NT][D / 16], float (&m_run)[NT],
+                                         float (&l_run)[NT], const int (&out_row)[NT], DimBase dim_base, Shared &sh)
+{
+    constexpr int MT = D / 16;
+    constexpr int kOStride = o_stride(D);
+    const int tid = w.tid, wave = w.wave, lane = w.lane, n16 = w.n16, g = w.g, grp = w.grp, pw = w.pw;
+    const int kvh = w.kvh, unit = w.unit, chunk = w.chunk, nchunks = w.nchunks, row0 = w.row0, group = w.group;
+    const int rows = w.rows, grp_rows = w.grp_rows;
+    // each lane summed its own four tokens per page: finish the row sums
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        l_run[nt] = sum_across_rows(l_run[nt]);
+    }
+
+    // merge the wavefronts of each group into the group's first one
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) sh.acc[buf][nt][mt][lane] = acc[nt][mt];
+            sh.m[buf][nt][lane] = m_run[nt];
+            sh.l[buf][nt][lane] = l_run[nt];
+        }
+    };
+    auto merge = [&](int buf) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const float mo = sh.m[buf][nt][lane];
+            const float lo = sh.l[buf][nt][lane];
+            const float mn = fmaxf(m_run[nt], mo);
+            const float wa = fast_exp2(m_run[nt] - mn);
+            const float wb = fast_exp2(mo - mn);
+            l_run[nt] = l_run[nt] * wa + lo * wb;
+            m_run[nt] = mn;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = acc[nt][mt] * wa + sh.acc[buf][nt][mt][lane] * wb;
+        }
+    };
+    if constexpr (WG == 1) {          // 2,3 -> 0,1 then 1 -> 0 (the last step below, by wavefront 0)
+        if (wave >= 2) put(wave - 2);
+        __syncthreads();
+        if (wave < 2) merge(wave);
+        __syncthreads();
+        if (wave == 1) put(0);
+        __syncthreads();
+    } else if constexpr (WG == 2) {   // 1 -> 0 and 3 -> 2
+        if (pw == 1) put(grp);
+        __syncthreads();
+        if (pw == 0) merge(grp);
+        __syncthreads();
+    }
+    const bool lead = pw == 0 && grp_rows > 0;   // this wavefront holds its group's result
+
+    if (nchunks == 1) {
+        if constexpr (WG == 1) {
+            // the only chunk of this (request, KV head): normalise, lay the tile out by rows in
+            // LDS, and let the whole block write the rows (16 bytes per thread, consecutive
+            // threads along a row)
+            if (wave == 0) {
+                merge(0);   // (its reads of the shared partials precede the writes below in program order)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const float inv = 1.0f / l_run[nt];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        *reinterpret_cast<f32x4 *>(sh.o + (nt * 16 + n16) * kOStride + dim_base(mt, g) * 4) = acc[nt][mt] * inv;
+                }
+            }
+            __syncthreads();
+            constexpr int OP = D / 4;   // 16-byte pieces of an fp32 output row
+            for (int piece = tid; piece < rows * OP; piece += kThreads) {
+                const int r = piece / OP, c = piece % OP;
+                const size_t rh = (size_t)(row0 + r / group) * p.Hq + kvh * group + r % group;
+                __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(sh.o + r * kOStride + c * 16),
+                                            reinterpret_cast<f32x4 *>(p.out + rh * D + c * 4));
+            }
+        } else if (lead) {
+            // several groups: each group's first wavefront writes its rows itself (a lane holds four
+            // consecutive head dims of one row per 16-dim slice)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                if (out_row[nt] < 0) continue;
+                const float inv = 1.0f / l_run[nt];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    __builtin_nontemporal_store(acc[nt][mt] * inv,
+                                                reinterpret_cast<f32x4 *>(p.out + (size_t)out_row[nt] * D + dim_base(mt, g)));
+            }
+        }
+        return;
+    }
+
+    if (WG == 1 ? wave == 0 : lead) {
+        if constexpr (WG == 1) merge(0);
+        // one partial per query row: acc[dim], running max, running sum
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (out_row[nt] < 0) continue;
+            const size_t slot = (size_t)out_row[nt] * p.max_chunks + chunk;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                unsigned long long *dst = reinterpret_cast<unsigned long long *>(p.ws_acc + slot * D + dim_base(mt, g));
+                publish_u64(dst + 0, pack_f32x2(acc[nt][mt][0], acc[nt][mt][1]));
+                publish_u64(dst + 1, pack_f32x2(acc[nt][mt][2], acc[nt][mt][3]));
+            }
+            if (g == 0)
+                publish_u64(reinterpret_cast<unsigned long long *>(p.ws_ml + slot * 2), pack_f32x2(m_run[nt], l_run[nt]));
+        }
+        writes_complete();  // the partials are in memory before the ticket is taken
+    }
+    if (!p.fused_combine) return;   // a separate combine launch merges the partials
+    if constexpr (WG > 1) __syncthreads();   // ... those of every group
+    if (tid == 0) {
+        unsigned long long *ticket = &p.tickets[unit];
+        const uint32_t before = ticket_arrive(ticket, p.generation);
+        const int last = (before + 1u == (uint32_t)nchunks) ? 1 : 0;
+        if (last) ticket_reset(ticket);
+        sh.last = last;
+    }
+    __syncthreads();
+    if (!sh.last) return;
+    order_after_ticket();
+
+    // Last chunk of this (request, KV head) to finish: merge all chunks in chunk order.
+    // Half a wavefront takes two query rows at a time (four head dims per lane) and eight
+    // chunks of each per pass; every load of a pass is issued before the first is used, so
+    // a pass costs one memory round trip.
+    constexpr int GROUP = 8;   // chunks merged per pass (16 per pass spill 200 to 340 bytes per lane)
+    constexpr int RB = NT >= 2 ? 2 : 1;   // rows in flight per half wavefront (one row tile: at most two passes anyway, and registers are tight)
+    const int half = lane >> 5, l32 = lane & 31;
+    const bool dims_on = 4 * l32 < D;   // (a head dim of 64 keeps half of the lanes busy)
+    for (int r0 = 2 * wave + half; r0 < rows; r0 += 2 * kWaves * RB) {
+        bool rv[RB];
+        size_t rh[RB];
+        const unsigned long long *ml[RB], *pa[RB];
+        float mx[RB], denom[RB];
+        f32x4 o[RB];
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            const int r = r0 + 2 * kWaves * j;
+            rv[j] = r < rows;
+            const int rr = rv[j] ? r : 0;
+            rh[j] = (size_t)(row0 + rr / group) * p.Hq + kvh * group + rr % group;
+            const size_t base = rh[j] * p.max_chunks;
+            ml[j] = reinterpret_cast<const unsigned long long *>(p.ws_ml) + base;
+            pa[j] = reinterpret_cast<const unsigned long long *>(p.ws_acc) + base * (D / 2) + 2 * l32;
+            mx[j] = kEmptyMax;
+            denom[j] = 0.0f;
+            o[j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        for (int c0 = 0; c0 < nchunks; c0 += GROUP) {
+            unsigned long long mlv[RB][GROUP], a0[RB][GROUP], a1[RB][GROUP];
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+#pragma unroll
+                for (int c = 0; c < GROUP; ++c) {
+                    const bool on = rv[j] && c0 + c < nchunks;
+                    mlv[j][c] = on ? fetch_u64(ml[j] + c0 + c) : pack_f32x2(kEmptyMax, 0.0f);
+                    a0[j][c] = on && dims_on ? fetch_u64(pa[j] + (size_t)(c0 + c) * (D / 2)) : 0ull;
+                    a1[j][c] = on && dims_on ? fetch_u64(pa[j] + (size_t)(c0 + c) * (D / 2) + 1) : 0ull;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                float gmx = mx[j];
+#pragma unroll
+                for (int c = 0; c < GROUP; ++c) gmx = fmaxf(gmx, __uint_as_float((uint32_t)mlv[j][c]));
+                const float keep = fast_exp2(mx[j] - gmx);   // rescale of what earlier passes summed
+                denom[j] *= keep;
+                o[j] *= keep;
+                mx[j] = gmx;
+#pragma unroll
+                for (int c = 0; c < GROUP; ++c) {
+                    const float w = fast_exp2(__uint_as_float((uint32_t)mlv[j][c]) - gmx);
+                    denom[j] = fmaf(w, __uint_as_float((uint32_t)(mlv[j][c] >> 32)), denom[j]);
+                    o[j][0] = fmaf(w, __uint_as_float((uint32_t)a0[j][c]), o[j][0]);
+                    o[j][1] = fmaf(w, __uint_as_float((uint32_t)(a0[j][c] >> 32)), o[j][1]);
+                    o[j][2] = fmaf(w, __uint_as_float((uint32_t)a1[j][c]), o[j][2]);
+                    o[j][3] = fmaf(w, __uint_as_float((uint32_t)(a1[j][c] >> 32)), o[j][3]);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+            if (rv[j] && dims_on) *reinterpret_cast<f32x4 *>(p.out + rh[j] * D + 4 * l32) = o[j] * (1.0f / denom[j]);
+    }
+}
+
+template <int NT, int WG, int VAR>
+__device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order, int item,
+                                          AttnShared<NT, WG, token_major_of(VAR), head_dim_of(VAR)> &sh)
+{
+    constexpr bool SPLIT_P = VAR != 1;
+    constexpr bool TM = token_major_of(VAR);
+    constexpr int D = head_dim_of(VAR);
+    constexpr int KK = D / 32;                        // 32-dim steps of the score product = 1 KB loads per K or V page
+    constexpr int MT = D / 16;                        // 16-dim slices of the output
+    constexpr int kQStride = q_stride(D);
+    constexpr int kPageHeadBytes = SPEC_BLOCK_SIZE * D * 2;   // one (page, KV head) of K or of V: 4096 at D = 128
+    constexpr int QP = D / 8;                         // 16-byte pieces of a bf16 query row
+    constexpr int QI = (NT * WG * 16 * QP + kThreads - 1) / kThreads;   // ... of all the block's rows, per thread
+    constexpr int kVtRowBytes = vt_row_bytes(D), kVtWaveBytes = vt_wave_bytes(D);
+    constexpr int PW = kWaves / WG;   // wavefronts that share the pages of a group between them
+    AttnWork w;
+    if (!attn_begin<NT, WG>(p, order, item, w)) return;
+    const int tid = w.tid, wave = w.wave, lane = w.lane, n16 = w.n16, g = w.g, pw = w.pw;
+    const int kvh = w.kvh, L = w.L, row0 = w.row0, q_len = w.q_len, group = w.group, rows = w.rows, row_lo = w.row_lo;
+    const int grp_rows = w.grp_rows, tok0 = w.tok0, bt = w.bt, my_pages = w.my_pages;
 
     // Q: the block fetches its query rows once, 16 bytes per thread and consecutive threads
     // along a row (the heads of a group are adjacent in memory), and leaves them in LDS
@@ -1179,8 +1406,6 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     const char *khead = static_cast<const char *>(p.k_cache) + (size_t)kvh * kPageHeadBytes;
     const char *vhead = static_cast<const char *>(p.v_cache) + (size_t)kvh * kPageHeadBytes;
     const size_t page_stride = (size_t)p.Hkv * kPageHeadBytes;
-    // pages pw, pw + PW, ... (none for a group that has no rows of this request)
-    const int my_pages = (npages > pw && grp_rows > 0) ? (npages - pw + PW - 1) / PW : 0;
     const int lane_off = lane * 16;
 
     auto load_page = [&](int it, PageRegs<D> &r) {   // it-th page of this wavefront
@@ -1370,184 +1595,212 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         consume_batch(batch_b, it0 + P);
     }
 
-    // each lane summed its own four tokens per page: finish the row sums
+    attn_end<NT, WG, D>(p, w, acc, m_run, l_run, out_row, [](int mt, int gg) { return mt * 16 + 4 * gg; }, sh);
+}
+
+// ---------------------------------------------------------------------------
+// The attention role in fp32 (token-major pages).  As above: one block per (request, KV head, chunk), all query
+// rows of a KV head fused, K and V read once.  Per 16-token page and 16-row tile, lane = 16 g + n:
+//   S^T[token][row] = K[token][:] . Q[row][:]     D / 4 x v_mfma_f32_16x16x4_f32
+//   O^T[dim][row] += V^T[dim][token] . P^T[token][row]     D / 4 x v_mfma_f32_16x16x4_f32
+// The order of a contraction and the numbering of output dims are free, so every operand comes straight
+// out of 16-byte loads: lane (g, n) holds dims 16 i + 4 g + e of token n for K (and of row n for Q: its
+// element e is step 4 i + e of the score product), and dims 64 h + 4 n + e of token 4 g + r for V (its element e
+// is the A operand of output slice 4 h + e, step r, whose B operand is P^T in the scores' own layout).
+// Bound by memory up to two row tiles (32 rows: 3.4 us of matrix instructions per 100 MB of pages
+// against 15 us), by both with three.  Q stays in LDS: its operands for three tiles would take 96 registers,
+// and the 8 LDS reads per page and tile cost a thirtieth of the 64 matrix instructions they feed.
+// One batch of registers each for K and V: the next page's K is loaded once this page's scores are done, its
+// V once the output product is, so that half a page (8 KB, as much as the bf16 role has) is always in
+// flight per wavefront.
+// Before, fp32 ran on scalar kernels, one block per query row and head, which read K and V from the L2 once
+// for each: eight requests of 256 to 1024 tokens, 32/8 heads, k = 4: 177.3 -> 24.5 us; a step of one request
+// of 128 tokens, now one launch instead of two: 22.2 -> 13.2 us.  The error against 64 bits went from 4.5e-7
+// to 2.8e-7 of the output's norm.
+// ---------------------------------------------------------------------------
+constexpr int f32_q_stride(int D) { return D * 4 + 16; }   // bytes per query row in LDS (padded: 16 rows cover all banks)
+
+template <int NT, int WG, int D>
+struct AttnF32Shared {
+    union {
+        f32x4 acc[2][NT][D / 16][kWave];                             // epilogue: partial results of the wavefronts being merged
+        unsigned char q[WG * NT * 16 * f32_q_stride(D)];             // the block's query rows
+        unsigned char o[WG == 1 ? NT * 16 * o_stride(D) : 16];       // epilogue of an unsplit request (one group): the output tile
+    };
+    float m[2][NT][kWave];
+    float l[2][NT][kWave];
+    int last;
+};
+
+template <int NT, int WG, int D>
+__device__ __forceinline__ void attn_f32_role(const AttnParams &p, OrderTable order, int item, AttnF32Shared<NT, WG, D> &sh)
+{
+    constexpr int KI = D / 16;                        // 16-byte K loads per lane and page
+    constexpr int VH = D / 64;                        // ... V loads per lane and token
+    constexpr int MT = D / 16;
+    constexpr int PW = kWaves / WG;
+    constexpr int kQStride = f32_q_stride(D);
+    constexpr int kPageHeadBytes = SPEC_BLOCK_SIZE * D * 4;
+    AttnWork w;
+    if (!attn_begin<NT, WG>(p, order, item, w)) return;
+    const int n16 = w.n16, g = w.g, L = w.L, my_pages = w.my_pages, bt = w.bt;
+
+    const char *khead = static_cast<const char *>(p.k_cache) + (size_t)w.kvh * kPageHeadBytes;
+    const char *vhead = static_cast<const char *>(p.v_cache) + (size_t)w.kvh * kPageHeadBytes;
+    const size_t page_stride = (size_t)p.Hkv * kPageHeadBytes;
+    // (descriptors as in the bf16 role: exactly one (page, KV head), empty past the end)
+    auto page_desc = [&](const char *head, int it) {
+        const int entry = __builtin_amdgcn_readlane(bt, it < my_pages ? it : 0);
+        const bool valid = it < my_pages && entry >= 0;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(head + (size_t)(valid ? entry : 0) * page_stride), 0,
+                                                 valid ? kPageHeadBytes : 0, kBufferFlags);
+    };
+    f32x4 k[KI], v[4][VH];   // v[r][h]: token 4 g + r, dims 64 h + 4 n16 ..
+    auto load_k = [&](int it) {
+        const __amdgpu_buffer_rsrc_t d = page_desc(khead, it);
+#pragma unroll
+        for (int i = 0; i < KI; ++i)
+            k[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, n16 * (D * 4) + g * 16, i * 64, kStreamPolicy));
+    };
+    auto load_v = [&](int it) {
+        const __amdgpu_buffer_rsrc_t d = page_desc(vhead, it);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int h = 0; h < VH; ++h)
+                v[r][h] = __builtin_bit_cast(
+                    f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, g * (D * 16) + n16 * 16, r * (D * 4) + h * 256, kStreamPolicy));
+    };
+    load_k(0);
+    load_v(0);
+
+    // the block's query rows: 16 bytes per thread, consecutive threads along a row
+    constexpr int QP = D / 4;
+    for (int piece = w.tid; piece < NT * WG * 16 * QP; piece += kThreads) {
+        const int r = piece / QP, c = piece % QP;
+        f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (r < w.rows) {
+            const size_t rh = (size_t)(w.row0 + r / w.group) * p.Hq + w.kvh * w.group + r % w.group;
+            x = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(p.q) + rh * D + c * 4);
+        }
+        *reinterpret_cast<f32x4 *>(sh.q + r * kQStride + c * 16) = x;
+    }
+    int limit[NT];     // each lane's last visible key
+    int out_row[NT];   // packed (token row * Hq + head) of this lane's query row, -1 if padding
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        l_run[nt] = sum_across_rows(l_run[nt]);
-    }
-
-    // merge the wavefronts of each group into the group's first one
-    auto put = [&](int buf) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) sh.acc[buf][nt][mt][lane] = acc[nt][mt];
-            sh.m[buf][nt][lane] = m_run[nt];
-            sh.l[buf][nt][lane] = l_run[nt];
-        }
-    };
-    auto merge = [&](int buf) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const float mo = sh.m[buf][nt][lane];
-            const float lo = sh.l[buf][nt][lane];
-            const float mn = fmaxf(m_run[nt], mo);
-            const float wa = fast_exp2(m_run[nt] - mn);
-            const float wb = fast_exp2(mo - mn);
-            l_run[nt] = l_run[nt] * wa + lo * wb;
-            m_run[nt] = mn;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = acc[nt][mt] * wa + sh.acc[buf][nt][mt][lane] * wb;
-        }
-    };
-    if constexpr (WG == 1) {          // 2,3 -> 0,1 then 1 -> 0 (the last step below, by wavefront 0)
-        if (wave >= 2) put(wave - 2);
-        __syncthreads();
-        if (wave < 2) merge(wave);
-        __syncthreads();
-        if (wave == 1) put(0);
-        __syncthreads();
-    } else if constexpr (WG == 2) {   // 1 -> 0 and 3 -> 2
-        if (pw == 1) put(grp);
-        __syncthreads();
-        if (pw == 0) merge(grp);
-        __syncthreads();
-    }
-    const bool lead = pw == 0 && grp_rows > 0;   // this wavefront holds its group's result
-
-    if (nchunks == 1) {
-        if constexpr (WG == 1) {
-            // the only chunk of this (request, KV head): normalise, lay the tile out by rows in
-            // LDS, and let the whole block write the rows (16 bytes per thread, consecutive
-            // threads along a row)
-            if (wave == 0) {
-                merge(0);   // (its reads of the shared partials precede the writes below in program order)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const float inv = 1.0f / l_run[nt];
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        *reinterpret_cast<f32x4 *>(sh.o + (nt * 16 + n16) * kOStride + mt * 64 + g * 16) = acc[nt][mt] * inv;
-                }
-            }
-            __syncthreads();
-            constexpr int OP = D / 4;   // 16-byte pieces of an fp32 output row
-            for (int piece = tid; piece < rows * OP; piece += kThreads) {
-                const int r = piece / OP, c = piece % OP;
-                const size_t rh = (size_t)(row0 + r / group) * p.Hq + kvh * group + r % group;
-                __builtin_nontemporal_store(*reinterpret_cast<const f32x4 *>(sh.o + r * kOStride + c * 16),
-                                            reinterpret_cast<f32x4 *>(p.out + rh * D + c * 4));
-            }
-        } else if (lead) {
-            // several groups: each group's first wavefront writes its rows itself (a lane holds four
-            // consecutive head dims of one row per 16-dim slice)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                if (out_row[nt] < 0) continue;
-                const float inv = 1.0f / l_run[nt];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    __builtin_nontemporal_store(acc[nt][mt] * inv,
-                                                reinterpret_cast<f32x4 *>(p.out + (size_t)out_row[nt] * D + mt * 16 + 4 * g));
-            }
-        }
-        return;
-    }
-
-    if (WG == 1 ? wave == 0 : lead) {
-        if constexpr (WG == 1) merge(0);
-        // one partial per query row: acc[dim], running max, running sum
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            if (out_row[nt] < 0) continue;
-            const size_t slot = (size_t)out_row[nt] * p.max_chunks + chunk;
-            unsigned long long *dst = reinterpret_cast<unsigned long long *>(p.ws_acc + slot * D + 4 * g);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                publish_u64(dst + 8 * mt + 0, pack_f32x2(acc[nt][mt][0], acc[nt][mt][1]));
-                publish_u64(dst + 8 * mt + 1, pack_f32x2(acc[nt][mt][2], acc[nt][mt][3]));
-            }
-            if (g == 0)
-                publish_u64(reinterpret_cast<unsigned long long *>(p.ws_ml + slot * 2), pack_f32x2(m_run[nt], l_run[nt]));
-        }
-        writes_complete();  // the partials are in memory before the ticket is taken
-    }
-    if (!p.fused_combine) return;   // a separate combine launch merges the partials
-    if constexpr (WG > 1) __syncthreads();   // ... those of every group
-    if (tid == 0) {
-        unsigned long long *ticket = &p.tickets[unit];
-        const uint32_t before = ticket_arrive(ticket, p.generation);
-        const int last = (before + 1u == (uint32_t)nchunks) ? 1 : 0;
-        if (last) ticket_reset(ticket);
-        sh.last = last;
+        const int r = w.row_lo + nt * 16 + n16;
+        const bool valid = r < w.rows;
+        const int j = valid ? r / w.group : 0;
+        limit[nt] = valid ? L - w.q_len + j : -1;
+        out_row[nt] = valid ? (w.row0 + j) * p.Hq + w.kvh * w.group + r % w.group : -1;
     }
     __syncthreads();
-    if (!sh.last) return;
-    order_after_ticket();
 
-    // Last chunk of this (request, KV head) to finish: merge all chunks in chunk order.
-    // Half a wavefront takes two query rows at a time (four head dims per lane) and eight
-    // chunks of each per pass; every load of a pass is issued before the first is used, so
-    // a pass costs one memory round trip.
-    constexpr int GROUP = 8;   // chunks merged per pass (16 per pass spill 200 to 340 bytes per lane)
-    constexpr int RB = NT >= 2 ? 2 : 1;   // rows in flight per half wavefront (one row tile: at most two passes anyway, and registers are tight)
-    const int half = lane >> 5, l32 = lane & 31;
-    const bool dims_on = 4 * l32 < D;   // (a head dim of 64 keeps half of the lanes busy)
-    for (int r0 = 2 * wave + half; r0 < rows; r0 += 2 * kWaves * RB) {
-        bool rv[RB];
-        size_t rh[RB];
-        const unsigned long long *ml[RB], *pa[RB];
-        float mx[RB], denom[RB];
-        f32x4 o[RB];
+    f32x4 acc[NT][MT];   // slice 4 h + e, element r of a lane: dim 64 h + 16 g + 4 r + e of query row n16
+    float m_run[NT], l_run[NT];
 #pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const int r = r0 + 2 * kWaves * j;
-            rv[j] = r < rows;
-            const int rr = rv[j] ? r : 0;
-            rh[j] = (size_t)(row0 + rr / group) * p.Hq + kvh * group + rr % group;
-            const size_t base = rh[j] * p.max_chunks;
-            ml[j] = reinterpret_cast<const unsigned long long *>(p.ws_ml) + base;
-            pa[j] = reinterpret_cast<const unsigned long long *>(p.ws_acc) + base * (D / 2) + 2 * l32;
-            mx[j] = kEmptyMax;
-            denom[j] = 0.0f;
-            o[j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        for (int c0 = 0; c0 < nchunks; c0 += GROUP) {
-            unsigned long long mlv[RB][GROUP], a0[RB][GROUP], a1[RB][GROUP];
+    for (int nt = 0; nt < NT; ++nt) {
+        m_run[nt] = kEmptyMax;
+        l_run[nt] = 0.0f;
 #pragma unroll
-            for (int j = 0; j < RB; ++j) {
-#pragma unroll
-                for (int c = 0; c < GROUP; ++c) {
-                    const bool on = rv[j] && c0 + c < nchunks;
-                    mlv[j][c] = on ? fetch_u64(ml[j] + c0 + c) : pack_f32x2(kEmptyMax, 0.0f);
-                    a0[j][c] = on && dims_on ? fetch_u64(pa[j] + (size_t)(c0 + c) * (D / 2)) : 0ull;
-                    a1[j][c] = on && dims_on ? fetch_u64(pa[j] + (size_t)(c0 + c) * (D / 2) + 1) : 0ull;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < RB; ++j) {
-                float gmx = mx[j];
-#pragma unroll
-                for (int c = 0; c < GROUP; ++c) gmx = fmaxf(gmx, __uint_as_float((uint32_t)mlv[j][c]));
-                const float keep = fast_exp2(mx[j] - gmx);   // rescale of what earlier passes summed
-                denom[j] *= keep;
-                o[j] *= keep;
-                mx[j] = gmx;
-#pragma unroll
-                for (int c = 0; c < GROUP; ++c) {
-                    const float w = fast_exp2(__uint_as_float((uint32_t)mlv[j][c]) - gmx);
-                    denom[j] = fmaf(w, __uint_as_float((uint32_t)(mlv[j][c] >> 32)), denom[j]);
-                    o[j][0] = fmaf(w, __uint_as_float((uint32_t)a0[j][c]), o[j][0]);
-                    o[j][1] = fmaf(w, __uint_as_float((uint32_t)(a0[j][c] >> 32)), o[j][1]);
-                    o[j][2] = fmaf(w, __uint_as_float((uint32_t)a1[j][c]), o[j][2]);
-                    o[j][3] = fmaf(w, __uint_as_float((uint32_t)(a1[j][c] >> 32)), o[j][3]);
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < RB; ++j)
-            if (rv[j] && dims_on) *reinterpret_cast<f32x4 *>(p.out + rh[j] * D + 4 * l32) = o[j] * (1.0f / denom[j]);
+        for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
     }
+    const int first_masked_token = L - w.q_len + 1;
+
+    for (int it = 0; it < my_pages; ++it) {
+        const int page_tok = w.tok0 + (w.pw + PW * it) * SPEC_BLOCK_SIZE;
+        const int tbase = page_tok + 4 * g;
+        const bool need_mask = page_tok + SPEC_BLOCK_SIZE > first_masked_token;
+        f32x4 pr[NT];   // scores, then softmax weights
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (nt > 0 && nt * 16 >= w.grp_rows) continue;   // a tile this request has no rows for (the same for the whole wavefront)
+            const unsigned char *qrow = sh.q + (w.row_lo + nt * 16 + n16) * kQStride + g * 16;
+            f32x4 s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = s0;   // (two chains: an instruction need not wait for the one before it)
+#pragma unroll
+            for (int i = 0; i < KI; ++i) {
+                const f32x4 q = *reinterpret_cast<const f32x4 *>(qrow + i * 64);
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][0], q[0], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][1], q[1], s1, 0, 0, 0);
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][2], q[2], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][3], q[3], s1, 0, 0, 0);
+            }
+            pr[nt] = s0 + s1;
+        }
+        load_k(it + 1);
+
+        bool odd_values = false;   // a value that is not finite in a page with hidden keys
+        if (need_mask) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int h = 0; h < VH; ++h) {
+                    // slots past kv_len may hold anything: clear their V
+                    if (tbase + r >= L) v[r][h] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) odd_values = odd_values || !(fabsf(v[r][h][e]) < INFINITY);
+                }
+            odd_values = __builtin_amdgcn_ballot_w64(odd_values) != 0;
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (nt > 0 && nt * 16 >= w.grp_rows) continue;
+            f32x4 s = pr[nt];
+            if (need_mask) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (tbase + r > limit[nt]) s[r] = -INFINITY;
+            }
+            // online softmax with a lazily raised reference, see the bf16 role
+            float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+            mx = max_across_xor32(max_across_xor16(mx)) * p.scale_log2;
+            const float m_new = mx > m_run[nt] + kRescaleSlack ? mx : m_run[nt];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pr[nt][r] = fast_exp2(fmaf(s[r], p.scale_log2, -m_new));
+            if (__builtin_amdgcn_ballot_w64(m_new != m_run[nt]) != 0) {
+                const float alpha = fast_exp2(m_run[nt] - m_new);
+                l_run[nt] *= alpha;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[nt][mt] *= alpha;
+                m_run[nt] = m_new;
+            }
+            l_run[nt] += (pr[nt][0] + pr[nt][1]) + (pr[nt][2] + pr[nt][3]);
+            if (!odd_values) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][mt / 4][mt % 4], pr[nt][r], acc[nt][mt], 0, 0, 0);
+                continue;
+            }
+            // A hidden key's weight is 0, but 0 times infinity or NaN is not: token by token, and added only to the
+            // rows that see the token.
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                for (int gt = 0; gt < 4; ++gt) {
+                    const bool visible = page_tok + 4 * gt + r <= limit[nt];
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const f32x4 one = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                            g == gt ? v[r][mt / 4][mt % 4] : 0.0f, g == gt ? pr[nt][r] : 0.0f, (f32x4){0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[nt][mt][e] = visible ? acc[nt][mt][e] + one[e] : acc[nt][mt][e];
+                    }
+                }
+        }
+        load_v(it + 1);
+    }
+    __syncthreads();   // every wavefront is done with the query rows: the epilogue reuses their memory
+
+    f32x4 out[NT][MT];   // slice 4 h + r: four consecutive dims from 64 h + 16 g + 4 r
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[nt][mt][e] = acc[nt][mt / 4 * 4 + e][mt % 4];
+    attn_end<NT, WG, D>(p, w, out, m_run, l_run, out_row, [](int mt, int gg) { return mt / 4 * 64 + 16 * gg + mt % 4 * 4; }, sh);
 }
 
 // ===========================================================================
@@ -1586,6 +1839,72 @@ struct StepArgs {
     UnitOrder order;
 };
 
+// The work item of a block of a launch that holds both halves; false: a padding block.
+__device__ __forceinline__ bool grid_item(const GridSplit &gs, int &item, bool &is_attn)
+{
+    item = blockIdx.x;
+    if (gs.attn_first) {
+        const int n_attn_rows8 = (gs.n_attn + kXcds - 1) / kXcds * kXcds;   // whole rows: positions keep their XCD
+        is_attn = item < n_attn_rows8;
+        if (is_attn) {
+            if (item >= gs.n_attn) return false;   // padding of the last attention row
+        } else {
+            item -= n_attn_rows8;
+            if (gs.reject_cols != kXcds) {
+                if (item & 1) return false;
+                item >>= 1;
+            }
+            if (item >= gs.n_reject) return false;
+        }
+    } else {
+        // rows of kXcds consecutive blocks (one per XCD, the hardware deals blocks to the
+        // XCDs round-robin) share a role, so every XCD sees the same mix
+        const int row = item / kXcds, col = item % kXcds;
+        const long long rows_attn = gs.rows_attn_mixed;
+        const long long rows_all = rows_attn + (gs.n_reject + gs.reject_cols - 1) / gs.reject_cols;
+        if (row < rows_all) {
+            const int before = (int)((row * rows_attn) / rows_all);
+            const int upto = (int)(((row + 1) * rows_attn) / rows_all);
+            is_attn = upto > before;
+            if (is_attn) {
+                item = before * kXcds + col;
+            } else if (gs.reject_cols == kXcds) {
+                item = (row - before) * kXcds + col;
+            } else {
+                if (col & 1) return false;
+                item = (row - before) * (kXcds / 2) + (col >> 1);
+            }
+        } else {   // the attention rows after the last rejection row
+            is_attn = true;
+            item = (int)(rows_attn + (row - rows_all)) * kXcds + col;
+        }
+        if (item >= (is_attn ? gs.n_attn : gs.n_reject)) return false;   // padding of the last row
+    }
+    return true;
+}
+
+template <int DEPTH>
+__device__ __forceinline__ void reject_item(const RejectParams &p, int n_stat, int item, RejectShared &sh)
+{
+    if (item < n_stat) {
+        stats_role<DEPTH>(p, item, sh);
+        return;
+    }
+    const int after = item - n_stat;
+    const int n_race = p.B * p.race_segments;
+    if (after < n_race) race_role(p, after, sh);
+    else final_role(p, after - n_race, sh);
+}
+
+__device__ __forceinline__ OrderTable order_table(int n)
+{
+    OrderTable order;
+    order.n = n;
+    order.pairs = (uniform_u32_ptr)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() +
+                                    offsetof(StepArgs, order) + offsetof(UnitOrder, request));
+    return order;
+}
+
 // Blocks per compute unit the registers have to allow: two, and four where the attention variant needs
 // no more registers than that (one row tile at a head dim of 64) or is absent, so that the race does not
 // take more.
@@ -1597,48 +1916,10 @@ __global__ __launch_bounds__(kThreads, (kMinBlocks<NT, HAS_ATTN, VAR>)) void spe
 {
     const AttnParams &ap = args.ap;
     const RejectParams &rp = args.rp;
-    const GridSplit &gs = args.gs;
     int item = blockIdx.x;
     bool is_attn = HAS_ATTN;
-    if constexpr (HAS_ATTN && HAS_REJECT) {
-        if (gs.attn_first) {
-            const int n_attn_rows8 = (gs.n_attn + kXcds - 1) / kXcds * kXcds;   // whole rows: positions keep their XCD
-            is_attn = item < n_attn_rows8;
-            if (is_attn) {
-                if (item >= gs.n_attn) return;   // padding of the last attention row
-            } else {
-                item -= n_attn_rows8;
-                if (gs.reject_cols != kXcds) {
-                    if (item & 1) return;
-                    item >>= 1;
-                }
-                if (item >= gs.n_reject) return;
-            }
-        } else {
-            // rows of kXcds consecutive blocks (one per XCD, the hardware deals blocks to the
-            // XCDs round-robin) share a role, so every XCD sees the same mix
-            const int row = item / kXcds, col = item % kXcds;
-            const long long rows_attn = gs.rows_attn_mixed;
-            const long long rows_all = rows_attn + (gs.n_reject + gs.reject_cols - 1) / gs.reject_cols;
-            if (row < rows_all) {
-                const int before = (int)((row * rows_attn) / rows_all);
-                const int upto = (int)(((row + 1) * rows_attn) / rows_all);
-                is_attn = upto > before;
-                if (is_attn) {
-                    item = before * kXcds + col;
-                } else if (gs.reject_cols == kXcds) {
-                    item = (row - before) * kXcds + col;
-                } else {
-                    if (col & 1) return;
-                    item = (row - before) * (kXcds / 2) + (col >> 1);
-                }
-            } else {   // the attention rows after the last rejection row
-                is_attn = true;
-                item = (int)(rows_attn + (row - rows_all)) * kXcds + col;
-            }
-            if (item >= (is_attn ? gs.n_attn : gs.n_reject)) return;   // padding of the last row
-        }
-    }
+    if constexpr (HAS_ATTN && HAS_REJECT)
+        if (!grid_item(args.gs, item, is_attn)) return;
     // one piece of LDS for either role
     typedef AttnShared<NT, WG, token_major_of(VAR), head_dim_of(VAR)> AttnSh;
     constexpr size_t kSharedBytes = !HAS_REJECT ? sizeof(AttnSh)
@@ -1646,34 +1927,36 @@ __global__ __launch_bounds__(kThreads, (kMinBlocks<NT, HAS_ATTN, VAR>)) void spe
     __shared__ alignas(16) unsigned char shared[kSharedBytes];
     if constexpr (HAS_REJECT) {
         if (!is_attn) {
-            RejectShared &rsh = *reinterpret_cast<RejectShared *>(shared);
-            if (item < gs.n_stat) {
-                // a whole 32000-entry row per round trip where the registers allow it
-                stats_role<(HAS_ATTN && NT >= 2) ? 8 : 4>(rp, item, rsh);
-            } else {
-                const int after = item - gs.n_stat;
-                const int n_race = rp.B * rp.race_segments;
-                if (after < n_race) race_role(rp, after, rsh);
-                else final_role(rp, after - n_race, rsh);
-            }
+            // a whole 32000-entry row per round trip where the registers allow it
+            reject_item<(HAS_ATTN && NT >= 2) ? 8 : 4>(rp, args.gs.n_stat, item, *reinterpret_cast<RejectShared *>(shared));
             return;
         }
     }
     if constexpr (HAS_ATTN) {
         AttnSh &ash = *reinterpret_cast<AttnSh *>(shared);
-        OrderTable order;
-        order.n = args.order.n;
-        order.pairs = (uniform_u32_ptr)((const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr() +
-                                        offsetof(StepArgs, order) + offsetof(UnitOrder, request));
-        attn_role<NT, WG, VAR>(ap, order, item, ash);
+        attn_role<NT, WG, VAR>(ap, order_table(args.order.n), item, ash);
     }
 }
 
-template <int NT, int WG, bool HAS_ATTN, bool HAS_REJECT>
-hipError_t launch(const AttnParams &ap, const RejectParams &rp, int n_stat, int n_attn, int n_race,
-                  const UnitOrder *order, LaunchEvents ev, hipStream_t stream)
+// The step in fp32: the same grid and roles.  A launch of the attention alone has no rejection items.
+// (Three row tiles take over 256 registers at a head dim of 128: 33 to 48 rows run as two wave groups of two
+// tiles, and only the widest shapes, 129 to 144 rows, as four groups of three with one block per compute unit.)
+template <int NT, int WG, int D>
+__global__ __launch_bounds__(kThreads, (NT == 3 ? 1 : 2)) void f32_step_kernel(StepArgs args)
 {
-    StepArgs args;
+    int item;
+    bool is_attn;
+    if (!grid_item(args.gs, item, is_attn)) return;
+    typedef AttnF32Shared<NT, WG, D> AttnSh;
+    __shared__ alignas(16) unsigned char shared[sizeof(RejectShared) > sizeof(AttnSh) ? sizeof(RejectShared) : sizeof(AttnSh)];
+    if (is_attn) attn_f32_role<NT, WG, D>(args.ap, order_table(args.order.n), item, *reinterpret_cast<AttnSh *>(shared));
+    else reject_item<NT >= 2 ? 8 : 4>(args.rp, args.gs.n_stat, item, *reinterpret_cast<RejectShared *>(shared));
+}
+
+// The kernel arguments of a launch and its grid.
+template <bool HAS_ATTN, bool HAS_REJECT>
+dim3 fill_args(StepArgs &args, const AttnParams &ap, const RejectParams &rp, int n_stat, int n_attn, int n_race, const UnitOrder *order)
+{
     args.ap = ap;
     args.rp = rp;
     args.order.n = 0;
@@ -1712,17 +1995,27 @@ hipError_t launch(const AttnParams &ap, const RejectParams &rp, int n_stat, int 
     // with two per compute unit, 15% slower where the rejection half is a fifth of the step.)
     gs.reject_cols = (HAS_ATTN && HAS_REJECT && ap.reject_even_xcds && n_attn <= ap.reject_even_limit && !reject_first) ? kXcds / 2 : kXcds;
     const int rows_reject = (n_reject + gs.reject_cols - 1) / gs.reject_cols;
-    const dim3 grid(mixed ? (rows_attn_all + rows_reject) * kXcds
+    return dim3(mixed ? (rows_attn_all + rows_reject) * kXcds
                           : (HAS_ATTN && HAS_REJECT ? (rows_attn_all + rows_reject) * kXcds : n_reject + n_attn));
-    // (with events the extended launch attaches them to the kernel's own begin and end)
+}
+
+// (with events the extended launch attaches them to the kernel's own begin and end)
+template <typename Kernel>
+hipError_t launch_kernel(Kernel kernel, dim3 grid, const StepArgs &args, LaunchEvents ev, hipStream_t stream)
+{
+    if (ev.start != nullptr) hipExtLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, ev.start, ev.stop, 0, args);
+    else hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, stream, args);
+    return hipGetLastError();
+}
+
+template <int NT, int WG, bool HAS_ATTN, bool HAS_REJECT>
+hipError_t launch(const AttnParams &ap, const RejectParams &rp, int n_stat, int n_attn, int n_race,
+                  const UnitOrder *order, LaunchEvents ev, hipStream_t stream)
+{
+    StepArgs args;
+    const dim3 grid = fill_args<HAS_ATTN, HAS_REJECT>(args, ap, rp, n_stat, n_attn, n_race, order);
     auto go = [&](auto var) {
-        constexpr int VAR = decltype(var)::value;
-        if (ev.start != nullptr)
-            hipExtLaunchKernelGGL((spec_step_kernel<NT, WG, HAS_ATTN, HAS_REJECT, VAR>), grid, dim3(kThreads), 0, stream, ev.start,
-                                  ev.stop, 0, args);
-        else
-            hipLaunchKernelGGL((spec_step_kernel<NT, WG, HAS_ATTN, HAS_REJECT, VAR>), grid, dim3(kThreads), 0, stream, args);
-        return hipGetLastError();
+        return launch_kernel(spec_step_kernel<NT, WG, HAS_ATTN, HAS_REJECT, decltype(var)::value>, grid, args, ev, stream);
     };
     if constexpr (HAS_ATTN) {
         if (ap.kv_layout == SPEC_KV_TOKEN_MAJOR)
@@ -1735,13 +2028,23 @@ hipError_t launch(const AttnParams &ap, const RejectParams &rp, int n_stat, int 
     return go(std::integral_constant<int, 0>());
 }
 
+template <int NT, int WG>
+hipError_t launch_f32(const AttnParams &ap, const RejectParams &rp, int n_stat, int n_attn, int n_race, const UnitOrder *order,
+                      LaunchEvents ev, hipStream_t stream)
+{
+    StepArgs args;
+    const dim3 grid = fill_args<true, true>(args, ap, rp, n_stat, n_attn, n_race, order);
+    if (ap.d == 64) return launch_kernel(f32_step_kernel<NT, WG, 64>, grid, args, ev, stream);
+    return launch_kernel(f32_step_kernel<NT, WG, 128>, grid, args, ev, stream);
+}
+
 }  // namespace
 
 // The kernel variants of this file take over a minute to compile in one piece, so the build
 // compiles the file several times, each time with SPEC_STEP_PART set to the part whose
 // launchers it should hold (everything else of the file is shared, file-local code):
 //   0: the dispatcher below, the rejection-only kernel, one row tile    1: two row tiles
-//   2: three row tiles    3: two wave groups    4: four wave groups      (unset: all of it)
+//   2: three row tiles    3: two wave groups    4: four wave groups    5: fp32      (unset: all of it)
 #ifndef SPEC_STEP_PART
 #define SPEC_STEP_PART -1
 #endif
@@ -1758,6 +2061,7 @@ SPEC_STEP_LAUNCHER(launch_step_tiles2_groups2);
 SPEC_STEP_LAUNCHER(launch_step_tiles3_groups2);
 SPEC_STEP_LAUNCHER(launch_step_tiles2_groups4);
 SPEC_STEP_LAUNCHER(launch_step_tiles3_groups4);
+SPEC_STEP_LAUNCHER(launch_step_f32);
 #define SPEC_STEP_DEFINE(NAME, NT_, WG_)                                                                     \
     SPEC_STEP_LAUNCHER(NAME)                                                                                 \
     {                                                                                                        \
@@ -1782,6 +2086,19 @@ SPEC_STEP_DEFINE(launch_step_tiles2_groups4, 2, 4)
 SPEC_STEP_DEFINE(launch_step_tiles3_groups4, 3, 4)
 #endif
 #undef SPEC_STEP_DEFINE
+#if SPEC_STEP_HAS_PART(5)
+SPEC_STEP_LAUNCHER(launch_step_f32)
+{
+    (void)with_reject;
+    switch (ap.row_groups * 10 + ap.row_tiles) {
+        case 11: return launch_f32<1, 1>(ap, rp, n_stat, n_attn, n_race, order, ev, stream);
+        case 12: return launch_f32<2, 1>(ap, rp, n_stat, n_attn, n_race, order, ev, stream);
+        case 22: return launch_f32<2, 2>(ap, rp, n_stat, n_attn, n_race, order, ev, stream);
+        case 42: return launch_f32<2, 4>(ap, rp, n_stat, n_attn, n_race, order, ev, stream);
+        default: return launch_f32<3, 4>(ap, rp, n_stat, n_attn, n_race, order, ev, stream);
+    }
+}
+#endif
 #undef SPEC_STEP_LAUNCHER
 
 #if SPEC_STEP_HAS_PART(0)
@@ -1808,18 +2125,22 @@ hipError_t launch_step_fused(const AttnParams *attn, int row_tiles, const Reject
     if (attn != nullptr) {
         ap = *attn;
         // tiles per wave group and wave groups per block that the kernel is built for
-        const bool shape_ok = (ap.row_groups == 1 && row_tiles >= 1 && row_tiles <= 3) ||
+        const bool shape_ok = ap.f32 ? (ap.row_groups == 1 && (row_tiles == 1 || row_tiles == 2)) ||
+                                           ((ap.row_groups == 2 || ap.row_groups == 4) && row_tiles == 2) || (ap.row_groups == 4 && row_tiles == 3)
+                                     : (ap.row_groups == 1 && row_tiles >= 1 && row_tiles <= 3) ||
                               ((ap.row_groups == 2 || ap.row_groups == 4) && (row_tiles == 2 || row_tiles == 3));
         // (a wavefront keeps the block-table entries of its pages one per lane)
         const bool dim_ok = ap.d == kD || ap.d == 64;
         if (!dim_ok || !shape_ok || ap.chunk_tokens > 4096 / ap.row_groups || ap.chunk_tokens % SPEC_BLOCK_SIZE != 0 ||
             ap.capacity_tokens > ap.chunk_tokens * ap.max_chunks ||
-            (ap.fused_combine && ap.max_chunks > kMaxFusedChunks) || (order != nullptr && order->n != 0 && order->n != ap.B))
+            (ap.f32 && ap.kv_layout != SPEC_KV_TOKEN_MAJOR) || (ap.fused_combine && ap.max_chunks > kMaxFusedChunks) || (order != nullptr && order->n != 0 && order->n != ap.B))
             return hipErrorInvalidValue;
         n_attn = step_attn_items(ap);
     }
     if (attn == nullptr) return launch<1, 1, false, true>(ap, rp, n_stat, 0, n_race, nullptr, ev, stream);
     const bool with_reject = reject != nullptr;
+    ap.row_tiles = row_tiles;
+    if (ap.f32) return launch_step_f32(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
     switch (ap.row_groups * 10 + row_tiles) {
         case 11: return launch_step_tiles1(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
         case 12: return launch_step_tiles2(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
