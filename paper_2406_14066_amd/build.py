@@ -26,7 +26,7 @@ def sources():
 # step_kernel.hip holds dozens of kernel variants; it is compiled once per part (see SPEC_STEP_PART
 # in that file), in parallel with the other sources, and the objects are linked.
 STEP_KERNEL = "step_kernel.hip"
-STEP_PARTS = 6
+STEP_PARTS = 5
 
 
 def compile_jobs(objdir: str):

@@ -360,7 +360,10 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
         // 13.6 us, 16 chunks 19.3 us, 2 chunks 17.2 us.
         int64_t min_chunk = 64;
         if (tu.target_blocks == 0) {
-            const int64_t most = std::max<int64_t>(8, (max_len + 1023) / 1024);
+            // (fp32 takes about twice as long per token: chunks of 512 tokens. Two requests of 8000, 32/8 heads, k = 4:
+            // 8 chunks 51.9 us, 16 chunks 38.9 us.)
+            const int worth = a->qkv_dtype == SPEC_F32 ? 512 : 1024;
+            const int64_t most = std::max<int64_t>(8, (max_len + worth - 1) / worth);
             if (nsplit > most) nsplit = most;
             min_chunk = 256;
         }
@@ -381,7 +384,10 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
     pl.fused_combine = (pl.use_mfma && pl.max_chunks <= kMaxFusedChunks) ? 1 : 0;
     // (a request that is not split writes its output directly: the matrix kernel needs no partial
     // slots when no request can have a second chunk)
-    const size_t slots = (pl.use_mfma && pl.max_chunks == 1) ? 0 : (size_t)a->T * a->Hq * pl.max_chunks;
+    // fp32 has room for the scalar kernels' chunks of 256 tokens, so that a workspace serves them too
+    const bool f32_type = a->qkv_dtype == SPEC_F32;
+    const int slot_chunks = f32_type ? std::max(pl.max_chunks, (max_len + 255) / 256) : pl.max_chunks;
+    const size_t slots = (pl.use_mfma && pl.max_chunks == 1 && !f32_type) ? 0 : (size_t)a->T * a->Hq * slot_chunks;
     pl.acc_bytes = align_up(slots * a->d * sizeof(float));
     pl.ml_bytes = align_up(slots * 2 * sizeof(float));
     pl.ticket_bytes = align_up((size_t)a->B * a->Hkv * sizeof(unsigned long long));
@@ -421,16 +427,14 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     // 51.4 / 52.4 us for 256 requests, k = 2, V = 32000), about 256 beside an attention half, where every block
     // holds a slot of the attention's while it waits (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
     // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7)
-    const int race_blocks = tu.race_blocks > 0 ? tu.race_blocks : (attn_us < 0.0 ? 1024 : 256);
-    int rsegs = (race_blocks + r->B - 1) / r->B;
-    const int rmax_by_len = (r->V + 2047) / 2048;
-    if (rsegs > rmax_by_len) rsegs = rmax_by_len;
-    if (rsegs > 64) rsegs = 64;
-    if (rsegs < 1) rsegs = 1;
-    int rlen = (r->V + rsegs - 1) / rsegs;
-    rlen = (rlen + 1023) / 1024 * 1024;   // a block takes 1024 ids at a time
-    pl.race_seg_len = rlen;
-    pl.race_segments = (r->V + rlen - 1) / rlen;
+    const auto race_split = [&](int blocks, int multiple, int &segments, int &len) {
+        int n = std::min({(blocks + r->B - 1) / r->B, (r->V + 2047) / 2048, 64});
+        if (n < 1) n = 1;
+        len = (int)std::min<int64_t>((((int64_t)r->V + n - 1) / n + multiple - 1) / multiple * multiple, INT32_MAX / 4 * 4);
+        segments = (int)(((int64_t)r->V + len - 1) / len);
+    };
+    // (a block takes 1024 ids at a time)
+    race_split(tu.race_blocks > 0 ? tu.race_blocks : (attn_us < 0.0 ? 1024 : 256), 1024, pl.race_segments, pl.race_seg_len);
     // requests per item of the final stage: as many as leave 8 items (the kernel says why they are grouped)
     pl.final_shift = 0;
     while (pl.final_shift < kMaxFinalShift && (16 << pl.final_shift) <= r->B && (pl.stat_segments << (pl.final_shift + 1)) <= 32)
@@ -464,7 +468,10 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     pl.stats_off = base;
     pl.stats_bytes = align_up((size_t)rows * pl.stat_segments * kStatWords * sizeof(unsigned long long));
     pl.partial_off = pl.stats_off + pl.stats_bytes;
-    pl.partial_bytes = align_up(((size_t)r->B * pl.race_segments * 2 + r->B) * sizeof(unsigned long long));
+    // (room for the segments of 512 blocks at least, so that what fits the static scratch does not depend on the split)
+    int room = 0, room_len = 0;
+    race_split(tu.race_blocks > 0 ? tu.race_blocks : 512, 4, room, room_len);
+    pl.partial_bytes = align_up(((size_t)r->B * std::max(pl.race_segments, room) * 2 + r->B) * sizeof(unsigned long long));
     pl.total_bytes = pl.stats_bytes + pl.partial_bytes;
     return pl;
 }

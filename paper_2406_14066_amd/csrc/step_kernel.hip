@@ -2044,7 +2044,7 @@ hipError_t launch_f32(const AttnParams &ap, const RejectParams &rp, int n_stat, 
 // compiles the file several times, each time with SPEC_STEP_PART set to the part whose
 // launchers it should hold (everything else of the file is shared, file-local code):
 //   0: the dispatcher below, the rejection-only kernel, one row tile    1: two row tiles
-//   2: three row tiles    3: two wave groups    4: four wave groups    5: fp32      (unset: all of it)
+//   2: three row tiles    3: two wave groups    4: four wave groups    5: fp32 (step_f32.hip)    (unset: all of it)
 #ifndef SPEC_STEP_PART
 #define SPEC_STEP_PART -1
 #endif
