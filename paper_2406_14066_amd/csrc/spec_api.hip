@@ -412,8 +412,11 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     memset(&pl, 0, sizeof pl);
     // logit rows that get a statistics pass: the draft rows only when there is a draft distribution
     const int rows = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * r->T - r->B : r->T;
-    // statistics: about 256 blocks in all, segments of >= 8192 logits, at most 32 per row
-    int segs = (256 + rows - 1) / rows;
+    // statistics: segments of >= 8192 logits, at most 32 per row; about 1024 blocks in all when the rejection half runs
+    // alone (what 4 blocks per compute unit hold; with fewer, some units get two rows and others one: 48
+    // requests, V = 128256, 256 / 1024 / 2048 blocks 50.7 / 48.2 / 49.5 us, 16 of them at k = 4 29.1 / 26.7 / 29.2),
+    // about 256 beside an attention half
+    int segs = ((attn_us < 0.0 ? 1024 : 256) + rows - 1) / rows;
     const int max_by_len = (r->V + 8191) / 8192;
     if (segs > max_by_len) segs = max_by_len;
     if (segs > 32) segs = 32;
@@ -444,8 +447,7 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     // position order and the rows after a request's first rejection left unread.  That turns the
     // pass into a chain of k+1 dependent stages (about 12 us each, then the race), which must stay
     // hidden: under a launch that streams (KV and logit bytes at 5.5 TB/s) for clearly longer than
-    // the chain takes, or, when the rejection half runs alone, behind several rounds of blocks per
-    // position.  Measured (step with / without): B=256 k=2 (64/8 heads) -4%, the same at k=7 -15%,
+    // the chain takes (the rejection half alone: see below).  Measured (step with / without): B=256 k=2 (64/8 heads) -4%, the same at k=7 -15%,
     // B=64 k=8 (32/32 heads, L=1024) -8%, B=64 k=4 -3%, B=32 k=1..3 -2%, B=32 k=4 +2%, B=32 k=8 +16%,
     // B=16 k=2 (L=2048) +2%, B=8 k=4 +32%.
     pl.early_stop = 0;
@@ -459,8 +461,19 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
             const double logits_us = (double)rows * r->V * 4.0 / 5.5e6;
             wanted = r->B >= 32 && 12.0 * q + 30.0 <= 0.85 * (attn_us + logits_us);
         } else {
-            const int64_t per_position = (int64_t)(r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 : 1) * r->B * pl.stat_segments;
-            wanted = (int64_t)rows * pl.stat_segments >= 3ll * compute_units() && per_position >= compute_units();
+            // One stage per position: it streams what is still needed of its rows (at an acceptance rate of 0.7),
+            // in 6 us at least, and has a block per compute unit.  Against all rows in one go, in one
+            // launch: B=256 V=32000 k=1 / 2 / 7 +3 / -6 / -14%, B=128 k=4 +18%, B=512 V=8192 k=4 +4%; V=128256 B=256
+            // k=1 -6%, B=128 k=2 -9%, B=40 k=7 (too few blocks per stage) +22%; greedy V=32000 k=3 B=256 / 512
+            // +17 / -12%; the rule takes the better side in each.
+            const int per_position = (r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 : 1) * r->B;
+            double staged = 0.0, all = 0.0, needed = 1.0;
+            for (int j = 0; j < q; ++j, needed *= 0.7) {
+                const double us = (double)(j < q - 1 ? per_position : r->B) * r->V * 4.0 / 5.5e6;
+                all += us;
+                staged += std::max(6.0, needed * us);
+            }
+            wanted = staged <= 0.95 * all && (int64_t)per_position * pl.stat_segments >= compute_units();
         }
         if (tu.early_stop >= 0) wanted = tu.early_stop != 0;
         if (uniform && wanted) { pl.early_stop = 1; pl.uniform_k = q - 1; }
