@@ -112,6 +112,16 @@ __device__ __forceinline__ float sum_across_rows(float v)   // over lanes l, l ^
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// One gfx950 transposing LDS read: the 16 lanes of a row give the addresses of a 4 x 16 block of 16-bit
+// elements, 8 bytes each (lane n: block row n / 4, elements 4 (n % 4) .. + 3), and lane n receives block
+// column n.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 read_transposed(const unsigned char *src)
+{
+    typedef __attribute__((address_space(3))) s16x4 *lds_s16x4_ptr;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)src));
+}
+
 // 16 bytes of logits that this launch will not read again (see kStreamPolicy).
 __device__ __forceinline__ float4 load_streaming(const float *p)
 {
@@ -1028,11 +1038,16 @@ constexpr int o_stride(int D) { return D * 4 + 16; }   // bytes per fp32 output 
 // four row groups of a wavefront, 4 tokens apart, land 16 banks apart: no conflicts.
 constexpr int vt_row_bytes(int D) { return D * 2 + 16; }
 constexpr int vt_wave_bytes(int D) { return SPEC_BLOCK_SIZE * vt_row_bytes(D); }
+// Which blocks walk their pages staged (see the staged walk in attn_role).
+constexpr bool staged_walk(int WG, bool TM) { return WG > 1 && TM; }
 
 template <int NT, int WG, bool TM = false, int D = kD>
 struct AttnShared {
     static constexpr int kRowsMax = WG * NT * 16;
+    static constexpr bool kStaged = staged_walk(WG, TM);
     union {
+        // staged walk: two rounds of a page per wavefront, K and V
+        unsigned char ring[kStaged ? 2 : 1][kStaged ? kWaves : 1][2][kStaged ? vt_wave_bytes(D) : 16];
         f32x4 acc[2][NT][D / 16][kWave];          // epilogue: partial results of the wavefronts being merged
         unsigned char q[kRowsMax * q_stride(D)];  // prologue: the block's query rows
         unsigned char o[WG == 1 ? NT * 16 * o_stride(D) : 16];   // epilogue of an unsplit request (one group): the output tile
@@ -1040,7 +1055,7 @@ struct AttnShared {
     float m[2][NT][kWave];
     float l[2][NT][kWave];
     int last;
-    alignas(16) unsigned char vt[TM ? kWaves * vt_wave_bytes(D) : 16];   // token-major pages: V staged per wavefront
+    alignas(16) unsigned char vt[TM && !kStaged ? kWaves * vt_wave_bytes(D) : 16];   // token-major pages: V staged per wavefront
 };
 
 // The order in which the attention items take the requests (longest first), as the kernel
@@ -1073,10 +1088,12 @@ struct AttnWork {
 };
 
 // The block's place in the work: request, KV head, chunk, rows, pages.  False: nothing to do.
-template <int NT, int WG>
+// (STAGED: the wavefronts of all groups share the page loads between them, see the staged walk.)
+template <int NT, int WG, bool STAGED>
 __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order, int item, AttnWork &w)
 {
     constexpr int PW = kWaves / WG;   // wavefronts that share the pages of a group between them
+    constexpr int STEP = STAGED ? kWaves : PW;   // a wavefront loads every STEP-th page
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave / PW;        // this wavefront's row group
@@ -1084,6 +1101,7 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     const int lane = tid & 63;
     const int n16 = lane & 15;
     const int g = lane >> 4;
+    const int first = STAGED ? wave : pw;   // ... from this one on
     // Items are chunk-major: all first chunks (requests longest first, KV heads innermost),
     // then all second chunks, ...  Consecutive blocks go to different XCDs, so every XCD
     // gets the same mix of chunk indices; the chunk indices that only the longest requests
@@ -1109,8 +1127,8 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     // When no request is split, a wavefront's block-table entries do not depend on kv_len:
     // fetch them alongside it (entries past the request's pages are never used).
     int bt = 0;
-    if (p.max_chunks == 1 && pw + PW * lane < p.max_blocks_per_req)
-        bt = p.block_table[(size_t)b * p.max_blocks_per_req + pw + PW * lane];
+    if (p.max_chunks == 1 && first + STEP * lane < p.max_blocks_per_req)
+        bt = p.block_table[(size_t)b * p.max_blocks_per_req + first + STEP * lane];
     const int L = uniform_load(p.kv_len, b);
     const int row0 = uniform_load(p.cu_q_len, b);
     const int q_len = uniform_load(p.cu_q_len, b + 1) - row0;
@@ -1136,15 +1154,15 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     const int npages = (tok1 - tok0 + SPEC_BLOCK_SIZE - 1) / SPEC_BLOCK_SIZE;  // <= 64 * PW
     const int page0 = tok0 / SPEC_BLOCK_SIZE;
 
-    // block-table entries of this wavefront's pages (pw, pw + PW, ...), one per lane
-    if (p.max_chunks != 1 && pw + PW * lane < npages)
-        bt = p.block_table[(size_t)b * p.max_blocks_per_req + page0 + pw + PW * lane];
+    // block-table entries of this wavefront's pages (every STEP-th), one per lane
+    if (p.max_chunks != 1 && first + STEP * lane < npages)
+        bt = p.block_table[(size_t)b * p.max_blocks_per_req + page0 + first + STEP * lane];
     {
         // an entry outside the pool is never turned into an address: the page reads as zeros
-        const bool bad = pw + PW * lane < npages && (unsigned)bt >= (unsigned)p.num_blocks;
+        const bool bad = first + STEP * lane < npages && (unsigned)bt >= (unsigned)p.num_blocks;
         if (bad) bt = -1;
         const unsigned long long bad_lanes = __builtin_amdgcn_ballot_w64(bad);
-        if (bad_lanes != 0 && kvh == 0 && grp == 0 && p.errors != nullptr && lane == 0)
+        if (bad_lanes != 0 && kvh == 0 && (STAGED || grp == 0) && p.errors != nullptr && lane == 0)
             atomicAdd(p.errors, (unsigned long long)__builtin_popcountll(bad_lanes));
     }
 
@@ -1152,8 +1170,8 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     w.kvh = kvh; w.unit = unit; w.chunk = chunk; w.nchunks = nchunks;
     w.L = L; w.row0 = row0; w.q_len = q_len; w.group = group;
     w.rows = rows; w.row_lo = row_lo; w.grp_rows = grp_rows; w.tok0 = tok0; w.npages = npages; w.bt = bt;
-    // pages pw, pw + PW, ... (none for a group that has no rows of this request)
-    w.my_pages = (npages > pw && grp_rows > 0) ? (npages - pw + PW - 1) / PW : 0;
+    // (none for a group that has no rows of this request, unless it loads for the others)
+    w.my_pages = (npages > first && (STAGED || grp_rows > 0)) ? (npages - first + STEP - 1) / STEP : 0;
     return true;
 }
 
@@ -1356,6 +1374,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
 {
     constexpr bool SPLIT_P = VAR != 1;
     constexpr bool TM = token_major_of(VAR);
+    constexpr bool STAGED = staged_walk(WG, TM);
     constexpr int D = head_dim_of(VAR);
     constexpr int KK = D / 32;                        // 32-dim steps of the score product = 1 KB loads per K or V page
     constexpr int MT = D / 16;                        // 16-dim slices of the output
@@ -1366,7 +1385,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     constexpr int kVtRowBytes = vt_row_bytes(D), kVtWaveBytes = vt_wave_bytes(D);
     constexpr int PW = kWaves / WG;   // wavefronts that share the pages of a group between them
     AttnWork w;
-    if (!attn_begin<NT, WG>(p, order, item, w)) return;
+    if (!attn_begin<NT, WG, STAGED>(p, order, item, w)) return;
     const int tid = w.tid, wave = w.wave, lane = w.lane, n16 = w.n16, g = w.g, pw = w.pw;
     const int kvh = w.kvh, L = w.L, row0 = w.row0, q_len = w.q_len, group = w.group, rows = w.rows, row_lo = w.row_lo;
     const int grp_rows = w.grp_rows, tok0 = w.tok0, bt = w.bt, my_pages = w.my_pages;
@@ -1417,7 +1436,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             const_cast<char *>(khead + (size_t)page * page_stride), 0, bytes, kBufferFlags);
         const __amdgpu_buffer_rsrc_t vd = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(vhead + (size_t)page * page_stride), 0, bytes, kBufferFlags);
-        if constexpr (TM) {
+        if constexpr (TM && !STAGED) {
             // K: token n16, dims 32 i + 8 g .. + 7 sit at n16 * 2 D + 64 i + 16 g
 #pragma unroll
             for (int i = 0; i < KK; ++i)
@@ -1451,7 +1470,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         const bool need_mask = page_tok + SPEC_BLOCK_SIZE > first_masked_token;
         const int tbase = page_tok + 4 * g;
 
-        if constexpr (TM) {
+        if constexpr (TM && !STAGED) {
             // V through this wavefront's LDS region: rows in, operand order out (LDS executes a
             // wavefront's accesses in order, so the reads see the writes without a barrier)
             unsigned char *vl = sh.vt + wave * kVtWaveBytes;
@@ -1539,60 +1558,123 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         }
     };
 
-    // Two register batches of P pages each.  While one batch is consumed the loads of the
-    // other are in flight.  The order inside a half-step matters: first wait for the batch
-    // about to be consumed (at that point it is the only one outstanding, so the full
-    // wait the compiler emits waits for nothing else), then issue the other batch's loads,
-    // then do the arithmetic, which needs no further wait.
-    // pages per batch: two bring nothing once the launch keeps the memory system busy, except with the
-    // half-size pages of a head dim of 64 (the same bytes in flight per wavefront as at 128)
-    constexpr int P = D == 64 ? 2 : 1;
-    PageRegs<D> batch_a[P], batch_b[P];
-    auto load_batch = [&](int it, PageRegs<D>(&r)[P]) {
-#pragma unroll
-        for (int j = 0; j < P; ++j) load_page(it + j, r[j]);
-    };
-    auto arrived = [&](PageRegs<D>(&r)[P]) {
-#pragma unroll
-        for (int j = 0; j < P; ++j) {
-            if constexpr (KK == 4)
-                asm volatile("" ::"v"(r[j].k[0]), "v"(r[j].k[1]), "v"(r[j].k[2]), "v"(r[j].k[3]), "v"(r[j].v[0]),
-                             "v"(r[j].v[1]), "v"(r[j].v[2]), "v"(r[j].v[3])
-                             : "memory");
-            else
-                asm volatile("" ::"v"(r[j].k[0]), "v"(r[j].k[1]), "v"(r[j].v[0]), "v"(r[j].v[1]) : "memory");
-        }
-    };
-    auto consume_batch = [&](PageRegs<D>(&r)[P], int it) {
-#pragma unroll
-        for (int j = 0; j < P; ++j)
-            if (it + j < my_pages) consume(r[j], pw + PW * (it + j));
-    };
-    load_batch(0, batch_a);
-
     // Q as the B operand of S^T = K Q^T, out of LDS (the first pages are on their way)
+    auto stage_q = [&] {
 #pragma unroll
-    for (int i = 0; i < QI; ++i) {
-        const int piece = tid + i * kThreads;
-        if (QI * kThreads == NT * WG * 16 * QP || piece < NT * WG * 16 * QP)
-            *reinterpret_cast<u32x4 *>(sh.q + (piece / QP) * kQStride + (piece % QP) * 16) = qpiece[i];
-    }
-    __syncthreads();
+        for (int i = 0; i < QI; ++i) {
+            const int piece = tid + i * kThreads;
+            if (QI * kThreads == NT * WG * 16 * QP || piece < NT * WG * 16 * QP)
+                *reinterpret_cast<u32x4 *>(sh.q + (piece / QP) * kQStride + (piece % QP) * 16) = qpiece[i];
+        }
+        __syncthreads();
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-            qreg[nt][kk] = *reinterpret_cast<const bf16x8 *>(sh.q + (row_lo + nt * 16 + n16) * kQStride + kk * 64 + g * 16);
-    }
-    __syncthreads();   // the epilogue reuses this memory
+            for (int kk = 0; kk < KK; ++kk)
+                qreg[nt][kk] = *reinterpret_cast<const bf16x8 *>(sh.q + (row_lo + nt * 16 + n16) * kQStride + kk * 64 + g * 16);
+        }
+        __syncthreads();   // the epilogue reuses this memory
+    };
 
-    for (int it0 = 0; it0 < my_pages; it0 += 2 * P) {
-        arrived(batch_a);
-        load_batch(it0 + P, batch_b);
-        consume_batch(batch_a, it0);
-        arrived(batch_b);
-        load_batch(it0 + 2 * P, batch_a);
-        consume_batch(batch_b, it0 + P);
+    if constexpr (STAGED) {
+        // The staged walk, for wave groups on token-major pages.  All groups need all pages, so the block loads each
+        // page once, a page per wavefront and round, DEPTH rounds ahead in registers, and hands it to the groups
+        // through LDS (two buffers, one barrier per round): whole rows go in, operands come out (K as 16
+        // bytes of a token row, V through the transposing LDS read; rows padded as above).  When every group loaded
+        // the pages for itself, half (three quarters) of the loads in flight were duplicates, K's came in
+        // half cache lines, and V was transposed once per group.  Attention alone, 64/8 heads, k = 7, 96 / 256
+        // requests of 256 to 1024 tokens: 82.8 -> 66.9 / 191.5 -> 145.2 us; 64/4 heads, k = 4 / 8: 81.3 -> 65.5 /
+        // 124.8 -> 113.1 us.  Pages in the matrix-operand layout gain less and not always (the same shapes: 64.5
+        // -> 65.6, 152.0 -> 143.6, 67.9 -> 65.0, 107.8 -> 109.4; two split requests 28.6 -> 30.0), so there every
+        // group still loads its operands itself.
+        constexpr int DEPTH = NT >= 3 && D == 128 ? 1 : 2;   // (three row tiles leave no registers for a second round)
+        constexpr int LR = D / 8;   // lanes per token row of a 1 KB load (16 bytes each)
+        const int rounds = (w.npages + kWaves - 1) / kWaves;
+        PageRegs<D> st[DEPTH];
+        auto store_page = [&](int buf, const PageRegs<D> &r) {
+#pragma unroll
+            for (int i = 0; i < KK; ++i) {
+                const int at = ((kWave / LR) * i + lane / LR) * kVtRowBytes + (lane % LR) * 16;
+                *reinterpret_cast<u32x4 *>(sh.ring[buf][wave][0] + at) = r.k[i];
+                *reinterpret_cast<u32x4 *>(sh.ring[buf][wave][1] + at) = r.v[i];
+            }
+        };
+        auto fetch_page = [&](int buf, int slot, PageRegs<D> &r) {
+            const unsigned char *ks = sh.ring[buf][slot][0], *vs = sh.ring[buf][slot][1];
+#pragma unroll
+            for (int i = 0; i < KK; ++i) {
+                r.k[i] = *reinterpret_cast<const u32x4 *>(ks + n16 * kVtRowBytes + i * 64 + g * 16);
+                const unsigned char *src = vs + (4 * g + (n16 >> 2)) * kVtRowBytes + (n16 & 3) * 8 + i * 64;
+                const u32x2 lo = read_transposed(src), hi = read_transposed(src + 32);
+                r.v[i] = (u32x4){lo.x, lo.y, hi.x, hi.y};
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) load_page(i, st[i]);
+        stage_q();
+        store_page(0, st[0]);
+        load_page(DEPTH, st[0]);
+        __syncthreads();
+        for (int t = 0; t < rounds; t += DEPTH) {
+#pragma unroll
+            for (int i = 0; i < DEPTH; ++i) {
+                const int round = t + i;
+                if (grp_rows > 0) {
+#pragma unroll 1
+                    for (int slot = pw; slot < kWaves; slot += PW) {
+                        const int page = round * kWaves + slot;
+                        if (page < w.npages) {
+                            PageRegs<D> cur;
+                            fetch_page(round & 1, slot, cur);
+                            consume(cur, page);
+                        }
+                    }
+                }
+                store_page((round + 1) & 1, st[(i + 1) % DEPTH]);
+                load_page(round + 1 + DEPTH, st[(i + 1) % DEPTH]);
+                __syncthreads();
+            }
+        }
+    } else {
+        // Two register batches of P pages each.  While one batch is consumed the loads of the
+        // other are in flight.  The order inside a half-step matters: first wait for the batch
+        // about to be consumed (at that point it is the only one outstanding, so the full
+        // wait the compiler emits waits for nothing else), then issue the other batch's loads,
+        // then do the arithmetic, which needs no further wait.
+        // pages per batch: two bring nothing once the launch keeps the memory system busy, except with the
+        // half-size pages of a head dim of 64 (the same bytes in flight per wavefront as at 128)
+        constexpr int P = D == 64 ? 2 : 1;
+        PageRegs<D> batch_a[P], batch_b[P];
+        auto load_batch = [&](int it, PageRegs<D>(&r)[P]) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) load_page(it + j, r[j]);
+        };
+        auto arrived = [&](PageRegs<D>(&r)[P]) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                if constexpr (KK == 4)
+                    asm volatile("" ::"v"(r[j].k[0]), "v"(r[j].k[1]), "v"(r[j].k[2]), "v"(r[j].k[3]), "v"(r[j].v[0]),
+                                 "v"(r[j].v[1]), "v"(r[j].v[2]), "v"(r[j].v[3])
+                                 : "memory");
+                else
+                    asm volatile("" ::"v"(r[j].k[0]), "v"(r[j].k[1]), "v"(r[j].v[0]), "v"(r[j].v[1]) : "memory");
+            }
+        };
+        auto consume_batch = [&](PageRegs<D>(&r)[P], int it) {
+#pragma unroll
+            for (int j = 0; j < P; ++j)
+                if (it + j < my_pages) consume(r[j], pw + PW * (it + j));
+        };
+        load_batch(0, batch_a);
+        stage_q();
+        for (int it0 = 0; it0 < my_pages; it0 += 2 * P) {
+            arrived(batch_a);
+            load_batch(it0 + P, batch_b);
+            consume_batch(batch_a, it0);
+            arrived(batch_b);
+            load_batch(it0 + 2 * P, batch_a);
+            consume_batch(batch_b, it0 + P);
+        }
     }
 
     attn_end<NT, WG, D>(p, w, acc, m_run, l_run, out_row, [](int mt, int gg) { return mt * 16 + 4 * gg; }, sh);
@@ -1642,7 +1724,7 @@ __device__ __forceinline__ void attn_f32_role(const AttnParams &p, OrderTable or
     constexpr int kQStride = f32_q_stride(D);
     constexpr int kPageHeadBytes = SPEC_BLOCK_SIZE * D * 4;
     AttnWork w;
-    if (!attn_begin<NT, WG>(p, order, item, w)) return;
+    if (!attn_begin<NT, WG, false>(p, order, item, w)) return;
     const int n16 = w.n16, g = w.g, L = w.L, my_pages = w.my_pages, bt = w.bt;
 
     const char *khead = static_cast<const char *>(p.k_cache) + (size_t)w.kvh * kPageHeadBytes;
