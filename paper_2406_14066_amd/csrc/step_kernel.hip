@@ -1029,13 +1029,15 @@ constexpr int o_stride(int D) { return D * 4 + 16; }   // bytes per fp32 output 
 // rows) the groups of one block read the same pages at the same time, so the pages cross the
 // memory interface once and the groups find each other's loads in the compute unit's cache or
 // in flight.
-// Token-major pages ([16 tokens][D dims] per page and KV head).  K is loaded straight into the
-// matrix operand order from that layout too (a lane's 16 bytes are 8 consecutive dims of one
-// token); V has to be transposed (the PV product wants, per lane, four consecutive tokens of one
-// dim): each wavefront loads its V page as whole rows (coalesced 16-byte loads), stages it in a
-// region of its own in LDS and reads it back two bytes at a time in operand order.  Token rows
-// are padded by 16 bytes (272 at D = 128): the 16 lanes of a row group then read 8 banks, and the
-// four row groups of a wavefront, 4 tokens apart, land 16 banks apart: no conflicts.
+// Token-major pages ([16 tokens][D dims] per page and KV head).  The matrix operands want, per lane, 8
+// consecutive dims of one token (K) and four consecutive tokens of one dim (V).  Each wavefront loads its page as
+// whole rows (1 KB per load, 16 bytes per lane), stages it in a region of its own in LDS and reads it back in operand
+// order, V through the transposing read.  (K can be loaded in operand order directly, but each load then
+// touches 16 half cache lines, and the other halves have often left the cache by the time the next load wants
+// them.  Attention alone: 64 requests on 32/8 heads of 64, k = 3: 31.3 -> 28.7 us; 24 on 64/8 heads, k = 4:
+// 62.6 -> 58.1; four of 20 to 28 k tokens on 32/8 heads, k = 8: 95.0 -> 87.7; 256 on 64/8 heads, k = 2, which the
+// memory system bounds already: 120.5 -> 119.7.)  Token rows are padded by 16 bytes
+// (272 at D = 128) so that neither the row writes nor the operand reads have bank conflicts.
 constexpr int vt_row_bytes(int D) { return D * 2 + 16; }
 constexpr int vt_wave_bytes(int D) { return SPEC_BLOCK_SIZE * vt_row_bytes(D); }
 // Which blocks walk their pages staged (see the staged walk in attn_role).
@@ -1048,6 +1050,7 @@ struct AttnShared {
     union {
         // staged walk: two rounds of a page per wavefront, K and V
         unsigned char ring[kStaged ? 2 : 1][kStaged ? kWaves : 1][2][kStaged ? vt_wave_bytes(D) : 16];
+        alignas(16) unsigned char vt[TM && !kStaged ? 2 * kWaves * vt_wave_bytes(D) : 16];   // token-major pages: K and V staged per wavefront
         f32x4 acc[2][NT][D / 16][kWave];          // epilogue: partial results of the wavefronts being merged
         unsigned char q[kRowsMax * q_stride(D)];  // prologue: the block's query rows
         unsigned char o[WG == 1 ? NT * 16 * o_stride(D) : 16];   // epilogue of an unsplit request (one group): the output tile
@@ -1055,7 +1058,6 @@ struct AttnShared {
     float m[2][NT][kWave];
     float l[2][NT][kWave];
     int last;
-    alignas(16) unsigned char vt[TM && !kStaged ? kWaves * vt_wave_bytes(D) : 16];   // token-major pages: V staged per wavefront
 };
 
 // The order in which the attention items take the requests (longest first), as the kernel
@@ -1436,15 +1438,8 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             const_cast<char *>(khead + (size_t)page * page_stride), 0, bytes, kBufferFlags);
         const __amdgpu_buffer_rsrc_t vd = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(vhead + (size_t)page * page_stride), 0, bytes, kBufferFlags);
-        if constexpr (TM && !STAGED) {
-            // K: token n16, dims 32 i + 8 g .. + 7 sit at n16 * 2 D + 64 i + 16 g
 #pragma unroll
-            for (int i = 0; i < KK; ++i)
-                r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(kd, n16 * (D * 2) + g * 16, i * 64, kStreamPolicy);
-        } else {
-#pragma unroll
-            for (int i = 0; i < KK; ++i) r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(kd, lane_off, i * 1024, kStreamPolicy);
-        }
+        for (int i = 0; i < KK; ++i) r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(kd, lane_off, i * 1024, kStreamPolicy);
         // V: in operand order already, or (token-major) as whole rows: with D / 8 lanes per row, lane L of load i holds
         // token (512 / D) i + 8 L / D, dims 8 (L % (D / 8)) .. + 7
 #pragma unroll
@@ -1471,31 +1466,25 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         const int tbase = page_tok + 4 * g;
 
         if constexpr (TM && !STAGED) {
-            // V through this wavefront's LDS region: rows in, operand order out (LDS executes a
-            // wavefront's accesses in order, so the reads see the writes without a barrier)
-            unsigned char *vl = sh.vt + wave * kVtWaveBytes;
+            // through this wavefront's LDS region: rows in, operand order out (LDS executes a wavefront's
+            // accesses in order, so the reads see the writes without a barrier)
+            unsigned char *kl = sh.vt + wave * (2 * kVtWaveBytes), *vl = kl + kVtWaveBytes;
             constexpr int LR = D / 8;   // lanes per token row of a 1 KB load (16 bytes each)
 #pragma unroll
-            for (int i = 0; i < KK; ++i)
-                *reinterpret_cast<u32x4 *>(vl + ((kWave / LR) * i + lane / LR) * kVtRowBytes + (lane % LR) * 16) = cur.v[i];
+            for (int i = 0; i < KK; ++i) {
+                const int at = ((kWave / LR) * i + lane / LR) * kVtRowBytes + (lane % LR) * 16;
+                *reinterpret_cast<u32x4 *>(kl + at) = cur.k[i];
+                *reinterpret_cast<u32x4 *>(vl + at) = cur.v[i];
+            }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const unsigned char *src = vl + (4 * g) * kVtRowBytes + n16 * 2;
 #pragma unroll
-            for (int pp = 0; pp < KK; ++pp) {
-                uint32_t w[4];
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf) {
-                    const unsigned char *e = src + (32 * pp + 16 * hf) * 2;
-                    const uint32_t t0 = *reinterpret_cast<const uint16_t *>(e);
-                    const uint32_t t1 = *reinterpret_cast<const uint16_t *>(e + kVtRowBytes);
-                    const uint32_t t2 = *reinterpret_cast<const uint16_t *>(e + 2 * kVtRowBytes);
-                    const uint32_t t3 = *reinterpret_cast<const uint16_t *>(e + 3 * kVtRowBytes);
-                    w[2 * hf + 0] = t0 | (t1 << 16);
-                    w[2 * hf + 1] = t2 | (t3 << 16);
-                }
-                cur.v[pp] = (u32x4){w[0], w[1], w[2], w[3]};
+            for (int i = 0; i < KK; ++i) {
+                cur.k[i] = *reinterpret_cast<const u32x4 *>(kl + n16 * kVtRowBytes + i * 64 + g * 16);
+                const unsigned char *src = vl + (4 * g + (n16 >> 2)) * kVtRowBytes + (n16 & 3) * 8 + i * 64;
+                const u32x2 lo = read_transposed(src), hi = read_transposed(src + 32);
+                cur.v[i] = (u32x4){lo.x, lo.y, hi.x, hi.y};
             }
         }
 
@@ -1677,6 +1666,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         }
     }
 
+    if constexpr (TM && !STAGED) __syncthreads();   // every wavefront is done with its staging region: the epilogue reuses the memory
     attn_end<NT, WG, D>(p, w, acc, m_run, l_run, out_row, [](int mt, int gg) { return mt * 16 + 4 * gg; }, sh);
 }
 
