@@ -266,7 +266,9 @@ __global__ __launch_bounds__(kRepackWaves *kWave) void kv_repack_kernel(const ui
     }
 }
 
-// KV append: one thread per (packed row, kv head, group of 8 elements).
+// KV append: one thread per (packed row, kv head, group of 8 elements).  Latency is what a launch of this size takes: the
+// chain of dependent loads before the stores, and the stores of V in the tiled layout.  256 requests, k = 4, 8
+// heads of 128, tiled pages: 8.98 -> 7.50 us per call, of which the host takes 7.
 template <typename T>
 __global__ void kv_append_kernel(KvAppendParams p)
 {
@@ -277,9 +279,28 @@ __global__ void kv_append_kernel(KvAppendParams p)
     const int g = (int)(idx % groups);
     const int kvh = (int)((idx / groups) % p.Hkv);
     const int row = (int)(idx / ((size_t)groups * p.Hkv));
-    const int b = find_request(p.cu_q_len, p.B, p.T, row);
-    const int q_len = p.cu_q_len[b + 1] - p.cu_q_len[b];
-    const int pos = p.kv_len[b] - q_len + (row - p.cu_q_len[b]);
+    // The rows to move do not depend on where they go, and with one draft length for all requests the first guess
+    // of the request is right: both are fetched at once with the guess's length, so that two dependent
+    // round trips (lengths, page index) are left before the stores instead of four.
+    struct alignas(8 * sizeof(T)) Vec8 { T e[8]; };
+    const size_t from = ((size_t)row * p.Hkv + kvh) * p.d;
+    const Vec8 new_k = *reinterpret_cast<const Vec8 *>(static_cast<const T *>(p.new_k) + from + g * 8);
+    Vec8 new_v;
+    if (p.kv_layout == SPEC_KV_TOKEN_MAJOR) {
+        new_v = *reinterpret_cast<const Vec8 *>(static_cast<const T *>(p.new_v) + from + g * 8);
+    } else {   // every groups-th dim: the stores below then fall into 2 cache lines per row and instruction, not 16
+#pragma unroll
+        for (int e = 0; e < 8; ++e) new_v.e[e] = static_cast<const T *>(p.new_v)[from + g + e * groups];
+    }
+    int b = min((int)(((long long)row * p.B) / p.T), p.B - 1);
+    int begin = p.cu_q_len[b], end = p.cu_q_len[b + 1], len = p.kv_len[b];
+    if (begin > row || row >= end) {
+        b = find_request(p.cu_q_len, p.B, p.T, row);
+        begin = p.cu_q_len[b];
+        end = p.cu_q_len[b + 1];
+        len = p.kv_len[b];
+    }
+    const int pos = len - (end - begin) + (row - begin);
     // position and page index come from device memory: a row that would land outside the
     // request's block-table row or outside the pool is not written, and counted
     int page = -1;
@@ -290,20 +311,16 @@ __global__ void kv_append_kernel(KvAppendParams p)
         return;
     }
     const int slot = pos % SPEC_BLOCK_SIZE;
-    const T *sk = static_cast<const T *>(p.new_k) + ((size_t)row * p.Hkv + kvh) * p.d + g * 8;
-    const T *sv = static_cast<const T *>(p.new_v) + ((size_t)row * p.Hkv + kvh) * p.d + g * 8;
     T *dk = static_cast<T *>(p.k_cache);
     T *dv = static_cast<T *>(p.v_cache);
     // the 8 elements of a thread are contiguous in the cache in every case but one (V in the tiled
     // layout, where consecutive dims of a token are 16 bytes apart): whole-vector stores where they are
-    struct alignas(8 * sizeof(T)) Vec8 { T e[8]; };
-    *reinterpret_cast<Vec8 *>(dk + k_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = *reinterpret_cast<const Vec8 *>(sk);
+    *reinterpret_cast<Vec8 *>(dk + k_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = new_k;
     if (p.kv_layout == SPEC_KV_TOKEN_MAJOR) {
-        *reinterpret_cast<Vec8 *>(dv + v_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = *reinterpret_cast<const Vec8 *>(sv);
+        *reinterpret_cast<Vec8 *>(dv + v_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = new_v;
     } else {
-        const Vec8 v = *reinterpret_cast<const Vec8 *>(sv);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dv[v_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8 + e, p.d)] = v.e[e];
+        for (int e = 0; e < 8; ++e) dv[v_index(p.kv_layout, page, p.Hkv, kvh, slot, g + e * groups, p.d)] = new_v.e[e];
     }
 }
 
