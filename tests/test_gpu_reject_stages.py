@@ -97,3 +97,21 @@ def test_requests_grouped_in_the_final_stage(harness, B, mode):
             if mode == sv.ACCEPT_POINT_DRAFT:
                 ref = oracle.reject_onehot(w.target_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
             check_reject(w, res, ref=ref, max_excluded=1)
+
+
+def test_offsets_far_apart_and_segments_of_nothing(harness):
+    """Row statistics whose segments differ by thousands of powers of two, and segments of nothing but -inf: the
+    accept chain rescales them exactly (a segment far below the row's maximum adds nothing)."""
+    print("case far offsets", flush=True)
+    w = _logits_only(3, 32768, [4, 2, 8], seed=3)
+    V = w.V
+    w.target_logits[:, : V // 4] -= 3000.0
+    w.draft_logits[:, : V // 4] -= 3000.0
+    w.target_logits[:, V // 4: V // 2] = -np.inf
+    w.draft_logits[:, V // 4: V // 2] = -np.inf
+    rng = np.random.default_rng(0)
+    w.draft_tokens = rng.integers(V // 2, V, size=w.T - w.B).astype(np.int32)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    assert ds.plan()["stat_segments"] >= 4
+    ds.run_reject()
+    check_reject(w, ds.results())
