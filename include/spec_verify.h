@@ -37,10 +37,9 @@
  *   - Speed: bf16 runs on the matrix-instruction kernel, the whole step in one
  *     launch, for every draft length and group width within the limits (up to
  *     9 * 16 fused rows per KV head) and both head dims: fastest with pages in
- *     the SPEC_KV_MFMA layout; token-major pages take the same kernel, 3 to 8%
- *     slower up to 48 fused rows and about 20% slower beyond (V is transposed
- *     through LDS inside the kernel).  fp32 (token-major pages) has a one-launch
- *     kernel of its own.  spec_verify_plan tells which path a call takes.
+ *     the SPEC_KV_MFMA layout; token-major pages take the same kernel, 1 to 5%
+ *     slower (K and V pass through LDS inside the kernel).  fp32 (token-major
+ *     pages) has a one-launch kernel of its own.  spec_verify_plan tells which path a call takes.
  */
 #ifndef SPEC_VERIFY_H
 #define SPEC_VERIFY_H
