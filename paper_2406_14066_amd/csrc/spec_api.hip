@@ -445,11 +445,13 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
 
     // Early stop: with one draft length for all requests the statistics items can be taken in
     // position order and the rows after a request's first rejection left unread.  That turns the
-    // pass into a chain of k+1 dependent stages (about 12 us each, then the race), which must stay
-    // hidden: under a launch that streams (KV and logit bytes at 5.5 TB/s) for clearly longer than
-    // the chain takes (the rejection half alone: see below).  Measured (step with / without): B=256 k=2 (64/8 heads) -4%, the same at k=7 -15%,
-    // B=64 k=8 (32/32 heads, L=1024) -8%, B=64 k=4 -3%, B=32 k=1..3 -2%, B=32 k=4 +2%, B=32 k=8 +16%,
-    // B=16 k=2 (L=2048) +2%, B=8 k=4 +32%.
+    // pass into a chain of k+1 dependent stages (then the race), which must stay mostly hidden under the launch's
+    // streams (KV and logit bytes at 5.5 TB/s), the more logits it may save the less so; the rejection half
+    // alone: see below.  Step without / with, in us: 64/8 heads, B=96 k=7 102 / 94 (at an acceptance rate of 0.9
+    // instead of 0.7 103 / 109, and B=128 below 88 / 88: long chains are left out), k=3 64 / 64, B=64 k=7 72 / 96,
+    // B=48 k=7 57 / 79, B=128 L=512 k=4 87 / 80, B=256 k=2 156 / 149, V=128256 B=64 k=4 113 / 136; 32/8 heads, B=128
+    // L=512 k=2 64 / 61; 32/32 heads, L=1024, B=32 k=2 / 4 / 8 94 / 92, 97 / 95, 103 / 104, B=64 k=4 / 8 181 / 178,
+    // 199 / 182, B=16 L=2048 k=2 96 / 104.
     pl.early_stop = 0;
     pl.uniform_k = 0;
     if (r->T > r->B && r->T % r->B == 0) {
@@ -459,7 +461,9 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
         bool wanted;
         if (attn_us >= 0.0) {
             const double logits_us = (double)rows * r->V * 4.0 / 5.5e6;
-            wanted = r->B >= 32 && 12.0 * q + 30.0 <= 0.85 * (attn_us + logits_us);
+            // a stage: a block reads its segment at its share of the memory's rate (12.5 KB per microsecond), and a hop
+            const double chain_us = q * (2.0 + pl.stat_seg_len * 4.0 / 12500.0) + 30.0;
+            wanted = r->B >= 32 && chain_us <= 0.9 * attn_us + 2.5 * logits_us;
         } else {
             // One stage per position: it streams what is still needed of its rows (at an acceptance rate of 0.7),
             // in 6 us at least, and has a block per compute unit.  Against all rows in one go, in one
