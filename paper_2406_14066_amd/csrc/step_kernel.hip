@@ -7,11 +7,11 @@
 //
 //   statistics   one (logit row, vocabulary segment) each: offset and sum of
 //                exponentials, published with the call's generation tag.
-//   race         one (request, vocabulary segment) each: recomputes the request's
-//                (cheap) accept chain from the published statistics, then races
+//   race         one (request, vocabulary segment) each: computes its random variates, recomputes the
+//                request's (cheap) accept chain from the published statistics, then races
 //                its segment for the next token.
-//   final        one per request: picks the race winner, writes the request's
-//                outputs and counters.
+//   final        one per group of requests: picks the race winners, writes the requests'
+//                outputs and adds up their counters.
 //   attention    one (request, KV head, KV chunk) each; the block that completes
 //                the LAST chunk of a (request, KV head) merges the chunk partials
 //                and writes the output.
