@@ -1323,7 +1323,11 @@ __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w,
     // Last chunk of this (request, KV head) to finish: merge all chunks in chunk order.
     // Half a wavefront takes two query rows at a time (four head dims per lane) and eight
     // chunks of each per pass; every load of a pass is issued before the first is used, so
-    // a pass costs one memory round trip.
+    // a pass costs one memory round trip.  (Lanes past the last row or past a head dim of 64 load what the
+    // first ones do and store nothing: with conditions of their own the loads took a branch each.  Eight requests on
+    // 64/8 heads of 128, k = 1, two chunks: 10.94 -> 10.75 us; 16 on 32/8 heads of 64, k = 8: 15.8 -> 14.7.  With two
+    // rows in flight of 128 dims, where those loads are too many, it costs 2%: 75.1 / 77.3 us for four of 6000
+    // tokens on 64/4 heads, k = 8.)
     constexpr int GROUP = 8;   // chunks merged per pass (16 per pass spill 200 to 340 bytes per lane)
     constexpr int RB = NT >= 2 ? 2 : 1;   // rows in flight per half wavefront (one row tile: at most two passes anyway, and registers are tight)
     const int half = lane >> 5, l32 = lane & 31;
@@ -1342,7 +1346,7 @@ __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w,
             rh[j] = (size_t)(row0 + rr / group) * p.Hq + kvh * group + rr % group;
             const size_t base = rh[j] * p.max_chunks;
             ml[j] = reinterpret_cast<const unsigned long long *>(p.ws_ml) + base;
-            pa[j] = reinterpret_cast<const unsigned long long *>(p.ws_acc) + base * (D / 2) + 2 * l32;
+            pa[j] = reinterpret_cast<const unsigned long long *>(p.ws_acc) + base * (D / 2) + 2 * (l32 % (D / 4));
             mx[j] = kEmptyMax;
             denom[j] = 0.0f;
             o[j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
@@ -1353,10 +1357,21 @@ __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w,
             for (int j = 0; j < RB; ++j) {
 #pragma unroll
                 for (int c = 0; c < GROUP; ++c) {
-                    const bool on = rv[j] && c0 + c < nchunks;
-                    mlv[j][c] = on ? fetch_u64(ml[j] + c0 + c) : pack_f32x2(kEmptyMax, 0.0f);
-                    a0[j][c] = on && dims_on ? fetch_u64(pa[j] + (size_t)(c0 + c) * (D / 2)) : 0ull;
-                    a1[j][c] = on && dims_on ? fetch_u64(pa[j] + (size_t)(c0 + c) * (D / 2) + 1) : 0ull;
+                    const unsigned long long *al = pa[j] + (size_t)(c0 + c) * (D / 2);
+                    if constexpr (RB == 1 || D < 4 * 32) {
+                        mlv[j][c] = pack_f32x2(kEmptyMax, 0.0f);
+                        a0[j][c] = a1[j][c] = 0ull;
+                        if (c0 + c < nchunks) {   // the same for the whole block: one branch for the three
+                            mlv[j][c] = fetch_u64(ml[j] + c0 + c);
+                            a0[j][c] = fetch_u64(al);
+                            a1[j][c] = fetch_u64(al + 1);
+                        }
+                    } else {
+                        const bool on = rv[j] && c0 + c < nchunks;
+                        mlv[j][c] = on ? fetch_u64(ml[j] + c0 + c) : pack_f32x2(kEmptyMax, 0.0f);
+                        a0[j][c] = on ? fetch_u64(al) : 0ull;
+                        a1[j][c] = on ? fetch_u64(al + 1) : 0ull;
+                    }
                 }
             }
 #pragma unroll
