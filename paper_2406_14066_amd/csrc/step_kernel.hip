@@ -52,6 +52,7 @@
 // per decision (segment sums, log-sum-exp, p/q of the draft token, the comparison
 // with u) is fp64.
 #include "common.h"
+#include "grid_split.h"
 
 #include <hip/hip_ext.h>
 
@@ -2081,13 +2082,7 @@ dim3 fill_args(StepArgs &args, const AttnParams &ap, const RejectParams &rp, int
     const bool reject_first = HAS_ATTN && HAS_REJECT && n_reject <= ap.reject_first_limit;
     if (reject_first) gs.attn_first = 0;
     const bool mixed = HAS_ATTN && HAS_REJECT && !gs.attn_first;
-    // The rejection stages of a request wait for each other, so the last rejection item sits
-    // well before the end of the grid: the tail of the launch is attention only.
     const int rows_attn_all = (n_attn + kXcds - 1) / kXcds;
-    gs.rows_attn_mixed = (int)(rows_attn_all * (double)ap.reject_span);
-    if (gs.rows_attn_mixed < 1) gs.rows_attn_mixed = 1;
-    if (gs.rows_attn_mixed > rows_attn_all) gs.rows_attn_mixed = rows_attn_all;
-    if (reject_first) gs.rows_attn_mixed = 0;
     // XCDs 1, 3, 5, 7 of this device stream from memory some 6% slower than XCDs 0, 2, 4, 6 (block
     // traces of equal attention blocks), and a launch ends with its slowest XCD.  When there is at
     // most one attention block per compute unit (all resident from the start, the rejection blocks
@@ -2097,6 +2092,7 @@ dim3 fill_args(StepArgs &args, const AttnParams &ap, const RejectParams &rp, int
     // with two per compute unit, 15% slower where the rejection half is a fifth of the step.)
     gs.reject_cols = (HAS_ATTN && HAS_REJECT && ap.reject_even_xcds && n_attn <= ap.reject_even_limit && !reject_first) ? kXcds / 2 : kXcds;
     const int rows_reject = (n_reject + gs.reject_cols - 1) / gs.reject_cols;
+    gs.rows_attn_mixed = reject_first ? 0 : attention_rows_mixed(rows_attn_all, rows_reject, ap.reject_span);
     return dim3(mixed ? (rows_attn_all + rows_reject) * kXcds
                           : (HAS_ATTN && HAS_REJECT ? (rows_attn_all + rows_reject) * kXcds : n_reject + n_attn));
 }
