@@ -425,11 +425,18 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     seg_len = (seg_len + 3) / 4 * 4;
     pl.stat_seg_len = seg_len;
     pl.stat_segments = (r->V + seg_len - 1) / seg_len;
+    // (how long the launch streams when an attention half runs beside: KV and logit bytes at 5.5 TB/s)
+    const double logits_us = (double)rows * r->V * 4.0 / 5.5e6;
     // race: segments of >= 2048 vocabulary ids, at most 64 per request; about 1024 blocks in all when the
     // rejection half runs alone (what 4 blocks per compute unit hold: 256 / 512 / 1024 / 1536 blocks 59.3 / 53.8 /
-    // 51.4 / 52.4 us for 256 requests, k = 2, V = 32000), about 256 beside an attention half, where every block
-    // holds a slot of the attention's while it waits (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
-    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7)
+    // 51.4 / 52.4 us for 256 requests, k = 2, V = 32000).  Beside an attention half, where every block
+    // holds a slot of the attention's while it waits, about 256 (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
+    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7), or 512 where the segments
+    // of 256 blocks are longer than 16384 ids and take, at a block's share of the memory's rate (12.5 KB per microsecond),
+    // more than 0.18 of the launch: the last request's race then ends the launch.  64/8 heads, 400 tokens, k = 1,
+    // 256 / 512 blocks (and that share): V = 64128, 128 requests 70.3 / 59.2 us (0.36), 256 132.9 / 117.1 (0.37); V = 128256,
+    // 64 requests 52.8 / 44.2 (0.55), 128 118.7 / 89.6 (0.55); 2000 tokens, k = 4, V = 128256, 24 requests
+    // 76.5 / 77.0 (0.08); V = 32000, 256 requests 91.9 / 94.8 (0.22), 64 (segments of 8192) 28.5 / 32.3.
     const auto race_split = [&](int blocks, int multiple, int &segments, int &len) {
         int n = std::min({(blocks + r->B - 1) / r->B, (r->V + 2047) / 2048, 64});
         if (n < 1) n = 1;
@@ -438,6 +445,10 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     };
     // (a block takes 1024 ids at a time)
     race_split(tu.race_blocks > 0 ? tu.race_blocks : (attn_us < 0.0 ? 1024 : 256), 1024, pl.race_segments, pl.race_seg_len);
+    if (tu.race_blocks == 0 && attn_us >= 0.0 && pl.race_seg_len > 16384) {
+        const double race_us = pl.race_seg_len * (r->accept_mode == SPEC_ACCEPT_SAMPLE ? 8.0 : 4.0) / 12500.0;
+        if (race_us > 0.18 * (attn_us + logits_us)) race_split(512, 1024, pl.race_segments, pl.race_seg_len);
+    }
     // requests per item of the final stage: as many as leave 8 items (the kernel says why they are grouped)
     pl.final_shift = 0;
     while (pl.final_shift < kMaxFinalShift && (16 << pl.final_shift) <= r->B && (pl.stat_segments << (pl.final_shift + 1)) <= 32)
@@ -460,7 +471,6 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
         for (int b = 0; b < r->B && uniform; ++b) uniform = r->host_cu_q_len[b + 1] - r->host_cu_q_len[b] == q;
         bool wanted;
         if (attn_us >= 0.0) {
-            const double logits_us = (double)rows * r->V * 4.0 / 5.5e6;
             // a stage: a block reads its segment at its share of the memory's rate (12.5 KB per microsecond), and a hop
             const double chain_us = q * (2.0 + pl.stat_seg_len * 4.0 / 12500.0) + 30.0;
             wanted = r->B >= 32 && chain_us <= 0.9 * attn_us + 2.5 * logits_us;
