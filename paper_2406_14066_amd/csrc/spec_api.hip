@@ -405,18 +405,21 @@ double attn_estimate_us(const spec_attn_args *a)
 }
 
 // attn_us: rough duration of the attention half that runs in the same launch (microseconds), or
-// negative if the rejection half runs alone.
-RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0)
+// negative if the rejection half runs alone.  few_records: alone, but with no more statistics and race blocks than beside
+// an attention half (at most two per compute unit), for a workspace that has no room for more.
+RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0, bool few_records = false)
 {
     RejectPlan pl;
     memset(&pl, 0, sizeof pl);
     // logit rows that get a statistics pass: the draft rows only when there is a draft distribution
     const int rows = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * r->T - r->B : r->T;
-    // statistics: segments of >= 8192 logits, at most 32 per row; about 1024 blocks in all when the rejection half runs
-    // alone (what 4 blocks per compute unit hold; with fewer, some units get two rows and others one: 48
-    // requests, V = 128256, 256 / 1024 / 2048 blocks 50.7 / 48.2 / 49.5 us, 16 of them at k = 4 29.1 / 26.7 / 29.2),
-    // about 256 beside an attention half
-    int segs = ((attn_us < 0.0 ? 1024 : 256) + rows - 1) / rows;
+    // statistics: segments of >= 8192 logits, at most 32 per row; about 4 blocks per compute unit (what one holds) when the
+    // rejection half runs alone (with fewer, some units get two rows and others one: 48
+    // requests, V = 128256, 256 / 1024 / 2048 blocks on 256 units 50.7 / 48.2 / 49.5 us, 16 of them at k = 4 29.1 / 26.7 / 29.2),
+    // about one beside an attention half
+    const int cus = compute_units();
+    const bool many = attn_us < 0.0 && !few_records;
+    int segs = ((many ? 4 * cus : cus) + rows - 1) / rows;
     const int max_by_len = (r->V + 8191) / 8192;
     if (segs > max_by_len) segs = max_by_len;
     if (segs > 32) segs = 32;
@@ -427,12 +430,12 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     pl.stat_segments = (r->V + seg_len - 1) / seg_len;
     // (how long the launch streams when an attention half runs beside: KV and logit bytes at 5.5 TB/s)
     const double logits_us = (double)rows * r->V * 4.0 / 5.5e6;
-    // race: segments of >= 2048 vocabulary ids, at most 64 per request; about 1024 blocks in all when the
-    // rejection half runs alone (what 4 blocks per compute unit hold: 256 / 512 / 1024 / 1536 blocks 59.3 / 53.8 /
+    // race: segments of >= 2048 vocabulary ids, at most 64 per request; about 4 blocks per compute unit when the
+    // rejection half runs alone (256 / 512 / 1024 / 1536 blocks on 256 units 59.3 / 53.8 /
     // 51.4 / 52.4 us for 256 requests, k = 2, V = 32000).  Beside an attention half, where every block
-    // holds a slot of the attention's while it waits, about 256 (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
-    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7), or 512 where the segments
-    // of 256 blocks are longer than 16384 ids and take, at a block's share of the memory's rate (12.5 KB per microsecond),
+    // holds a slot of the attention's while it waits, about one (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
+    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7), or two where the segments
+    // are longer than 16384 ids and take, at a block's share of the memory's rate (12.5 KB per microsecond),
     // more than 0.18 of the launch: the last request's race then ends the launch.  64/8 heads, 400 tokens, k = 1,
     // 256 / 512 blocks (and that share): V = 64128, 128 requests 70.3 / 59.2 us (0.36), 256 132.9 / 117.1 (0.37); V = 128256,
     // 64 requests 52.8 / 44.2 (0.55), 128 118.7 / 89.6 (0.55); 2000 tokens, k = 4, V = 128256, 24 requests
@@ -444,10 +447,10 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
         segments = (int)(((int64_t)r->V + len - 1) / len);
     };
     // (a block takes 1024 ids at a time)
-    race_split(tu.race_blocks > 0 ? tu.race_blocks : (attn_us < 0.0 ? 1024 : 256), 1024, pl.race_segments, pl.race_seg_len);
+    race_split(tu.race_blocks > 0 ? tu.race_blocks : (many ? 4 * cus : (few_records ? 2 * cus : cus)), 1024, pl.race_segments, pl.race_seg_len);
     if (tu.race_blocks == 0 && attn_us >= 0.0 && pl.race_seg_len > 16384) {
         const double race_us = pl.race_seg_len * (r->accept_mode == SPEC_ACCEPT_SAMPLE ? 8.0 : 4.0) / 12500.0;
-        if (race_us > 0.18 * (attn_us + logits_us)) race_split(512, 1024, pl.race_segments, pl.race_seg_len);
+        if (race_us > 0.18 * (attn_us + logits_us)) race_split(2 * cus, 1024, pl.race_segments, pl.race_seg_len);
     }
     // requests per item of the final stage: as many as leave 8 items (the kernel says why they are grouped)
     pl.final_shift = 0;
@@ -503,6 +506,20 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     return pl;
 }
 
+// The most that the rejection half alone takes with this vocabulary, at this batch or any smaller one (fewer rows get more
+// segments each, so the records of one batch alone would not do: an engine sizes its workspace once, for its largest).
+size_t reject_room(const spec_reject_args *r, const Tuning &tu)
+{
+    const size_t rows = (size_t)(r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * (int64_t)r->T - r->B : r->T), B = (size_t)r->B;
+    const size_t slots = 4 * (size_t)compute_units();
+    const size_t stat_most = std::min<size_t>(((size_t)r->V + 8191) / 8192, 32);
+    const size_t race_most = std::min<size_t>(((size_t)r->V + 2047) / 2048, 64);
+    const size_t race_blocks = tu.race_blocks > 0 ? (size_t)tu.race_blocks : std::max<size_t>(slots, 512);
+    const size_t stats = std::min(rows * stat_most, rows + slots - 1);
+    const size_t race = std::min(B * race_most, B + race_blocks - 1);
+    return align_up(stats * kStatWords * sizeof(unsigned long long)) + align_up((race * 2 + B) * sizeof(unsigned long long));
+}
+
 // Requests by falling KV length (stable; from the host copy of kv_len).  The grid takes the
 // attention items in this order: blocks that run at the same time then take about
 // equally long, which the in-order hardware dispatcher needs to keep its block slots
@@ -536,8 +553,9 @@ struct StepPlan {
     bool has_attn = false, has_reject = false;
     AttnPlan apl;
     RejectPlan rpl;
+    RejectPlan rpl_small;           // for workspaces without room for rpl (never larger than rpl)
     UnitOrder order;
-    size_t workspace_bytes = 0;     // what callers are told: enough for this call and for its rejection half alone
+    size_t workspace_bytes = 0;     // what callers are told: enough for this call, and for its rejection half alone at this batch or a smaller one
     // (for telling a hash collision from a hit)
     int32_t B = 0, T = 0, V = 0;
 };
@@ -621,12 +639,22 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
         if (e.apl.use_mfma) make_order(a, e.order);
         base = e.apl.total_bytes;
     }
-    if (r != nullptr)
-        e.rpl = plan_reject(r, base, tu, (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0);
-    e.workspace_bytes = base + (r != nullptr ? e.rpl.total_bytes : 0);
-    // (a workspace made for the step also serves its rejection half alone, which may race in more segments)
-    if (a != nullptr && r != nullptr) e.workspace_bytes = std::max(e.workspace_bytes, plan_reject(r, 0, tu).total_bytes);
+    e.workspace_bytes = base;
+    if (r != nullptr) {
+        const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
+        e.rpl = plan_reject(r, base, tu, attn_us);
+        e.rpl_small = attn_us < 0.0 ? plan_reject(r, base, tu, attn_us, true) : e.rpl;
+        if (e.rpl_small.total_bytes > e.rpl.total_bytes) e.rpl_small = e.rpl;
+        e.workspace_bytes = std::max(base + e.rpl.total_bytes, (attn_us < 0.0 ? base : 0) + reject_room(r, tu));
+    }
     return e;
+}
+
+// The rejection half's plan on a workspace of `have` bytes.  The blocks of a half that runs alone are chosen for speed, and
+// their records take more room than those of few blocks: a workspace that holds only the latter still serves.
+const RejectPlan &reject_plan_for(const StepPlan &plan, size_t have)
+{
+    return plan.rpl.stats_off + plan.rpl.total_bytes <= have ? plan.rpl : plan.rpl_small;
 }
 
 // Tag of a call's tickets (see step_kernel.hip); unique per call within the process, never 0.
@@ -741,7 +769,7 @@ spec_status step_on_workspace(const spec_attn_args *attn, const spec_reject_args
                               void *workspace, size_t workspace_bytes, void *hip_stream)
 {
     const AttnPlan &apl = plan.apl;
-    const RejectPlan &rpl = plan.rpl;
+    const RejectPlan &rpl = reject_plan_for(plan, workspace_bytes);
     const spec_status st = check_workspace(workspace, workspace_bytes, apl.total_bytes + rpl.total_bytes);
     if (st != SPEC_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -866,7 +894,7 @@ spec_status spec_reject_sample(const spec_reject_args *reject, void *workspace, 
     if (plan.status != SPEC_OK) return plan.status;
     st = validate_reject_tokens(reject);
     if (st != SPEC_OK) return st;
-    const RejectPlan &pl = plan.rpl;
+    const RejectPlan &pl = reject_plan_for(plan, workspace_bytes);
     st = check_workspace(workspace, workspace_bytes, pl.total_bytes);
     if (st != SPEC_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -891,7 +919,7 @@ spec_status spec_verify_step_static(const spec_attn_args *attn, const spec_rejec
     const StepPlan *plan = nullptr;
     const spec_status st = prepare_step(attn, reject, plan);
     if (st != SPEC_OK) return st;
-    if (plan->apl.total_bytes + plan->rpl.total_bytes > SPEC_STATIC_SCRATCH_BYTES) return SPEC_EWORKSPACE;
+    if (plan->apl.total_bytes + plan->rpl_small.total_bytes > SPEC_STATIC_SCRATCH_BYTES) return SPEC_EWORKSPACE;
     void *ws = static_scratch_of_current_device();
     if (ws == nullptr) return SPEC_EHIP;
     return step_on_workspace(attn, reject, *plan, ws, SPEC_STATIC_SCRATCH_BYTES, hip_stream);

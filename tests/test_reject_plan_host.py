@@ -1,6 +1,9 @@
 """How the planner splits the rejection half (host only: plans are made without a GPU)."""
+import ctypes as C
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2406_14066_amd import spec_verify as sv
 
@@ -46,3 +49,54 @@ def test_large_vocabulary_beside_a_short_attention_half(B, k, length, V, least):
                                                    (128, 4, 400, 32000, 2)])
 def test_few_race_blocks_beside_a_long_attention_half(B, k, length, V, segments):
     assert step_plan(B, k, length, V)["race_segments"] == segments
+
+
+def small_records(B, k, V, mode=sv.ACCEPT_SAMPLE):
+    """Bytes of the rejection half's records with about 256 statistics and 512 race blocks: the least that
+    the half alone works with."""
+    rows = (2 * k + 1) * B if mode == sv.ACCEPT_SAMPLE else (k + 1) * B
+
+    def split(blocks, n, least, most):
+        segs = max(1, min((blocks + n - 1) // n, (V + least - 1) // least, most))
+        length = ((V + segs - 1) // segs + 3) // 4 * 4
+        return (V + length - 1) // length
+
+    def align(n):
+        return (n + 255) // 256 * 256
+
+    return align(24 * rows * split(256, rows, 8192, 32)) + align(8 * (2 * B * split(512, B, 2048, 64) + B))
+
+
+@pytest.mark.parametrize("mode", [sv.ACCEPT_SAMPLE, sv.ACCEPT_GREEDY, sv.ACCEPT_POINT_DRAFT])
+@pytest.mark.parametrize("V", [1024, 32000, 128256])
+def test_a_workspace_for_the_largest_batch_serves_every_smaller_one(V, mode):
+    largest = {}
+    for B in list(range(1, 66)) + [96, 127, 128, 255, 256, 600, 1500]:
+        for k in range(0, 9):
+            largest[B, k] = sv.spec_verify_workspace_bytes(None, reject_args(B, k, V, mode))
+            assert largest[B, k] >= small_records(B, k, V, mode)
+            if k > 0:
+                assert largest[B, k] >= largest[B, k - 1], (B, k)
+        if B > 1:
+            before = max(b for b, _ in largest if b < B)
+            assert all(largest[B, k] >= largest[before, k] for k in range(0, 9)), B
+    # ... and so does the workspace of a step of the largest batch
+    step = sv.spec_verify_workspace_bytes(attn_args(64, 8, 300), _with_mode(reject_args(64, 8, V), mode))
+    assert step >= largest[64, 8]
+
+
+def _with_mode(r, mode):
+    r.accept_mode = mode
+    return r
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the pointers of this test are not real")
+def test_a_workspace_without_room_for_many_blocks_is_not_refused():
+    for B in (1, 4, 15, 16, 33, 64, 200):
+        for k in (0, 1, 4, 8):
+            for V in (1024, 32000, 128256):
+                r, need = reject_args(B, k, V), small_records(B, k, V)
+                call = lambda n: sv.lib().spec_reject_sample(C.byref(r), FAKE, n, None)
+                # (no GPU here: past the size check the launch fails)
+                assert call(need) == sv.SPEC_EHIP, (B, k, V)
+                assert call(need - 256) == sv.SPEC_EWORKSPACE, (B, k, V)
