@@ -16,7 +16,7 @@ def test_few_records(B, k, V):
     import torch
     from paper_2406_14066_amd import harness as H
     print("case small workspace", B, k, V, flush=True)
-    w = W.make_workload("few", B=B, Hq=1, Hkv=1, d=64, V=V, dtype="f32", kv_len=[16] * B, k=k, draft_std=3.0,
+    w = W.make_workload("few", B=B, Hq=1, Hkv=1, d=64, V=V, dtype="f32", kv_len=[16] * B, k=[k] * B, draft_std=3.0,
                         sigma=0.8, data_seed=B, philox_seed=17, with_kv=False)
     w.k_pages = w.v_pages = np.zeros((1, 1, 16, 64), np.float32)
     w.q = np.zeros((w.T, 1, 64), np.float32)
