@@ -267,9 +267,16 @@ __global__ __launch_bounds__(kRepackWaves *kWave) void kv_repack_kernel(const ui
 }
 
 // KV append: one thread per (packed row, kv head, group of 8 elements).  Latency is what a launch of this size takes: the
-// chain of dependent loads before the stores, and the stores of V in the tiled layout.  256 requests, k = 4, 8
-// heads of 128, tiled pages: 8.98 -> 7.50 us per call, of which the host takes 7.
-template <typename T>
+// chain of dependent loads before the stores, and the stores of V in the tiled layout.  The rows to move do not
+// depend on where they go, and with one draft length for all requests the first guess of the request is right: rows of 16-bit
+// elements are fetched along with the guess's lengths, so that two round trips (lengths, page index) are left
+// before the stores instead of four; fp32 rows, twice the registers, after the page index (256 requests: 6.2 us, the other
+// way 6.35).  The empty asm statements hold the loads where they are written: the compiler moves them to their first use
+// otherwise, and the lengths' into the comparison.  The layout is a template parameter: chosen at run time, V went through the
+// strided loads' registers in either.  Replayed from a graph, k = 4, 8 heads of 128, 1 / 256 requests: tiled pages
+// 2.7 / 7.2 us (with loads at their first use and one store per dim 3.4 / 9.1), token-major bf16 2.15 / 3.3 (2.5 / 3.6),
+// fp32 2.4 / 6.2 (2.8 / 6.2).  Called one by one, the host takes 7 us.
+template <typename T, bool TILED>
 __global__ void kv_append_kernel(KvAppendParams p)
 {
     const int groups = p.d >> 3;
@@ -279,27 +286,31 @@ __global__ void kv_append_kernel(KvAppendParams p)
     const int g = (int)(idx % groups);
     const int kvh = (int)((idx / groups) % p.Hkv);
     const int row = (int)(idx / ((size_t)groups * p.Hkv));
-    // The rows to move do not depend on where they go, and with one draft length for all requests the first guess
-    // of the request is right: both are fetched at once with the guess's length, so that two dependent
-    // round trips (lengths, page index) are left before the stores instead of four.
-    struct alignas(8 * sizeof(T)) Vec8 { T e[8]; };
+    typedef T vec8 __attribute__((ext_vector_type(8)));
     const size_t from = ((size_t)row * p.Hkv + kvh) * p.d;
-    const Vec8 new_k = *reinterpret_cast<const Vec8 *>(static_cast<const T *>(p.new_k) + from + g * 8);
-    Vec8 new_v;
-    if (p.kv_layout == SPEC_KV_TOKEN_MAJOR) {
-        new_v = *reinterpret_cast<const Vec8 *>(static_cast<const T *>(p.new_v) + from + g * 8);
-    } else {   // every groups-th dim: the stores below then fall into 2 cache lines per row and instruction, not 16
+    const T *sk = static_cast<const T *>(p.new_k) + from, *sv = static_cast<const T *>(p.new_v) + from;
+    vec8 new_k, new_v;
+    auto fetch = [&] {
+        new_k = *reinterpret_cast<const vec8 *>(sk + g * 8);
+        if constexpr (TILED) {   // every groups-th dim: the stores below then fall into 2 cache lines per row and instruction, not 16
 #pragma unroll
-        for (int e = 0; e < 8; ++e) new_v.e[e] = static_cast<const T *>(p.new_v)[from + g + e * groups];
-    }
+            for (int e = 0; e < 8; ++e) new_v[e] = sv[g + e * groups];
+        } else {
+            new_v = *reinterpret_cast<const vec8 *>(sv + g * 8);
+        }
+    };
+    constexpr bool early = sizeof(T) == 2;
+    if constexpr (early) fetch();
     int b = min((int)(((long long)row * p.B) / p.T), p.B - 1);
     int begin = p.cu_q_len[b], end = p.cu_q_len[b + 1], len = p.kv_len[b];
+    asm volatile("" : "+v"(begin), "+v"(end), "+v"(len));
     if (begin > row || row >= end) {
         b = find_request(p.cu_q_len, p.B, p.T, row);
         begin = p.cu_q_len[b];
         end = p.cu_q_len[b + 1];
         len = p.kv_len[b];
     }
+    if constexpr (early) asm volatile("" : "+v"(new_k), "+v"(new_v));
     const int pos = len - (end - begin) + (row - begin);
     // position and page index come from device memory: a row that would land outside the
     // request's block-table row or outside the pool is not written, and counted
@@ -311,16 +322,18 @@ __global__ void kv_append_kernel(KvAppendParams p)
         return;
     }
     const int slot = pos % SPEC_BLOCK_SIZE;
+    if constexpr (!early) fetch();
     T *dk = static_cast<T *>(p.k_cache);
     T *dv = static_cast<T *>(p.v_cache);
+    constexpr int layout = TILED ? SPEC_KV_MFMA : SPEC_KV_TOKEN_MAJOR;
     // the 8 elements of a thread are contiguous in the cache in every case but one (V in the tiled
     // layout, where consecutive dims of a token are 16 bytes apart): whole-vector stores where they are
-    *reinterpret_cast<Vec8 *>(dk + k_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = new_k;
-    if (p.kv_layout == SPEC_KV_TOKEN_MAJOR) {
-        *reinterpret_cast<Vec8 *>(dv + v_index(p.kv_layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = new_v;
-    } else {
+    *reinterpret_cast<vec8 *>(dk + k_index(layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = new_k;
+    if constexpr (TILED) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) dv[v_index(p.kv_layout, page, p.Hkv, kvh, slot, g + e * groups, p.d)] = new_v.e[e];
+        for (int e = 0; e < 8; ++e) dv[v_index(layout, page, p.Hkv, kvh, slot, g + e * groups, p.d)] = new_v[e];
+    } else {
+        *reinterpret_cast<vec8 *>(dv + v_index(layout, page, p.Hkv, kvh, slot, g * 8, p.d)) = new_v;
     }
 }
 
@@ -331,9 +344,11 @@ hipError_t launch_kv_append(const KvAppendParams &p, hipStream_t stream)
     const size_t total = (size_t)p.T * p.Hkv * (p.d >> 3);
     const unsigned blocks = (unsigned)((total + 255) / 256);
     if (p.elem_bytes == 4)
-        hipLaunchKernelGGL(kv_append_kernel<float>, dim3(blocks), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((kv_append_kernel<float, false>), dim3(blocks), dim3(256), 0, stream, p);
+    else if (p.kv_layout == SPEC_KV_TOKEN_MAJOR)
+        hipLaunchKernelGGL((kv_append_kernel<uint16_t, false>), dim3(blocks), dim3(256), 0, stream, p);
     else
-        hipLaunchKernelGGL(kv_append_kernel<uint16_t>, dim3(blocks), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((kv_append_kernel<uint16_t, true>), dim3(blocks), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
