@@ -11,7 +11,7 @@ from test_reject_plan_host import small_records
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,k,V", [(1, 4, 32000), (15, 8, 128256), (33, 2, 40004)])
+@pytest.mark.parametrize("B,k,V", [(8, 4, 128256), (15, 8, 128256), (33, 2, 40004)])
 def test_few_records(B, k, V):
     import torch
     from paper_2406_14066_amd import harness as H
