@@ -34,6 +34,7 @@ struct AttnPlan {
     int32_t use_mfma;      // 1: matrix-instruction kernels (one launch for the step), 0: generic kernel
     int32_t row_tiles;     // 16-row tiles of query rows per wave group (mfma kernel, 1..3)
     int32_t row_groups;    // wave groups per attention block (1, 2 or 4): row_groups * row_tiles tiles cover max_q_len * (Hq/Hkv) rows
+    int32_t k_direct;      // the attention alone, bf16, token-major pages: K straight into operand order (see plan_attn)
     int32_t capacity_tokens;  // longest kv_len the plan allows for (chunk_tokens * max_chunks, capped by the bucket)
     int32_t fused_combine; // mfma kernel merges the chunk partials itself (few chunks) or leaves it to the combine kernel
     int32_t short_attn;    // the attention half streams for less time than the rejection stages' chain takes
@@ -62,7 +63,7 @@ struct AttnParams {
     int32_t row_groups;           // see AttnPlan
     int32_t reject_first_limit;   // fused step: up to this many rejection items go first in the grid (0: never)
     int32_t row_tiles;            // see AttnPlan
-    int32_t reserved;
+    int32_t k_direct;             // see AttnPlan
     const void *q, *k_cache, *v_cache;
     const int32_t *block_table, *kv_len, *cu_q_len;
     float *out;

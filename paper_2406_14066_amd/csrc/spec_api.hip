@@ -104,6 +104,8 @@ struct Tuning {
     int reject_first_limit = 1024; // SPEC_VERIFY_REJECT_FIRST_LIMIT: rejection blocks up to which they precede the blocks of a short attention half
     int split_p = 1;              // SPEC_VERIFY_SPLIT_P=0: softmax weights as one bf16 instead of high + low parts
     int reject_even = 1;          // SPEC_VERIFY_REJECT_EVEN=0: rejection blocks on all XCDs
+    int k_direct = -1;            // SPEC_VERIFY_K_DIRECT=0/1: the attention alone on token-major pages, K through LDS or straight into
+                                  // operand order where there is a kernel for it (-1: automatic)
     int spin_limit = 1 << 20;     // SPEC_VERIFY_SPIN_LIMIT: polls of a bounded wait (about a second at the default)
     uint32_t epoch = 1;           // changes with every reload: part of the plan cache's key
 };
@@ -142,6 +144,7 @@ void read_tuning()
     }
     if (const char *e = getenv("SPEC_VERIFY_SPLIT_P")) t.split_p = e[0] != '0';
     if (const char *e = getenv("SPEC_VERIFY_REJECT_EVEN")) t.reject_even = e[0] != '0';
+    if (const char *e = getenv("SPEC_VERIFY_K_DIRECT")) t.k_direct = e[0] != '0';
     if (const char *e = getenv("SPEC_VERIFY_SPIN_LIMIT")) {
         const long v = strtol(e, nullptr, 10);
         if (v >= 1 && v <= (1 << 30)) t.spin_limit = (int)v;
@@ -380,6 +383,34 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
         pl.chunk_tokens = 256;  // one key per thread of the generic kernel
     }
     pl.max_chunks = (max_len + pl.chunk_tokens - 1) / pl.chunk_tokens;
+    // Token-major pages of a head dim of 128, the attention alone, two or three row tiles per wavefront: K straight into
+    // operand order where the launch waits for the chain from a page's arrival to its scores rather than for memory.
+    // One wave group: unsplit requests of about equal lengths that do not all start at once (two blocks per
+    // compute unit), so that the last ones run thinly spread.  32/8 heads, through LDS / direct, in us: k = 8, 768 blocks, 120 tokens
+    // 22.4 / 21.6, 200 31.0 / 28.5, 400 42.3 / 38.3, 1000 (memory) 79.9 / 84.0; 1280 blocks, 200 +6%, 300 +6%, 450 +4%, 700 +2%, 1000
+    // -2%; k = 4, 768 blocks, 120 +6%, 300 -2%; 1280 blocks, 120 +6%, 200 +10%, 300 +2%, 700 -2%; lengths from a tenth of to
+    // twice the mean gain nothing.
+    // Two wave groups: at most a block per compute unit, with 256 tokens or fewer.  64/8 heads, k = 7, four requests of
+    // 16 / 100 / 200 tokens: direct 5, 4 and 6% faster; 64 requests (two blocks per unit) of 100 / 200 tokens 0 and 6% slower.
+    const int d_units = a->B * a->Hkv;
+    pl.k_direct = 0;
+    if (a->qkv_dtype == SPEC_BF16 && a->kv_layout == SPEC_KV_TOKEN_MAJOR && a->d == 128 && pl.use_mfma && pl.row_tiles >= 2) {
+        const int cus = compute_units();
+        if (pl.row_groups == 2) {
+            pl.k_direct = pl.chunk_tokens <= 256 && (int64_t)d_units * pl.max_chunks <= cus;
+        } else if (pl.row_groups == 1 && pl.max_chunks == 1 && a->host_kv_len != nullptr && d_units > 2 * cus) {
+            int64_t sum = 0;
+            int longest = 0;
+            for (int b = 0; b < a->B; ++b) {
+                sum += a->host_kv_len[b];
+                longest = std::max(longest, a->host_kv_len[b]);
+            }
+            const double mean = (double)sum / a->B;
+            const double most = d_units > 4 * cus ? 512.0 : (pl.row_tiles == 3 ? 256.0 : 160.0);
+            pl.k_direct = mean >= 96.0 && mean <= most && longest <= 1.35 * mean;
+        }
+        if (tu.k_direct >= 0) pl.k_direct = pl.row_groups <= 2 && tu.k_direct;
+    }
     pl.capacity_tokens = pl.chunk_tokens * pl.max_chunks;
     pl.fused_combine = (pl.use_mfma && pl.max_chunks <= kMaxFusedChunks) ? 1 : 0;
     // (a request that is not split writes its output directly: the matrix kernel needs no partial
@@ -684,6 +715,7 @@ AttnParams attn_params(const spec_attn_args *a, const AttnPlan &pl, char *ws, in
     p.capacity_tokens = pl.capacity_tokens;
     p.row_groups = pl.row_groups;
     p.row_tiles = pl.row_tiles;
+    p.k_direct = pl.k_direct;
     p.f32 = a->qkv_dtype == SPEC_F32 ? 1 : 0;
     const double scale = a->softmax_scale > 0.0f ? (double)a->softmax_scale : 1.0 / sqrt((double)a->d);
     p.scale_log2 = (float)(scale * kLog2eD);

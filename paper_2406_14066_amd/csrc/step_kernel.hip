@@ -1057,12 +1057,12 @@ constexpr int o_stride(int D) { return D * 4 + 16; }   // bytes per fp32 output 
 constexpr int vt_row_bytes(int D) { return D * 2 + 16; }
 constexpr int vt_wave_bytes(int D) { return SPEC_BLOCK_SIZE * vt_row_bytes(D); }
 // Which blocks walk their pages staged (see the staged walk in attn_role).
-constexpr bool staged_walk(int WG, bool TM) { return WG > 1 && TM; }
+constexpr bool staged_walk(int WG, bool TM, bool K_DIRECT) { return WG > 1 && TM && !K_DIRECT; }
 
-template <int NT, int WG, bool TM = false, int D = kD>
+template <int NT, int WG, bool TM = false, int D = kD, bool K_DIRECT = false>
 struct AttnShared {
     static constexpr int kRowsMax = WG * NT * 16;
-    static constexpr bool kStaged = staged_walk(WG, TM);
+    static constexpr bool kStaged = staged_walk(WG, TM, K_DIRECT);
     union {
         // staged walk: two rounds of a page per wavefront, K and V
         unsigned char ring[kStaged ? 2 : 1][kStaged ? kWaves : 1][2][kStaged ? vt_wave_bytes(D) : 16];
@@ -1401,13 +1401,14 @@ __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w,
     }
 }
 
-template <int NT, int WG, int VAR>
+// (K_DIRECT: see attn_k_direct_kernel)
+template <int NT, int WG, int VAR, bool K_DIRECT = false>
 __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order, int item,
-                                          AttnShared<NT, WG, token_major_of(VAR), head_dim_of(VAR)> &sh)
+                                          AttnShared<NT, WG, token_major_of(VAR), head_dim_of(VAR), K_DIRECT> &sh)
 {
     constexpr bool SPLIT_P = VAR != 1;
     constexpr bool TM = token_major_of(VAR);
-    constexpr bool STAGED = staged_walk(WG, TM);
+    constexpr bool STAGED = staged_walk(WG, TM, K_DIRECT);
     constexpr int D = head_dim_of(VAR);
     constexpr int KK = D / 32;                        // 32-dim steps of the score product = 1 KB loads per K or V page
     constexpr int MT = D / 16;                        // 16-dim slices of the output
@@ -1470,7 +1471,10 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         const __amdgpu_buffer_rsrc_t vd = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(vhead + (size_t)page * page_stride), 0, bytes, kBufferFlags);
 #pragma unroll
-        for (int i = 0; i < KK; ++i) r.k[i] = __builtin_amdgcn_raw_buffer_load_b128(kd, lane_off, i * 1024, kStreamPolicy);
+        for (int i = 0; i < KK; ++i)
+            r.k[i] = K_DIRECT   // in operand order: token n16, dims 32 i + 8 g .. + 7 sit at n16 * 2 D + 64 i + 16 g
+                         ? __builtin_amdgcn_raw_buffer_load_b128(kd, n16 * (D * 2) + g * 16, i * 64, kStreamPolicy)
+                         : __builtin_amdgcn_raw_buffer_load_b128(kd, lane_off, i * 1024, kStreamPolicy);
         // V: in operand order already, or (token-major) as whole rows: with D / 8 lanes per row, lane L of load i holds
         // token (512 / D) i + 8 L / D, dims 8 (L % (D / 8)) .. + 7
 #pragma unroll
@@ -1504,7 +1508,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
 #pragma unroll
             for (int i = 0; i < KK; ++i) {
                 const int at = ((kWave / LR) * i + lane / LR) * kVtRowBytes + (lane % LR) * 16;
-                *reinterpret_cast<u32x4 *>(kl + at) = cur.k[i];
+                if constexpr (!K_DIRECT) *reinterpret_cast<u32x4 *>(kl + at) = cur.k[i];
                 *reinterpret_cast<u32x4 *>(vl + at) = cur.v[i];
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1512,7 +1516,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
             for (int i = 0; i < KK; ++i) {
-                cur.k[i] = *reinterpret_cast<const u32x4 *>(kl + n16 * kVtRowBytes + i * 64 + g * 16);
+                if constexpr (!K_DIRECT) cur.k[i] = *reinterpret_cast<const u32x4 *>(kl + n16 * kVtRowBytes + i * 64 + g * 16);
                 const unsigned char *src = vl + (4 * g + (n16 >> 2)) * kVtRowBytes + (n16 & 3) * 8 + i * 64;
                 const u32x2 lo = read_transposed(src), hi = read_transposed(src + 32);
                 cur.v[i] = (u32x4){lo.x, lo.y, hi.x, hi.y};
@@ -2047,6 +2051,18 @@ __global__ __launch_bounds__(kThreads, (kMinBlocks<NT, HAS_ATTN, VAR>)) void spe
     }
 }
 
+// The attention alone on token-major pages of a head dim of 128, with K loaded straight into operand order
+// (each load touches 16 half cache lines) and only V staged, every wave group reading its pages itself.  The chain from a
+// page's arrival to its scores is shorter by a trip through LDS, which is what some launches wait for (the planner's
+// k_direct says which, and what both measured); a kernel of its own, because the choice inside the other costs its launches 0.7%.
+template <int NT, int WG>
+__global__ __launch_bounds__(kThreads, 2) void attn_k_direct_kernel(StepArgs args)
+{
+    typedef AttnShared<NT, WG, true, kD, true> AttnSh;
+    __shared__ alignas(16) unsigned char shared[sizeof(AttnSh)];
+    attn_role<NT, WG, 2, true>(args.ap, order_table(args.order.n), blockIdx.x, *reinterpret_cast<AttnSh *>(shared));
+}
+
 // The step in fp32: the same grid and roles.  A launch of the attention alone has no rejection items.
 // (Three row tiles take over 256 registers at a head dim of 128: 33 to 48 rows run as two wave groups of two
 // tiles, and only the widest shapes, 129 to 144 rows, as four groups of three with one block per compute unit.)
@@ -2121,6 +2137,9 @@ hipError_t launch(const AttnParams &ap, const RejectParams &rp, int n_stat, int 
     auto go = [&](auto var) {
         return launch_kernel(spec_step_kernel<NT, WG, HAS_ATTN, HAS_REJECT, decltype(var)::value>, grid, args, ev, stream);
     };
+    if constexpr (HAS_ATTN && !HAS_REJECT && WG <= 2 && NT >= 2)
+        if (ap.k_direct && ap.kv_layout == SPEC_KV_TOKEN_MAJOR && ap.d == kD)
+            return launch_kernel(attn_k_direct_kernel<NT, WG>, grid, args, ev, stream);
     if constexpr (HAS_ATTN) {
         if (ap.kv_layout == SPEC_KV_TOKEN_MAJOR)
             return ap.d == 64 ? go(std::integral_constant<int, 4>()) : go(std::integral_constant<int, 2>());

@@ -1,0 +1,113 @@
+"""Every page walk of the attention kernels (wave groups that share their pages through LDS, K straight into
+operand order, fp32) against the oracle: sizes at the edges of pages, tiles and rounds, and what the device
+finds in lengths and block tables -- found once, left out or read as zeros, by whichever wavefront it falls to."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2406_14066_amd import spec_verify as sv
+from paper_2406_14066_amd import workloads as W
+from parity_utils import ATTN_TOL
+
+pytestmark = pytest.mark.gpu
+
+# dtype, query heads, KV heads, largest draft length, K straight into operand order; row tiles, wave groups of the plan
+PATHS = [
+    ("bf16", 8, 4, 4, 0, 1, 1), ("bf16", 8, 2, 7, 0, 2, 1), ("bf16", 8, 2, 7, 1, 2, 1), ("bf16", 16, 4, 8, 0, 3, 1),
+    ("bf16", 16, 4, 8, 1, 3, 1), ("bf16", 16, 2, 6, 0, 2, 2), ("bf16", 16, 2, 6, 1, 2, 2), ("bf16", 16, 2, 8, 0, 3, 2),
+    ("bf16", 16, 2, 8, 1, 3, 2), ("bf16", 32, 2, 6, 0, 2, 4), ("bf16", 16, 1, 8, 0, 3, 4),
+    ("f32", 8, 4, 4, None, 1, 1), ("f32", 8, 2, 7, None, 2, 1), ("f32", 16, 2, 6, None, 2, 2), ("f32", 16, 1, 8, None, 3, 4),
+]
+IDS = ["%s-%d-%d-k%d%s" % (p[0], p[1], p[2], p[3], {0: "-lds", 1: "-direct", None: ""}[p[4]]) for p in PATHS]
+
+
+def _setup(tuning, path, kv_len, k, **kw):
+    from paper_2406_14066_amd.harness import DeviceStep
+    dtype, Hq, Hkv, k_max, direct, tiles, groups = path
+    if direct is not None:
+        tuning("SPEC_VERIFY_K_DIRECT", direct)
+    # (the first request has the longest draft; others fill only some of the wave groups)
+    w = W.make_workload("paths", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len),
+                        k=[min(x, k_max) for x in k], draft_std=2.0, sigma=0.8, data_seed=Hq + k_max, philox_seed=9, **kw)
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    plan = ds.plan()
+    assert (plan["row_tiles"], plan["row_groups"]) == (tiles, groups), plan
+    return w, ds
+
+
+def _run(ds):
+    """The attention alone; returns its output and what the device found."""
+    import torch
+    found = torch.zeros(1, dtype=torch.int64, device="cuda")
+    ds.attn_args.error_count = found.data_ptr()
+    ds.out.fill_(float("nan"))
+    ds.run_attn()
+    torch.cuda.synchronize()
+    return ds.out.cpu().numpy(), int(found.item())
+
+
+def _oracle(w):
+    return oracle.verify_attn(w.q, w.k_pages, w.v_pages, w.block_table, w.kv_len, w.cu_q_len)
+
+
+def _rows(w, b):
+    return slice(int(w.cu_q_len[b]), int(w.cu_q_len[b + 1]))
+
+
+@pytest.mark.parametrize("path", PATHS, ids=IDS)
+@pytest.mark.parametrize("kv_len", [(9, 16, 17, 31, 64, 65, 127, 129, 255, 256), (257, 9, 300, 1000, 513, 64, 2049)], ids=["unsplit", "split"])
+def test_lengths_at_page_and_round_edges(tuning, path, kv_len):
+    print("case edges", path, kv_len, flush=True)
+    w, ds = _setup(tuning, path, kv_len, [8, 0, 1, 8, 3, 5, 8, 0, 2, 8][: len(kv_len)])
+    got, found = _run(ds)
+    assert found == 0
+    err = np.abs(got.astype(np.float64) - _oracle(w)).max()
+    assert err <= ATTN_TOL[path[0]], err
+    if path[4] == 1:      # the same operands in the same order: the same bits as through LDS
+        through_lds = list(path)
+        through_lds[4] = 0
+        _, ds0 = _setup(tuning, tuple(through_lds), kv_len, [8, 0, 1, 8, 3, 5, 8, 0, 2, 8][: len(kv_len)])
+        np.testing.assert_array_equal(got, _run(ds0)[0])
+
+
+@pytest.mark.parametrize("path", PATHS, ids=IDS)
+def test_impossible_lengths_are_left_out_and_counted(tuning, path):
+    import torch
+    print("case bad lengths", path, flush=True)
+    kv_len = (300, 45, 1000, 129, 64)
+    for bad_b, bad_len in [(2, 5000), (1, 0), (0, -7)]:
+        w, ds = _setup(tuning, path, kv_len, [8, 1, 4, 0, 2])
+        dev_len = w.kv_len.copy()
+        dev_len[bad_b] = bad_len
+        ds.kv_len.copy_(torch.from_numpy(dev_len))
+        got, found = _run(ds)
+        assert found == 1, (bad_b, bad_len, found)
+        assert np.isnan(got[_rows(w, bad_b)]).all()
+        ok = np.ones(w.T, dtype=bool)
+        ok[_rows(w, bad_b)] = False
+        err = np.abs(got[ok].astype(np.float64) - _oracle(w)[ok]).max()
+        assert err <= ATTN_TOL[path[0]], err
+
+
+@pytest.mark.parametrize("path", PATHS, ids=IDS)
+def test_bad_block_table_entries_read_as_zeros_and_are_counted_once(tuning, path):
+    import torch
+    print("case bad pages", path, flush=True)
+    kv_len = (300, 45, 1000, 129, 64)
+    bad = [(2, 7), (2, 30), (2, 62), (0, 18), (4, 0), (3, 8)]     # (request 2's and 0's last pages among them; request 3 fills one wave group)
+    w, ds = _setup(tuning, path, kv_len, [8, 1, 4, 0, 2])
+    table = w.block_table.copy()
+    for i, (b, p) in enumerate(bad):
+        table[b, p] = [w.num_blocks + 5, -3, 1 << 30][i % 3]
+    ds.block_table.copy_(torch.from_numpy(table))
+    got, found = _run(ds)
+    assert found == len(bad), found
+    assert np.isfinite(got).all()
+    spare = [p for p in range(w.num_blocks) if p not in set(w.block_table.ravel().tolist())][: len(bad)]
+    assert len(spare) == len(bad)
+    for (b, i), p in zip(bad, spare):
+        w.block_table[b, i] = p
+        w.k_pages[p] = 0
+        w.v_pages[p] = 0
+    err = np.abs(got.astype(np.float64) - _oracle(w)).max()
+    assert err <= ATTN_TOL[path[0]], err
