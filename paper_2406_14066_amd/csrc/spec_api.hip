@@ -106,6 +106,7 @@ struct Tuning {
     int reject_even = 1;          // SPEC_VERIFY_REJECT_EVEN=0: rejection blocks on all XCDs
     int k_direct = -1;            // SPEC_VERIFY_K_DIRECT=0/1: the attention alone on token-major pages, K through LDS or straight into
                                   // operand order where there is a kernel for it (-1: automatic)
+    int f32_scalar = -1;          // SPEC_VERIFY_F32_SCALAR=0/1: fp32 attention alone on the matrix-instruction / scalar kernel (-1: automatic)
     int spin_limit = 1 << 20;     // SPEC_VERIFY_SPIN_LIMIT: polls of a bounded wait (about a second at the default)
     uint32_t epoch = 1;           // changes with every reload: part of the plan cache's key
 };
@@ -145,6 +146,7 @@ void read_tuning()
     if (const char *e = getenv("SPEC_VERIFY_SPLIT_P")) t.split_p = e[0] != '0';
     if (const char *e = getenv("SPEC_VERIFY_REJECT_EVEN")) t.reject_even = e[0] != '0';
     if (const char *e = getenv("SPEC_VERIFY_K_DIRECT")) t.k_direct = e[0] != '0';
+    if (const char *e = getenv("SPEC_VERIFY_F32_SCALAR")) t.f32_scalar = e[0] != '0';
     if (const char *e = getenv("SPEC_VERIFY_SPIN_LIMIT")) {
         const long v = strtol(e, nullptr, 10);
         if (v >= 1 && v <= (1 << 30)) t.spin_limit = (int)v;
@@ -310,11 +312,34 @@ spec_status validate_reject(const spec_reject_args *r)
 // ---------------------------------------------------------------------------
 // Planning.
 // ---------------------------------------------------------------------------
+// The fp32 attention alone of a few short requests on wide query groups: is the scalar kernel (a block per query row and head)
+// faster than the matrix-instruction kernel, whose few blocks walk their pages one after the other?  Both
+// modelled from measurements, in us (matrix / scalar; 64/4 heads of 128, k = 4, tokens of each request: one request, 16
+// 10.0 / 5.8, 48 14.6 / 8.2, 128 26.5 / 15.6, 256 45.9 / 27.0, 700 53.2 / 46.5; four 128 27.2 / 30.0; 16/1 heads, k = 8, eight
+// requests, 128 45.1 / 32.0; 32/8 heads, k = 4, one request, 16 9.3 / 5.8, 128 12.9 / 15.7): of 608 calls the rule takes
+// 196, all of them 1.08 to 3 times as fast, 1.5 at the median, and leaves 12 that would be 1.2 times as fast or more.
+bool f32_scalar_is_faster(const AttnPlan &pl, int d, int max_len, int64_t rows)
+{
+    if (pl.row_tiles < 2) return false;
+    const bool wide = d == 128;
+    const int pages = (std::min(max_len, pl.chunk_tokens) + SPEC_BLOCK_SIZE - 1) / SPEC_BLOCK_SIZE;
+    const int per_wave = (pages * pl.row_groups + 3) / 4;
+    const double matrix_us = (4.0 + 1.2 * pl.row_tiles + 0.5 * (pl.row_groups - 1)) * (wide ? 1.0 : 0.8) +
+                             per_wave * (0.4 + 1.25 * pl.row_tiles) * (wide ? 1.0 : 0.57) * (pl.row_groups > 1 && pl.row_tiles == 2 ? 0.9 : 1.0) +
+                             (pl.max_chunks > 1 ? 3.0 : 0.0);
+    const double blocks = rows * std::max(1.0, max_len / 256.0);
+    const double load = blocks > 900.0 ? blocks / 450.0 : 1.0 + std::max(0.0, blocks - (max_len <= 64 ? 512.0 : 192.0)) / 900.0;
+    const int keys = std::min(max_len, 256);
+    const double scalar_us = (wide ? 4.6 + 0.087 * keys : 4.0 + 0.0445 * keys) * load + (max_len > 256 ? 3.0 : 0.0);
+    return scalar_us <= 0.95 * matrix_us;
+}
+
 // Split of the KV length.  The matrix-instruction kernel runs one block per (request, KV head,
 // chunk); the chunk is sized so that the launch has about one block per compute unit
 // (two with three row tiles), in multiples of the 16 tokens of a page.  The longest length the
 // plan allows for is the caller's bucket (max_kv_len) or, without one, the longest host length.
-AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
+// (alone: no rejection half in the same call)
+AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
 {
     AttnPlan pl;
     memset(&pl, 0, sizeof pl);
@@ -327,8 +352,8 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
     pl.max_q_len = max_q;
     const int group = a->Hq / a->Hkv;
     const int tiles = (max_q * group + 15) / 16;
-    // both types run on matrix-instruction kernels, bf16 in either page layout (token-major pages have
-    // their V transposed through LDS), fp32 on token-major pages, the only ones it has
+    // both types run on matrix-instruction kernels, bf16 in either page layout (token-major pages pass
+    // through LDS), fp32 on token-major pages, the only ones it has (a few calls excepted, see f32_scalar_is_faster)
     pl.use_mfma = tu.force_generic ? 0 : 1;
     pl.row_groups = 1;
     pl.row_tiles = tiles;
@@ -379,10 +404,17 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
         if (chunk > chunk_cap) chunk = chunk_cap;
         if (tu.chunk > 0 && tu.chunk <= chunk_cap) chunk = tu.chunk;
         pl.chunk_tokens = (int32_t)chunk;
-    } else {
-        pl.chunk_tokens = 256;  // one key per thread of the generic kernel
+        pl.max_chunks = (max_len + pl.chunk_tokens - 1) / pl.chunk_tokens;
+        if (f32 && alone && (tu.f32_scalar >= 0 ? tu.f32_scalar != 0 : f32_scalar_is_faster(pl, a->d, max_len, (int64_t)a->T * a->Hq))) {
+            pl.use_mfma = 0;
+            pl.row_groups = 1;
+            pl.row_tiles = tiles;
+        }
     }
-    pl.max_chunks = (max_len + pl.chunk_tokens - 1) / pl.chunk_tokens;
+    if (!pl.use_mfma) {
+        pl.chunk_tokens = 256;  // one key per thread of the generic kernel
+        pl.max_chunks = (max_len + pl.chunk_tokens - 1) / pl.chunk_tokens;
+    }
     // Token-major pages of a head dim of 128, the attention alone, two or three row tiles per wavefront: K straight into
     // operand order where the launch waits for the chain from a page's arrival to its scores rather than for memory.
     // One wave group: unsplit requests of about equal lengths that do not all start at once (two blocks per
@@ -415,7 +447,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu)
     pl.fused_combine = (pl.use_mfma && pl.max_chunks <= kMaxFusedChunks) ? 1 : 0;
     // (a request that is not split writes its output directly: the matrix kernel needs no partial
     // slots when no request can have a second chunk)
-    // fp32 has room for the scalar kernels' chunks of 256 tokens, so that a workspace serves them too
+    // fp32 has room for the scalar kernels' chunks of 256 tokens: the workspace of a step, or of another batch, serves the calls they take
     const bool f32_type = a->qkv_dtype == SPEC_F32;
     const int slot_chunks = f32_type ? std::max(pl.max_chunks, (max_len + 255) / 256) : pl.max_chunks;
     const size_t slots = (pl.use_mfma && pl.max_chunks == 1 && !f32_type) ? 0 : (size_t)a->T * a->Hq * slot_chunks;
@@ -665,7 +697,7 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     if (e.status != SPEC_OK) return e;
     size_t base = 0;
     if (a != nullptr) {
-        e.apl = plan_attn(a, tu);
+        e.apl = plan_attn(a, tu, r == nullptr);
         e.apl.short_attn = attn_estimate_us(a) <= 20.0 ? 1 : 0;
         if (e.apl.use_mfma) make_order(a, e.order);
         base = e.apl.total_bytes;

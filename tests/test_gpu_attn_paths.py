@@ -11,21 +11,21 @@ from parity_utils import ATTN_TOL
 
 pytestmark = pytest.mark.gpu
 
-# dtype, query heads, KV heads, largest draft length, K straight into operand order; row tiles, wave groups of the plan
+# dtype, query heads, KV heads, largest draft length, bf16: K straight into operand order, fp32: the scalar kernel; row tiles
+# and wave groups of the matrix-instruction kernel
 PATHS = [
     ("bf16", 8, 4, 4, 0, 1, 1), ("bf16", 8, 2, 7, 0, 2, 1), ("bf16", 8, 2, 7, 1, 2, 1), ("bf16", 16, 4, 8, 0, 3, 1),
     ("bf16", 16, 4, 8, 1, 3, 1), ("bf16", 16, 2, 6, 0, 2, 2), ("bf16", 16, 2, 6, 1, 2, 2), ("bf16", 16, 2, 8, 0, 3, 2),
     ("bf16", 16, 2, 8, 1, 3, 2), ("bf16", 32, 2, 6, 0, 2, 4), ("bf16", 16, 1, 8, 0, 3, 4),
-    ("f32", 8, 4, 4, None, 1, 1), ("f32", 8, 2, 7, None, 2, 1), ("f32", 16, 2, 6, None, 2, 2), ("f32", 16, 1, 8, None, 3, 4),
+    ("f32", 8, 4, 4, 0, 1, 1), ("f32", 8, 2, 7, 0, 2, 1), ("f32", 16, 2, 6, 0, 2, 2), ("f32", 16, 1, 8, 0, 3, 4), ("f32", 16, 1, 8, 1, 3, 4),
 ]
-IDS = ["%s-%d-%d-k%d%s" % (p[0], p[1], p[2], p[3], {0: "-lds", 1: "-direct", None: ""}[p[4]]) for p in PATHS]
+IDS = ["%s-%d-%d-k%d%s" % (p[0], p[1], p[2], p[3], ["-lds", "-direct", "-matrix", "-scalar"][p[4] + 2 * (p[0] == "f32")]) for p in PATHS]
 
 
 def _setup(tuning, path, kv_len, k, **kw):
     from paper_2406_14066_amd.harness import DeviceStep
     dtype, Hq, Hkv, k_max, direct, tiles, groups = path
-    if direct is not None:
-        tuning("SPEC_VERIFY_K_DIRECT", direct)
+    tuning("SPEC_VERIFY_K_DIRECT" if dtype == "bf16" else "SPEC_VERIFY_F32_SCALAR", direct)
     # (the first request has the longest draft; others fill only some of the wave groups)
     w = W.make_workload("paths", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len),
                         k=[min(x, k_max) for x in k], draft_std=2.0, sigma=0.8, data_seed=Hq + k_max, philox_seed=9, **kw)
@@ -63,7 +63,7 @@ def test_lengths_at_page_and_round_edges(tuning, path, kv_len):
     assert found == 0
     err = np.abs(got.astype(np.float64) - _oracle(w)).max()
     assert err <= ATTN_TOL[path[0]], err
-    if path[4] == 1:      # the same operands in the same order: the same bits as through LDS
+    if path[0] == "bf16" and path[4] == 1:      # the same operands in the same order: the same bits as through LDS
         through_lds = list(path)
         through_lds[4] = 0
         _, ds0 = _setup(tuning, tuple(through_lds), kv_len, [8, 0, 1, 8, 3, 5, 8, 0, 2, 8][: len(kv_len)])
