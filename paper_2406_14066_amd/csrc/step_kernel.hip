@@ -1362,7 +1362,8 @@ __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w,
                     if constexpr (RB == 1 || D < 4 * 32) {
                         mlv[j][c] = pack_f32x2(kEmptyMax, 0.0f);
                         a0[j][c] = a1[j][c] = 0ull;
-                        if (c0 + c < nchunks) {   // the same for the whole block: one branch for the three
+                        // the same for the whole wavefront: one branch for the three
+                        if (c0 + c < nchunks && (RB == 1 || __builtin_amdgcn_readfirstlane(r0) + 2 * kWaves * j < rows)) {
                             mlv[j][c] = fetch_u64(ml[j] + c0 + c);
                             a0[j][c] = fetch_u64(al);
                             a1[j][c] = fetch_u64(al + 1);
