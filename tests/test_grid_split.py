@@ -31,13 +31,13 @@ def period(rows_mixed, rows_reject):
     return (rows_mixed + rows_reject) / rows_mixed
 
 
-# (B, Hkv, rejection items: statistics, race, final) of steps whose period was 4.0 to 4.1, 2.0 and 5.95
+# (B, Hkv, rejection items: statistics, race, final) of steps whose period was 4.0 to 4.1
 @pytest.mark.parametrize("B,Hkv,items", [(96, 8, 864 + 288 + 12), (120, 8, 1080 + 360 + 15), (88, 8, 792 + 264 + 11), (112, 8, 1008 + 336 + 14)])
 def test_steps_that_were_in_step_with_the_compute_units(attention_rows_mixed, B, Hkv, items):
     rows_attn, rows_reject = B * Hkv // 8, (items + 7) // 8
     assert 3.9 < period(rows_attn // 2, rows_reject) < 4.1      # half of the attention rows, as they are
     rows = attention_rows_mixed(rows_attn, rows_reject, 0.5)
-    assert 4.19 < period(rows, rows_reject) < 4.5
+    assert 3.6 < period(rows, rows_reject) <= 3.7
 
 
 @pytest.mark.parametrize("span", [0.5, 0.3, 0.9])
@@ -46,11 +46,10 @@ def test_attention_rows_spread_over_the_compute_units(attention_rows_mixed, span
         for rows_reject in list(range(1, 400, 3)) + [512, 777, 1024, 4096]:
             rows = attention_rows_mixed(rows_attn, rows_reject, span)
             plain = min(max(int(rows_attn * span), 1), rows_attn)
-            assert 1 <= rows <= plain
+            assert 1 <= rows <= rows_attn
             p0, p1 = period(plain, rows_reject), period(rows, rows_reject)
-            near = [e for e in (2, 4, 6, 8) if abs(p0 - e) < 0.0499 * e]
-            if not near:
-                assert rows == plain or any(abs(abs(p0 - e) - 0.05 * e) < 1e-3 * e for e in (2, 4, 6, 8))
+            if not 3.69 < p0 < 3.81 and all(abs(p0 - e) > 0.0501 * e for e in (2, 4, 6, 8)):
+                assert rows == plain
             if rows < 24 or p1 > 8.6:
                 continue
             # the positions of the attention rows, as the kernel computes them, over the places of a group of 4
