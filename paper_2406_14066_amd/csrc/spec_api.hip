@@ -438,7 +438,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
                 longest = std::max(longest, a->host_kv_len[b]);
             }
             const double mean = (double)sum / a->B;
-            const double most = d_units > 4 * cus ? 512.0 : (pl.row_tiles == 3 ? 256.0 : 160.0);
+            const double most = d_units > 4 * cus ? 512.0 : (pl.row_tiles == 3 ? 256.0 : 208.0);
             pl.k_direct = mean >= 96.0 && mean <= most && longest <= 1.35 * mean;
         }
         if (tu.k_direct >= 0) pl.k_direct = pl.row_groups <= 2 && tu.k_direct;
