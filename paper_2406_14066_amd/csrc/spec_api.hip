@@ -468,9 +468,9 @@ double attn_estimate_us(const spec_attn_args *a)
 }
 
 // attn_us: rough duration of the attention half that runs in the same launch (microseconds), or
-// negative if the rejection half runs alone.  few_records: alone, but with no more statistics and race blocks than beside
+// negative if the rejection half runs alone; attn_blocks: its blocks.  few_records: alone, but with no more statistics and race blocks than beside
 // an attention half (at most two per compute unit), for a workspace that has no room for more.
-RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0, bool few_records = false)
+RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0, int64_t attn_blocks = 0, bool few_records = false)
 {
     RejectPlan pl;
     memset(&pl, 0, sizeof pl);
@@ -497,12 +497,18 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     // rejection half runs alone (256 / 512 / 1024 / 1536 blocks on 256 units 59.3 / 53.8 /
     // 51.4 / 52.4 us for 256 requests, k = 2, V = 32000).  Beside an attention half, where every block
     // holds a slot of the attention's while it waits, about one (256 / 512 / 1024 blocks: 154.2 / 155.9 / 160.6 us for the
-    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7), or two where the segments
-    // are longer than 16384 ids and take, at a block's share of the memory's rate (12.5 KB per microsecond),
-    // more than 0.18 of the launch: the last request's race then ends the launch.  64/8 heads, 400 tokens, k = 1,
-    // 256 / 512 blocks (and that share): V = 64128, 128 requests 70.3 / 59.2 us (0.36), 256 132.9 / 117.1 (0.37); V = 128256,
-    // 64 requests 52.8 / 44.2 (0.55), 128 118.7 / 89.6 (0.55); 2000 tokens, k = 4, V = 128256, 24 requests
-    // 76.5 / 77.0 (0.08); V = 32000, 256 requests 91.9 / 94.8 (0.22), 64 (segments of 8192) 28.5 / 32.3.
+    // step of those requests on 64/8 heads, 119.5 / 122.2 / 130.6 us for 96 of them at k = 7), unless the segments are long
+    // and the last request's race ends the launch.  How much of it a segment takes is estimated from a block's share of the
+    // memory's rate (12.5 KB per microsecond); 256 / 512 blocks and that share:
+    //   Attention blocks mixed with the others (more than two per unit): two race blocks per unit for segments above 16384 ids
+    // and 0.18, or, with a vocabulary above 32768, of 16384 and 0.135.  64/8 heads, 400 tokens, k = 1: V = 64128,
+    // 128 requests 70.3 / 59.2 us (0.36), 256 132.9 / 117.1 (0.37); V = 128256, 128 requests 118.7 / 89.6 (0.55); V = 32000, 256
+    // 91.9 / 94.8 (0.22).  32/32 heads, k = 4: 500 tokens, V = 128256, 32 requests (16384) 81.8 / 71.9 (0.14); 200 tokens,
+    // V = 64128, 96 requests 104.1 / 94.0 (0.14); V = 32000, 96 requests (11264) 71.0 / 72.9.
+    //   Attention blocks first (up to two per unit), which leave few slots: one and a half per unit for segments above 24576 and
+    // 0.18, if there is more than one attention block per unit.  V = 128256, 256 / 384 / 512 blocks: 64/8 heads, 64
+    // requests, k = 1, 700 tokens 75.5 / 68.7 / 64.9; k = 4, 150 tokens 89.0 / 81.9 / 92.6; 64/4 heads, k = 4, 150 tokens, 64
+    // requests (one attention block per unit) 86.5 / 81.3 / 109; k = 1, 700 tokens, 40 requests 39.0 / 42.9 / 42.9.
     const auto race_split = [&](int blocks, int multiple, int &segments, int &len) {
         int n = std::min({(blocks + r->B - 1) / r->B, (r->V + 2047) / 2048, 64});
         if (n < 1) n = 1;
@@ -511,9 +517,15 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     };
     // (a block takes 1024 ids at a time)
     race_split(tu.race_blocks > 0 ? tu.race_blocks : (many ? 4 * cus : (few_records ? 2 * cus : cus)), 1024, pl.race_segments, pl.race_seg_len);
-    if (tu.race_blocks == 0 && attn_us >= 0.0 && pl.race_seg_len > 16384) {
-        const double race_us = pl.race_seg_len * (r->accept_mode == SPEC_ACCEPT_SAMPLE ? 8.0 : 4.0) / 12500.0;
-        if (race_us > 0.18 * (attn_us + logits_us)) race_split(2 * cus, 1024, pl.race_segments, pl.race_seg_len);
+    if (tu.race_blocks == 0 && attn_us >= 0.0) {
+        const double share = pl.race_seg_len * (r->accept_mode == SPEC_ACCEPT_SAMPLE ? 8.0 : 4.0) / 12500.0 / (attn_us + logits_us);
+        if (attn_blocks > 2 * cus) {
+            const bool large_v = r->V > 32768;   // (rows whose statistics take long)
+            if ((pl.race_seg_len > 16384 && share > 0.18) || (large_v && pl.race_seg_len >= 16384 && share > 0.135))
+                race_split(2 * cus, 1024, pl.race_segments, pl.race_seg_len);
+        } else if (attn_blocks > cus && pl.race_seg_len > 24576 && share > 0.18) {
+            race_split(3 * cus / 2, 1024, pl.race_segments, pl.race_seg_len);
+        }
     }
     // requests per item of the final stage: as many as leave 8 items (the kernel says why they are grouped)
     pl.final_shift = 0;
@@ -705,8 +717,9 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     e.workspace_bytes = base;
     if (r != nullptr) {
         const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
-        e.rpl = plan_reject(r, base, tu, attn_us);
-        e.rpl_small = attn_us < 0.0 ? plan_reject(r, base, tu, attn_us, true) : e.rpl;
+        const int64_t attn_blocks = a != nullptr ? (int64_t)a->B * a->Hkv * e.apl.max_chunks : 0;
+        e.rpl = plan_reject(r, base, tu, attn_us, attn_blocks);
+        e.rpl_small = attn_us < 0.0 ? plan_reject(r, base, tu, attn_us, attn_blocks, true) : e.rpl;
         if (e.rpl_small.total_bytes > e.rpl.total_bytes) e.rpl_small = e.rpl;
         e.workspace_bytes = std::max(base + e.rpl.total_bytes, (attn_us < 0.0 ? base : 0) + reject_room(r, tu));
     }
