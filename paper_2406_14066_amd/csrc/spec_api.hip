@@ -534,13 +534,16 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
 
     // Early stop: with one draft length for all requests the statistics items can be taken in
     // position order and the rows after a request's first rejection left unread.  That turns the
-    // pass into a chain of k+1 dependent stages (then the race), which must stay mostly hidden under the launch's
-    // streams (KV and logit bytes at 5.5 TB/s), the more logits it may save the less so; the rejection half
-    // alone: see below.  Step without / with, in us: 64/8 heads, B=96 k=7 102 / 94 (at an acceptance rate of 0.9
-    // instead of 0.7 103 / 109, and B=128 below 88 / 88: long chains are left out), k=3 64 / 64, B=64 k=7 72 / 96,
-    // B=48 k=7 57 / 79, B=128 L=512 k=4 87 / 80, B=256 k=2 156 / 149, V=128256 B=64 k=4 113 / 136; 32/8 heads, B=128
+    // pass into a chain of k+1 dependent stages (then the race), which pays where it stays mostly hidden under the
+    // attention's stream, or where the logits it saves are many.  Both are weighed by their streams (KV and logit
+    // bytes at 5.5 TB/s) with weights fitted to measurements; the rejection half alone: see below.  Step without / with, in us:
+    // 64/8 heads, B=96 k=7 102 / 94, k=3 64 / 64, B=128 L=512 k=4 87 / 80, B=256 k=2 156 / 149; 32/8 heads, B=128
     // L=512 k=2 64 / 61; 32/32 heads, L=1024, B=32 k=2 / 4 / 8 94 / 92, 97 / 95, 103 / 104, B=64 k=4 / 8 181 / 178,
-    // 199 / 182, B=16 L=2048 k=2 96 / 104.
+    // 199 / 182.  Not where all attention blocks go first in the grid (two per compute unit or fewer): the chain then starts
+    // late in few slots (64/8 heads, B=64, L=1000, k=1 / 2, V=8192: 54 / 57, 57 / 64; k=4, V=32000 67 / 84).  Over 407 steps (32 to 256
+    // requests, k = 1 to 8, 150 to 1000 tokens, V = 8192, 32000 and 128256, acceptance rates of 0.5, 0.7 and 0.9) the rule
+    // loses 0.4% against the better side on average; worst, at a rate of 0.5, a long chain that it leaves out (B=128 k=8 L=150
+    // 92 / 82) and, at 0.9, one that it takes for few logits (V=8192, B=256 k=8 L=150 116 / 127).
     pl.early_stop = 0;
     pl.uniform_k = 0;
     if (r->T > r->B && r->T % r->B == 0) {
@@ -551,7 +554,7 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
         if (attn_us >= 0.0) {
             // a stage: a block reads its segment at its share of the memory's rate (12.5 KB per microsecond), and a hop
             const double chain_us = q * (2.0 + pl.stat_seg_len * 4.0 / 12500.0) + 30.0;
-            wanted = r->B >= 32 && chain_us <= 0.9 * attn_us + 2.5 * logits_us;
+            wanted = r->B >= 32 && attn_blocks > 2 * cus && chain_us <= 0.9 * attn_us + 2.5 * logits_us;
         } else {
             // One stage per position: it streams what is still needed of its rows (at an acceptance rate of 0.7),
             // in 6 us at least, and has a block per compute unit.  Against all rows in one go, in one

@@ -37,15 +37,15 @@ def step_plan(B, k, length, V, **kw):
     return sv.spec_verify_plan(attn_args(B, k, length, **kw), reject_args(B, k, V))
 
 
-# long race segments beside a short attention half end the launch: at least as many as 512 blocks give
-@pytest.mark.parametrize("B,k,length,V,least", [(128, 1, 400, 64128, 4), (256, 1, 400, 64128, 2), (64, 1, 400, 128256, 8),
-                                                (128, 1, 400, 128256, 4), (64, 4, 1000, 128256, 8)])
+# long race segments beside a short attention half end the launch: as many as 512 blocks give (384 where the attention goes first)
+@pytest.mark.parametrize("B,k,length,V,least", [(128, 1, 400, 64128, 4), (256, 1, 400, 64128, 2), (64, 1, 400, 128256, 6),
+                                                (128, 1, 400, 128256, 4), (64, 4, 1000, 128256, 6), (128, 4, 400, 64128, 3)])
 def test_large_vocabulary_beside_a_short_attention_half(B, k, length, V, least):
     assert step_plan(B, k, length, V)["race_segments"] >= least
 
 
 # where the segments are short, or the launch long, few blocks hold the attention's slots
-@pytest.mark.parametrize("B,k,length,V,segments", [(256, 2, 640, 32000, 1), (64, 1, 400, 32000, 4), (24, 4, 2000, 128256, 11),
+@pytest.mark.parametrize("B,k,length,V,segments", [(256, 2, 640, 32000, 1), (64, 1, 400, 32000, 4), (24, 4, 2000, 128256, 11), (48, 4, 150, 128256, 6),
                                                    (128, 4, 400, 32000, 2)])
 def test_few_race_blocks_beside_a_long_attention_half(B, k, length, V, segments):
     assert step_plan(B, k, length, V)["race_segments"] == segments
@@ -100,3 +100,14 @@ def test_a_workspace_without_room_for_many_blocks_is_not_refused():
                 # (no GPU here: past the size check the launch fails)
                 assert call(need) == sv.SPEC_EHIP, (B, k, V)
                 assert call(need - 256) == sv.SPEC_EWORKSPACE, (B, k, V)
+
+
+# the early stop's chain beside an attention half whose blocks all go first in the grid: measured slower in every case
+@pytest.mark.parametrize("B,k,length,V", [(64, 1, 1000, 32000), (64, 2, 1000, 8192), (64, 1, 1000, 128256), (32, 1, 1024, 8192)])
+def test_no_early_stop_beside_attention_blocks_that_go_first(B, k, length, V):
+    assert step_plan(B, k, length, V)["early_stop"] == 0
+
+
+@pytest.mark.parametrize("B,k,length,V", [(256, 2, 640, 32000), (128, 4, 512, 32000), (256, 1, 400, 64128)])
+def test_early_stop_beside_many_attention_blocks(B, k, length, V):
+    assert step_plan(B, k, length, V)["early_stop"] == 1
