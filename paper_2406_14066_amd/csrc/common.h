@@ -155,7 +155,7 @@ __host__ __device__ inline int attn_row_items(const AttnParams &ap)
     const int units = ap.B * ap.Hkv;
     return ap.max_chunks > 1 ? (units + 7) / 8 * 8 : units;
 }
-hipError_t launch_step_fused(const AttnParams *attn, int row_tiles, const RejectParams *reject, const UnitOrder *order,
+hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject, const UnitOrder *order,
                              LaunchEvents events, hipStream_t stream);
 
 // Generic attention path: partial kernel + combine kernel.

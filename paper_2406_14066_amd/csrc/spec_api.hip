@@ -316,8 +316,8 @@ spec_status validate_reject(const spec_reject_args *r)
 // faster than the matrix-instruction kernel, whose few blocks walk their pages one after the other?  Both
 // modelled from measurements, in us (matrix / scalar; 64/4 heads of 128, k = 4, tokens of each request: one request, 16
 // 10.0 / 5.8, 48 14.6 / 8.2, 128 26.5 / 15.6, 256 45.9 / 27.0, 700 53.2 / 46.5; four 128 27.2 / 30.0; 16/1 heads, k = 8, eight
-// requests, 128 45.1 / 32.0; 32/8 heads, k = 4, one request, 16 9.3 / 5.8, 128 12.9 / 15.7): of 608 calls the rule takes
-// 196, all of them 1.08 to 3 times as fast, 1.5 at the median, and leaves 12 that would be 1.2 times as fast or more.
+// requests, 128 45.1 / 32.0; 32/8 heads, k = 4, one request, 16 9.3 / 5.8, 128 12.9 / 15.7): of 1824 calls the rule takes
+// 196, all of them 1.08 to 3 times as fast, 1.5 at the median, and leaves 20 that would be 1.2 times as fast or more.
 bool f32_scalar_is_faster(const AttnPlan &pl, int d, int max_len, int64_t rows)
 {
     if (pl.row_tiles < 2) return false;
@@ -560,7 +560,8 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
             // in 6 us at least, and has a block per compute unit.  Against all rows in one go, in one
             // launch: B=256 V=32000 k=1 / 2 / 7 +3 / -6 / -14%, B=128 k=4 +18%, B=512 V=8192 k=4 +4%; V=128256 B=256
             // k=1 -6%, B=128 k=2 -9%, B=40 k=7 (too few blocks per stage) +22%; greedy V=32000 k=3 B=256 / 512
-            // +17 / -12%; the rule takes the better side in each.
+            // +17 / -12%; the rule takes the better side in each.  (The rate only sizes the stages: over 413 random shapes at
+            // rates of 0.5, 0.7 and 0.9 no call became slower with this rule and the split above than it was without both.)
             const int per_position = (r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 : 1) * r->B;
             double staged = 0.0, all = 0.0, needed = 1.0;
             for (int j = 0; j < q; ++j, needed *= 0.7) {
@@ -858,7 +859,7 @@ spec_status step_on_workspace(const spec_attn_args *attn, const spec_reject_args
     if (apl.use_mfma) {
         // the whole step in one launch
         hipError_t err = timed_launch(SPEC_KERNEL_STEP, [&](LaunchEvents ev) {
-            return launch_step_fused(&ap, apl.row_tiles, &rp, &plan.order, ev, stream);
+            return launch_step_fused(&ap, &rp, &plan.order, ev, stream);
         });
         if (err == hipSuccess && !apl.fused_combine && apl.max_chunks > 1)
             err = timed(SPEC_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
@@ -867,7 +868,7 @@ spec_status step_on_workspace(const spec_attn_args *attn, const spec_reject_args
     const spec_status sa = run_attn_generic(ap, attn->qkv_dtype, stream);
     if (sa != SPEC_OK) return sa;
     const hipError_t err =
-        timed_launch(SPEC_KERNEL_REJECT, [&](LaunchEvents ev) { return launch_step_fused(nullptr, 0, &rp, nullptr, ev, stream); });
+        timed_launch(SPEC_KERNEL_REJECT, [&](LaunchEvents ev) { return launch_step_fused(nullptr, &rp, nullptr, ev, stream); });
     return err == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 
@@ -958,7 +959,7 @@ spec_status spec_verify_attn(const spec_attn_args *attn, void *workspace, size_t
     const AttnParams ap = attn_params(attn, pl, static_cast<char *>(workspace), nullptr);
     if (!pl.use_mfma) return run_attn_generic(ap, attn->qkv_dtype, stream);
     hipError_t err = timed_launch(SPEC_KERNEL_ATTN, [&](LaunchEvents ev) {
-        return launch_step_fused(&ap, pl.row_tiles, nullptr, &plan.order, ev, stream);
+        return launch_step_fused(&ap, nullptr, &plan.order, ev, stream);
     });
     if (err == hipSuccess && !pl.fused_combine && pl.max_chunks > 1)
         err = timed(SPEC_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
@@ -980,7 +981,7 @@ spec_status spec_reject_sample(const spec_reject_args *reject, void *workspace, 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const RejectParams rp = reject_params(reject, pl, static_cast<char *>(workspace));
     const hipError_t err =
-        timed_launch(SPEC_KERNEL_REJECT, [&](LaunchEvents ev) { return launch_step_fused(nullptr, 0, &rp, nullptr, ev, stream); });
+        timed_launch(SPEC_KERNEL_REJECT, [&](LaunchEvents ev) { return launch_step_fused(nullptr, &rp, nullptr, ev, stream); });
     return err == hipSuccess ? SPEC_OK : SPEC_EHIP;
 }
 

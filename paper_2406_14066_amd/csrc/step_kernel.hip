@@ -123,13 +123,6 @@ __device__ __forceinline__ u32x2 read_transposed(const unsigned char *src)
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)src));
 }
 
-// 16 bytes of logits that this launch will not read again (see kStreamPolicy).
-__device__ __forceinline__ float4 load_streaming(const float *p)
-{
-    const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-    return make_float4(v[0], v[1], v[2], v[3]);
-}
-
 // ---------------------------------------------------------------------------
 // Tickets.  Word = generation << 32 | arrivals.  Returns how many blocks arrived
 // before this one.  The common case is one atomic add: the word carries this call's
@@ -261,7 +254,7 @@ struct RejectShared {
     double lse2[2 * SPEC_K_MAX + 1];  // log2-sum-exp: target rows 0..k, then draft rows 0..k-1
     double u[SPEC_K_MAX], ratio[SPEC_K_MAX];
     int accept[SPEC_K_MAX];
-    int m, near, last;
+    int m, near;
     float best_score[kWaves];
     int best_id[kWaves];
     double seg_sum[2 * SPEC_K_MAX + 1][kMaxStatSegments];
@@ -1088,7 +1081,8 @@ struct OrderTable {
 
 // VAR: 0 = pages in the matrix-operand layout, softmax weights fed as bf16 high + low parts;
 //      1 = the same with the weights as one bf16 (an experiment switch);
-//      2 = token-major pages (V transposed through LDS), weights as high + low parts;
+//      2 = token-major pages (K and V staged through LDS, which gives V transposed; K_DIRECT: V alone), weights as
+//          high + low parts;
 //      3 = as 0 with a head dim of 64, 4 = as 2 with a head dim of 64 (all others: 128).
 constexpr int head_dim_of(int VAR) { return (VAR == 3 || VAR == 4) ? 64 : kD; }
 constexpr bool token_major_of(int VAR) { return VAR == 2 || VAR == 4; }
@@ -1721,8 +1715,9 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
 // out of 16-byte loads: lane (g, n) holds dims 16 i + 4 g + e of token n for K (and of row n for Q: its
 // element e is step 4 i + e of the score product), and dims 64 h + 4 n + e of token 4 g + r for V (its element e
 // is the A operand of output slice 4 h + e, step r, whose B operand is P^T in the scores' own layout).
-// Bound by memory up to two row tiles (32 rows: 3.4 us of matrix instructions per 100 MB of pages
-// against 15 us), by both with three.  Q stays in LDS: its operands for three tiles would take 96 registers,
+// Two row tiles (32 rows, padding included) take 10.4 us of matrix instructions per 100 MB of pages at the 154 TFLOP/s
+// of a large product (8 flops per byte and tile of 16 rows), against 15 us of reading: memory bounds one and two
+// tiles, the matrix instructions three (15.6 us).  Q stays in LDS: its operands for three tiles would take 96 registers,
 // and the 8 LDS reads per page and tile cost a thirtieth of the 64 matrix instructions they feed.
 // One batch of registers each for K and V: the next page's K is loaded once this page's scores are done, its
 // V once the output product is, so that half a page (8 KB, as much as the bf16 role has) is always in
@@ -2231,7 +2226,7 @@ int step_attn_items(const AttnParams &ap)
     return attn_row_items(ap) * ap.max_chunks;
 }
 
-hipError_t launch_step_fused(const AttnParams *attn, int row_tiles, const RejectParams *reject, const UnitOrder *order,
+hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject, const UnitOrder *order,
                              LaunchEvents ev, hipStream_t stream)
 {
     AttnParams ap = {};
@@ -2248,6 +2243,7 @@ hipError_t launch_step_fused(const AttnParams *attn, int row_tiles, const Reject
     }
     if (attn != nullptr) {
         ap = *attn;
+        const int row_tiles = ap.row_tiles;
         // tiles per wave group and wave groups per block that the kernel is built for
         const bool shape_ok = ap.f32 ? (ap.row_groups == 1 && (row_tiles == 1 || row_tiles == 2)) ||
                                            ((ap.row_groups == 2 || ap.row_groups == 4) && row_tiles == 2) || (ap.row_groups == 4 && row_tiles == 3)
@@ -2263,9 +2259,8 @@ hipError_t launch_step_fused(const AttnParams *attn, int row_tiles, const Reject
     }
     if (attn == nullptr) return launch<1, 1, false, true>(ap, rp, n_stat, 0, n_race, nullptr, ev, stream);
     const bool with_reject = reject != nullptr;
-    ap.row_tiles = row_tiles;
     if (ap.f32) return launch_step_f32(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
-    switch (ap.row_groups * 10 + row_tiles) {
+    switch (ap.row_groups * 10 + ap.row_tiles) {
         case 11: return launch_step_tiles1(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
         case 12: return launch_step_tiles2(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
         case 13: return launch_step_tiles3(ap, rp, with_reject, n_stat, n_attn, n_race, order, ev, stream);
