@@ -36,10 +36,14 @@
  *     Hq % Hkv == 0, Hq/Hkv <= 16, kv_len[b] >= q_len[b] >= 1.
  *   - Speed: bf16 runs on the matrix-instruction kernel, the whole step in one
  *     launch, for every draft length and group width within the limits (up to
- *     9 * 16 fused rows per KV head) and both head dims: fastest with pages in
- *     the SPEC_KV_MFMA layout; token-major pages take the same kernel, 1 to 5%
- *     slower (K and V pass through LDS inside the kernel).  fp32 (token-major
- *     pages) has a one-launch kernel of its own.  spec_verify_plan tells which path a call takes.
+ *     9 * 16 fused rows per KV head) and both head dims.  Up to 48 fused rows
+ *     ((k + 1) * Hq / Hkv) it is fastest with pages in the SPEC_KV_MFMA layout;
+ *     token-major pages take the same kernel, 1 to 5% slower (K and V pass
+ *     through LDS inside the kernel).  With more rows the faster layout depends
+ *     on the shape: 64/8 heads, k = 7, 256 requests: token-major 4% faster.
+ *     fp32 (token-major pages) has a one-launch kernel of its own; the
+ *     attention alone of a few short requests on wide query groups takes the
+ *     scalar kernel, which is faster there.
  */
 #ifndef SPEC_VERIFY_H
 #define SPEC_VERIFY_H
@@ -212,7 +216,9 @@ typedef struct {
 /* Host-only: bytes of workspace the three calls below need for these shapes
  * (either argument may be NULL).  Returns 0 if the arguments are malformed.
  * The workspace must be 256-byte aligned device memory; its contents need no
- * initialisation and are undefined afterwards. */
+ * initialisation and are undefined afterwards.  A workspace asked for the largest
+ * batch and draft length serves the rejection half of smaller calls with that vocabulary too: where its
+ * records would not fit, the half runs with fewer blocks. */
 size_t spec_verify_workspace_bytes(const spec_attn_args *attn, const spec_reject_args *reject);
 
 /* (a) only: writes attn->out. */
@@ -252,8 +258,9 @@ spec_status spec_verify_step_static(const spec_attn_args *attn, const spec_rejec
  */
 #define SPEC_PATH_NONE 0
 #define SPEC_PATH_MFMA 1     /* bf16: matrix-instruction attention inside the one-launch step kernel */
-#define SPEC_PATH_GENERIC 2  /* fp32, in a one-launch kernel too; either type with SPEC_VERIFY_FORCE_GENERIC=1: the scalar
-                                attention kernel, plus a merge kernel when a request is split (launches tells them apart) */
+#define SPEC_PATH_GENERIC 2  /* fp32, whichever of its kernels runs (a step without SPEC_VERIFY_FORCE_GENERIC: the one-launch
+                                matrix-instruction kernel); either type with SPEC_VERIFY_FORCE_GENERIC=1: the scalar attention
+                                kernel, plus a merge kernel when a request is split */
 typedef struct {
     int32_t attn_path;       /* SPEC_PATH_* */
     int32_t row_tiles;       /* 16-row tiles of query rows per wavefront (1..3) */
@@ -393,7 +400,7 @@ int32_t spec_argmax_goodput(const spec_goodput_args *args, double *goodput_per_k
 #define SPEC_NUM_KERNELS 5
 #define SPEC_KERNEL_STEP 0          /* the whole step in one launch (attention + rejection sampling) */
 #define SPEC_KERNEL_ATTN 1          /* attention-only launch of the matrix-instruction kernel */
-#define SPEC_KERNEL_ATTN_GENERIC 2  /* scalar attention over one KV chunk (SPEC_VERIFY_FORCE_GENERIC=1) */
+#define SPEC_KERNEL_ATTN_GENERIC 2  /* scalar attention over one KV chunk (some fp32 attention-only calls; SPEC_VERIFY_FORCE_GENERIC=1) */
 #define SPEC_KERNEL_ATTN_COMBINE 3  /* merge of the generic kernel's chunk partials */
 #define SPEC_KERNEL_REJECT 4        /* rejection-sampling-only launch */
 spec_status spec_profile_begin(int32_t max_launches);
