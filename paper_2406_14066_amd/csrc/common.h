@@ -91,6 +91,13 @@ __host__ __device__ inline bool request_lengths_ok(int kv_len, int q_len, int ca
 //   race info of one request: m | near ties << 16
 constexpr int kStatWords = 3;
 
+// RejectParams::early_stop: what the statistics pass does about the rows after a request's first rejection
+enum : int32_t {
+    kReadAll = 0,    // takes the rows request by request and reads them all
+    kStopWait = 1,   // takes them in position order; a block waits for the request's earlier positions and skips its row after a rejection
+    kStopPeek = 2,   // the same, but it only looks at what has been published by then
+};
+
 struct RejectPlan {
     int32_t stat_segments, stat_seg_len;   // vocabulary segments per row in the statistics pass
     int32_t race_segments, race_seg_len;   // vocabulary segments per request in the race
@@ -111,8 +118,8 @@ struct RejectParams {
     int32_t race_segments, race_seg_len;
     int32_t spin_limit;                  // polls a consumer block spends waiting for its producers
     uint32_t generation;
-    int32_t early_stop;                  // statistics in position order, rows after a request's first rejection are not read (see stats_role)
-    int32_t uniform_k;                   // with early_stop: every request's draft length
+    int32_t early_stop;                  // one of the above
+    int32_t uniform_k;                   // with early stop: every request's draft length, or -1 (they differ; at most 256 requests)
     int32_t short_naps;                  // a small launch: the bounded waits poll at short intervals at first
     int32_t final_shift;                 // log2 of the requests per item of the final stage (0..kMaxFinalShift)
     const float *target_logits, *draft_logits;

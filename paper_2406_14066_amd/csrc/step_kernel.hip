@@ -19,9 +19,11 @@
 // lowest id) per (target row, segment) in the statistics stage and has no race; a
 // point-mass draft needs statistics of the target rows only and leaves the rejected
 // token out of the race.
-// Large batches with one draft length take the statistics items in position order and skip
-// the rows after a request's first rejection (stats_role): the accept chain of a request
-// stops there (Section 4), so those rows decide nothing.
+// Large batches take the statistics items in position order and skip the rows after a request's
+// first rejection (stats_role): the accept chain of a request stops there (Section 4), so those rows
+// decide nothing.  A block finds out by waiting for the earlier positions or by looking at what they
+// have published (kStopWait, kStopPeek; 96 requests on 64/8 heads, k = 7, V = 32000: 97.7 us with all rows read,
+// 93.3 waiting, 86.7 looking; the planner says which).
 // The rejection items keep that order among themselves and are mixed into the first part
 // of the attention items (see GridSplit), so that the rejection half, whose stages depend
 // on each other, runs underneath the attention stream and is done before it.
@@ -261,6 +263,7 @@ struct RejectShared {
     float seg_off[2 * SPEC_K_MAX + 1][kMaxStatSegments];
     // final stage: per request of the block
     int fin_ready[kMaxFinalGroup], fin_need[kMaxFinalGroup], fin_id[kMaxFinalGroup];
+    int pos_count[SPEC_K_MAX + 2][kWaves], pos_request;   // see position_item
     uint32_t fin_count[2];
     f32x4 variates[kRaceVec][kThreads];   // 1 / e_v of a race block's part, each thread its own
 };
@@ -697,6 +700,169 @@ __device__ __forceinline__ bool greedy_prefix(const RejectParams &p, int b, int 
     return true;
 }
 
+// The row of a statistics item in position order: the target and draft rows (the target rows, if the draft
+// is a point mass or the mode is greedy) of position 0 of all requests, then those of position 1, ...; a request's
+// bonus row counts as a target row of position k.
+struct PositionItem {
+    int j, b, row;
+};
+__device__ __forceinline__ bool position_item(const RejectParams &p, int rec, RejectShared &sh, PositionItem &at)
+{
+    const bool has_draft_rows = p.mode == SPEC_ACCEPT_SAMPLE;
+    bool is_draft = false;
+    if (p.uniform_k >= 0) {   // one draft length: the bonus rows make up the last position
+        const int k = p.uniform_k;
+        const int per_position = has_draft_rows ? 2 * p.B : p.B;
+        if (rec < per_position * k) {
+            at.j = rec / per_position;
+            const int w = rec - at.j * per_position;
+            at.b = has_draft_rows ? w >> 1 : w;
+            is_draft = has_draft_rows && (w & 1) != 0;
+        } else {
+            at.j = k;
+            at.b = rec - per_position * k;
+        }
+        const int row_t0 = at.b * (k + 1);
+        at.row = is_draft ? p.T + (row_t0 - at.b) + at.j : row_t0 + at.j;
+        return true;
+    }
+    // Draft lengths of their own (up to kThreads requests): thread t looks at request t, and the counts of requests with
+    // k >= 0, 1, ... say which position the item is in and which of its requests it belongs to.
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int row_t0 = tid < p.B ? p.cu_q_len[tid] : 0;
+    const int k = tid < p.B ? p.cu_q_len[tid + 1] - row_t0 - 1 : -1;
+#pragma unroll
+    for (int i = 0; i < SPEC_K_MAX + 2; ++i) {
+        const unsigned long long has = __builtin_amdgcn_ballot_w64(k >= i);
+        if (lane == 0) sh.pos_count[i][wave] = __builtin_popcountll(has);
+    }
+    if (tid == 0) sh.pos_request = -1;
+    __syncthreads();
+    int j = 0, n_draft = 0;
+    for (;; ++j) {
+        if (j > SPEC_K_MAX) return false;   // (lengths on the device that are not the host's)
+        int n_target = 0;
+        n_draft = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            n_target += sh.pos_count[j][w];
+            n_draft += sh.pos_count[j + 1][w];
+        }
+        const int n = n_target + (has_draft_rows ? n_draft : 0);
+        if (rec < n) break;
+        rec -= n;
+    }
+    // the rank-th request, in the given order, of those with k > j (target and draft row side by side), k == j
+    // (bonus rows, after them), or, with target rows only, k >= j
+    const bool bonus = has_draft_rows && rec >= 2 * n_draft;
+    const int rank = !has_draft_rows ? rec : (bonus ? rec - 2 * n_draft : rec >> 1);
+    is_draft = has_draft_rows && !bonus && (rec & 1) != 0;
+    const bool mine = !has_draft_rows ? k >= j : (bonus ? k == j : k > j);
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const int above = sh.pos_count[j + 1][w], from = sh.pos_count[j][w];
+        if (w < wave) before += !has_draft_rows ? from : (bonus ? from - above : above);
+    }
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(mine);
+    if (mine && before + __builtin_popcountll(mask & ((1ull << lane) - 1ull)) == rank) sh.pos_request = tid;
+    __syncthreads();
+    at.j = j;
+    at.b = __builtin_amdgcn_readfirstlane(sh.pos_request);
+    if (at.b < 0) return false;
+    const int t0 = uniform_load(p.cu_q_len, at.b);
+    at.row = is_draft ? p.T + (t0 - at.b) + j : t0 + j;
+    __syncthreads();   // (the statistics use the same memory)
+    return true;
+}
+
+// Do the records that have been published so far show that one of the first j accept tests of request b fails?  Does
+// not wait: a test whose records are not all there yet, or that is closer than a hundredth to its threshold, shows nothing
+// (the exact decision is the accept chain's; this one only says which rows need not be read).  Half a wavefront
+// looks at one position, a lane at one segment of its rows.
+static_assert(SPEC_K_MAX * 32 <= kThreads && kMaxStatSegments <= 32, "half a wavefront per position, a lane per segment");
+__device__ __forceinline__ bool rejected_before(const RejectParams &p, int b, int j)
+{
+    const int i = threadIdx.x >> 5, sg = threadIdx.x & 31;
+    const bool greedy = p.mode == SPEC_ACCEPT_GREEDY, has_draft_rows = p.mode == SPEC_ACCEPT_SAMPLE;
+    const int row_t0 = uniform_load(p.cu_q_len, b);
+    const int row_d0 = row_t0 - b;
+    bool reject = false;
+    if (i < j) {
+        const int x = p.draft_tokens[row_d0 + i];
+        bool here = true;
+        if (greedy) {
+            float best = -INFINITY;
+            int id = 0x7FFFFFFF;
+            if (sg < p.stat_segments) {
+                const unsigned long long *st = p.stats + kStatWords * ((size_t)(row_t0 + i) * p.stat_segments + sg);
+                const unsigned long long w0 = fetch_u64(st), w1 = fetch_u64(st + 1);
+                here = tagged_ok(w0, p.generation) && tagged_ok(w1, p.generation);
+                const float v = __uint_as_float((uint32_t)w0);
+                if (v >= best) { best = v; id = (int)(uint32_t)w1; }
+            }
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) {
+                const float ov = __shfl_xor(best, o);
+                const int oi = __shfl_xor(id, o);
+                if (ov > best || (ov == best && oi < id)) { best = ov; id = oi; }
+            }
+            reject = x != (id == 0x7FFFFFFF ? 0 : id);
+        } else {
+            unsigned long long t[kStatWords], d[kStatWords];
+            float off_t = kEmptyMax, off_d = kEmptyMax, sum_t = 0.0f, sum_d = 0.0f, tx = -INFINITY, dx = 0.0f;
+            if (sg < p.stat_segments) {
+                const unsigned long long *st = p.stats + kStatWords * ((size_t)(row_t0 + i) * p.stat_segments + sg);
+                const unsigned long long *sd = p.stats + kStatWords * ((size_t)(p.T + row_d0 + i) * p.stat_segments + sg);
+#pragma unroll
+                for (int w = 0; w < kStatWords; ++w) {
+                    t[w] = fetch_u64(st + w);
+                    d[w] = has_draft_rows ? fetch_u64(sd + w) : 0ull;
+                }
+            }
+            if ((unsigned)x < (unsigned)p.V) {
+                tx = p.target_logits[(size_t)(row_t0 + i) * p.V + x];
+                if (has_draft_rows) dx = p.draft_logits[(size_t)(row_d0 + i) * p.V + x];
+            }
+            const StepWords step = philox_step_words(p);
+            const uint4 w = philox4x32_10(make_uint4((uint32_t)i, (uint32_t)b, step.lo, (step.hi24 << 8) | 0u), p.seed_lo, p.seed_hi);
+            if (sg < p.stat_segments) {
+#pragma unroll
+                for (int u = 0; u < kStatWords; ++u)
+                    here = here && tagged_ok(t[u], p.generation) && (!has_draft_rows || tagged_ok(d[u], p.generation));
+                off_t = __uint_as_float((uint32_t)t[2]);
+                sum_t = (float)__longlong_as_double((long long)((t[0] & 0xFFFFFFFFull) | (t[1] << 32)));
+                if (has_draft_rows) {
+                    off_d = __uint_as_float((uint32_t)d[2]);
+                    sum_d = (float)__longlong_as_double((long long)((d[0] & 0xFFFFFFFFull) | (d[1] << 32)));
+                }
+            }
+            float mt = off_t, md = off_d;
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) {
+                mt = fmaxf(mt, __shfl_xor(mt, o));
+                md = fmaxf(md, __shfl_xor(md, o));
+            }
+            sum_t *= fast_exp2(off_t - mt);
+            sum_d *= fast_exp2(off_d - md);
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) {
+                sum_t += __shfl_xor(sum_t, o);
+                sum_d += __shfl_xor(sum_d, o);
+            }
+            // log2 of p/q: the offsets, which may be large, are taken off in fp64
+            float lr = (float)((double)tx * kLog2eD - (double)mt) - __builtin_amdgcn_logf(sum_t);
+            if (has_draft_rows) lr = (float)((double)tx * kLog2eD - (double)mt - ((double)dx * kLog2eD - (double)md)) -
+                                     (__builtin_amdgcn_logf(sum_t) - __builtin_amdgcn_logf(sum_d));
+            const float u = (float)(w.x >> 8) * 5.9604644775390625e-8f;
+            reject = __builtin_amdgcn_logf(u) > lr + 0.015f;
+        }
+        const unsigned long long missing = __builtin_amdgcn_ballot_w64(!here);
+        reject = reject && ((missing >> (threadIdx.x & 32)) & 0xFFFFFFFFull) == 0;
+    }
+    return __syncthreads_or(reject ? 1 : 0) != 0;
+}
+
 // Statistics items are ordered by request (its target rows, then its draft rows), so that
 // the first requests' statistics are complete early and their races can start while
 // later requests' rows are still being read.
@@ -705,33 +871,19 @@ __device__ __forceinline__ void stats_role(const RejectParams &p, int item, Reje
 {
     const int rec = item / p.stat_segments;          // (request, row of the request)
     const int seg = item - rec * p.stat_segments;
-    if (p.early_stop) {
-        // Position order (every request has uniform_k draft tokens): the target and draft rows (the
-        // target rows, if the draft is a point mass) of position 0 of all requests, then those of
-        // position 1, ..., then the bonus rows.  The rows
-        // of a position are only needed if the request's earlier positions were all accepted; by
-        // the time a block of position j starts, the statistics of positions < j were dispatched
-        // long before (two items per request and position), so the check costs a round trip, not a
-        // wait.  A row that is not needed gets a placeholder record, so that later stages, which
+    if (p.early_stop != kReadAll) {
+        // Position order: the rows of a position are only needed if the request's earlier positions were all
+        // accepted, and by the time a block of position j starts, those of positions < j were dispatched
+        // long before.  A row that is not needed gets a placeholder record, so that later stages, which
         // poll all of a request's records and use those up to the first rejection, find it.
-        const int k = p.uniform_k;
-        const bool has_draft_rows = p.mode == SPEC_ACCEPT_SAMPLE;
-        const int per_position = has_draft_rows ? 2 * p.B : p.B;
-        int j, b;
-        bool is_draft = false;
-        if (rec < per_position * k) {
-            j = rec / per_position;
-            const int w = rec - j * per_position;
-            b = has_draft_rows ? w >> 1 : w;
-            is_draft = has_draft_rows && (w & 1) != 0;
-        } else {
-            j = k;
-            b = rec - per_position * k;
-        }
-        const int row_t0 = b * (k + 1);
-        const int row = is_draft ? p.T + (row_t0 - b) + j : row_t0 + j;
+        PositionItem at;
+        if (!position_item(p, rec, sh, at)) return;
+        const int j = at.j, b = at.b, row = at.row;
         const bool greedy = p.mode == SPEC_ACCEPT_GREEDY;
-        if (j > 0 && (greedy ? greedy_prefix(p, b, j, sh) : accept_phase(p, b, sh, false, j)) && sh.m < j) {
+        bool skip = false;
+        if (j > 0 && p.early_stop == kStopPeek) skip = rejected_before(p, b, j);
+        else if (j > 0) skip = (greedy ? greedy_prefix(p, b, j, sh) : accept_phase(p, b, sh, false, j)) && sh.m < j;
+        if (skip) {
             if (threadIdx.x == 0) {
                 unsigned long long *dst = p.stats + 3 * ((size_t)row * p.stat_segments + seg);
                 if (greedy) {   // (largest logit, id) of nothing

@@ -99,6 +99,39 @@ def test_requests_grouped_in_the_final_stage(harness, B, mode):
             check_reject(w, res, ref=ref, max_excluded=1)
 
 
+# rows in position order, each skipped if what its request's earlier positions have published shows a rejection: one draft
+# length and several, one block's worth of requests and (several lengths, which then keep the request order) more
+@pytest.mark.parametrize("mode", [sv.ACCEPT_SAMPLE, sv.ACCEPT_GREEDY, sv.ACCEPT_POINT_DRAFT], ids=["sample", "greedy", "point"])
+@pytest.mark.parametrize("B,V,uniform", [(1, 1024, True), (1, 70000, False), (63, 2052, False), (64, 2052, True), (129, 17000, False),
+                                         (256, 2052, False), (257, 2052, False), (300, 1024, True)],
+                         ids=lambda v: str(v))
+def test_early_stop_that_looks_at_earlier_positions(harness, tuning, B, V, uniform, mode):
+    print("case look", B, V, uniform, mode, flush=True)
+    rng = np.random.default_rng(B + V)
+    w = _logits_only(B, V, [6] * B if uniform else rng.integers(0, 9, size=B), seed=B)
+    if mode == sv.ACCEPT_GREEDY:
+        hit = rng.random(w.T - B) < 0.7
+        rows = np.concatenate([np.arange(w.cu_q_len[b], w.cu_q_len[b + 1] - 1) for b in range(B)])
+        w.draft_tokens = np.where(hit, w.target_logits[rows].argmax(1), w.draft_tokens).astype(np.int32)
+    tuning("SPEC_VERIFY_EARLY_STOP", 2)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=mode)
+    assert ds.plan()["early_stop"] == (1 if w.T > B and (uniform or B <= 256) else 0)
+    for _ in range(2):   # the second call finds the first one's records cleared or out of date
+        ds.counters.zero_()
+        ds.out_tokens.fill_(-7)
+        ds.run_reject()
+        res = ds.results()
+        if mode == sv.ACCEPT_GREEDY:
+            ref = oracle.reject_greedy(w.target_logits, w.draft_tokens, w.cu_q_len)
+            for name in ("accepted_len", "next_token", "out_tokens", "counters"):
+                np.testing.assert_array_equal(res[name], getattr(ref, name))
+        else:
+            ref = None
+            if mode == sv.ACCEPT_POINT_DRAFT:
+                ref = oracle.reject_onehot(w.target_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
+            check_reject(w, res, ref=ref, max_excluded=1)
+
+
 def test_offsets_far_apart_and_segments_of_nothing(harness):
     """Row statistics whose segments differ by thousands of powers of two, and segments of nothing but -inf: the
     accept chain rescales them exactly (a segment far below the row's maximum adds nothing)."""
