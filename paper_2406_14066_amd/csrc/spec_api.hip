@@ -470,7 +470,8 @@ double attn_estimate_us(const spec_attn_args *a)
 // attn_us: rough duration of the attention half that runs in the same launch (microseconds), or
 // negative if the rejection half runs alone; attn_blocks: its blocks.  few_records: alone, but with no more statistics and race blocks than beside
 // an attention half (at most two per compute unit), for a workspace that has no room for more.
-RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0, int64_t attn_blocks = 0, bool few_records = false)
+RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0, int64_t attn_blocks = 0, bool few_records = false,
+                       bool peek = true)
 {
     RejectPlan pl;
     memset(&pl, 0, sizeof pl);
@@ -586,7 +587,8 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     // heads, B=200 k=3 93.7 / 90.0, B=64 k=5 (nothing is saved) 49.9 / 52.8.  Over 138 steps (24 to 256 requests, all modes, rates of
     // 0.5, 0.7 and 0.9) the rule takes a sixth of them, 15% faster to 5% slower, 5% faster in the mean.  Not where the
     // rejection half runs alone: its blocks fill the chip at once (four per unit) and start together; 120 such calls -7 to +29%.
-    if (r->T > r->B && (uniform_q > 0 || r->B <= 256)) {
+    // (peek: the kernel that takes the launch can.)
+    if (peek && r->T > r->B && (uniform_q > 0 || r->B <= 256)) {
         const int sides = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 : 1;
         const double in_flight = (double)cus / ((double)sides * r->B * pl.stat_segments);   // positions
         double saved_rows = 0.0;
@@ -749,8 +751,9 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     if (r != nullptr) {
         const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
         const int64_t attn_blocks = a != nullptr ? (int64_t)a->B * a->Hkv * e.apl.max_chunks : 0;
-        e.rpl = plan_reject(r, base, tu, attn_us, attn_blocks);
-        e.rpl_small = attn_us < 0.0 ? plan_reject(r, base, tu, attn_us, attn_blocks, true) : e.rpl;
+        const bool peek = attn_us < 0.0 || a->qkv_dtype == SPEC_BF16;
+        e.rpl = plan_reject(r, base, tu, attn_us, attn_blocks, false, peek);
+        e.rpl_small = attn_us < 0.0 ? plan_reject(r, base, tu, attn_us, attn_blocks, true, peek) : e.rpl;
         if (e.rpl_small.total_bytes > e.rpl.total_bytes) e.rpl_small = e.rpl;
         e.workspace_bytes = std::max(base + e.rpl.total_bytes, (attn_us < 0.0 ? base : 0) + reject_room(r, tu));
     }
