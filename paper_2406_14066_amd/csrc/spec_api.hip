@@ -422,14 +422,16 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
     // 22.4 / 21.6, 200 31.0 / 28.5, 400 42.3 / 38.3, 1000 (memory) 79.9 / 84.0; 1280 blocks, 200 +6%, 300 +6%, 450 +4%, 700 +2%, 1000
     // -2%; k = 4, 768 blocks, 120 +6%, 300 -2%; 1280 blocks, 120 +6%, 200 +10%, 300 +2%, 700 -2%; lengths from a tenth of to
     // twice the mean gain nothing.
-    // Two wave groups: at most a block per compute unit, with 256 tokens or fewer.  64/8 heads, k = 7, four requests of
-    // 16 / 100 / 200 tokens: direct 5, 4 and 6% faster; 64 requests (two blocks per unit) of 100 / 200 tokens 0 and 6% slower.
+    // Two wave groups of three row tiles: at most a block per compute unit, with 256 tokens or fewer.  64/8 heads, k = 7, four
+    // requests of 16 / 100 / 200 tokens: direct 5, 4 and 6% faster than the staged walk page by page; 64 requests (two blocks per unit) of
+    // 100 / 200 tokens 0 and 6% slower.  Two row tiles, which the staged walk takes in pairs of pages, are at least as fast that
+    // way (32 requests of 100 / 256 tokens, staged / direct 10.0 / 10.4, 13.2 / 14.5 us).
     const int d_units = a->B * a->Hkv;
     pl.k_direct = 0;
     if (a->qkv_dtype == SPEC_BF16 && a->kv_layout == SPEC_KV_TOKEN_MAJOR && a->d == 128 && pl.use_mfma && pl.row_tiles >= 2) {
         const int cus = compute_units();
         if (pl.row_groups == 2) {
-            pl.k_direct = pl.chunk_tokens <= 256 && (int64_t)d_units * pl.max_chunks <= cus;
+            pl.k_direct = pl.row_tiles == 3 && pl.chunk_tokens <= 256 && (int64_t)d_units * pl.max_chunks <= cus;
         } else if (pl.row_groups == 1 && pl.max_chunks == 1 && a->host_kv_len != nullptr && d_units > 2 * cus) {
             int64_t sum = 0;
             int longest = 0;

@@ -1558,6 +1558,16 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     constexpr bool TM = token_major_of(VAR);
     constexpr bool STAGED = staged_walk(WG, TM, K_DIRECT);
     constexpr int D = head_dim_of(VAR);
+    // Which walks take two pages at a time (consume_pair).  The staged one, up to two row tiles or a head dim of 64 (three of
+    // 128 leave no registers for a second page's operands): attention alone, 64/8 heads, k = 7, 96 / 256 requests of 256 to
+    // 1024 tokens 63.1 -> 61.0 / 138.6 -> 135.9 us; head dim 64, 64/4 heads, 32 requests of 300 to 2900, k = 3 35.1 -> 31.3, k = 5 42.9 ->
+    // 40.4.  A wavefront's own walk on token-major pages of 64 dims with two or three row tiles: 32/8 heads, 64 requests of
+    // 200 to 1900 tokens, k = 7 / 8 31.0 -> 30.0 / 33.0 -> 31.4; four of 9000 to 18000, k = 8 37.5 -> 34.4; 128 of 100, k = 5 14.9 -> 14.2.
+    // (Not elsewhere: one row tile of 64 dims 28.5 -> 28.3 and, 256 short requests, 38.5 -> 38.8; tiled pages of 64 dims 28.0 ->
+    // 28.4; 128 dims, one tile, 43.9 -> 50.5 at an occupancy step less, two tiles 41.1 -> 42.9.  With K straight into operand
+    // order it takes the staged walk's pairs, whose sums it has to equal.)
+    constexpr bool PAIRS_STAGED = STAGED && (NT <= 2 || D == 64);
+    constexpr bool PAIR_WALK = !STAGED && TM && ((D == 64 && NT >= 2) || (K_DIRECT && NT == 2 && WG == 2));
     constexpr int KK = D / 32;                        // 32-dim steps of the score product = 1 KB loads per K or V page
     constexpr int MT = D / 16;                        // 16-dim slices of the output
     constexpr int kQStride = q_stride(D);
@@ -1627,6 +1637,18 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         // token (512 / D) i + 8 L / D, dims 8 (L % (D / 8)) .. + 7
 #pragma unroll
         for (int i = 0; i < KK; ++i) r.v[i] = __builtin_amdgcn_raw_buffer_load_b128(vd, lane_off, i * 1024, kStreamPolicy);
+    };
+
+    // K or V of the it-th page of this wavefront
+    auto load_half = [&](int it, const char *head, bool direct, u32x4(&r)[KK]) {
+        const int entry = __builtin_amdgcn_readlane(bt, it < my_pages ? it : 0);
+        const bool valid = it < my_pages && entry >= 0;
+        const __amdgpu_buffer_rsrc_t desc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(head + (size_t)(valid ? entry : 0) * page_stride), 0, valid ? kPageHeadBytes : 0, kBufferFlags);
+#pragma unroll
+        for (int i = 0; i < KK; ++i)
+            r[i] = direct ? __builtin_amdgcn_raw_buffer_load_b128(desc, n16 * (D * 2) + g * 16, i * 64, kStreamPolicy)
+                          : __builtin_amdgcn_raw_buffer_load_b128(desc, lane_off, i * 1024, kStreamPolicy);
     };
 
     f32x4 acc[NT][MT];
@@ -1736,6 +1758,83 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
         }
     };
 
+    // Two pages at a time: their scores are two independent chains, one look at the reference serves both, and the output
+    // product contracts 32 tokens per instruction, which the matrix cores take at twice the rate of 16 (slots 8 g .. + 3 of
+    // the contraction are the first page's tokens 4 g .. + 3, the other four the second's).  k0, k1: the pages' K operands;
+    // then_values is called once they are used and gives V's: v[mt] for dims 16 mt .. + 15, the first page's tokens in x
+    // and y, the second's in z and w.  has1 == false: there is no second page (its operands are finite).
+    auto consume_pair = [&](const u32x4(&k0)[KK], const u32x4(&k1)[KK], auto then_values, int pi0, int pi1, bool has1) {
+        const int tb0 = tok0 + pi0 * SPEC_BLOCK_SIZE + 4 * g, tb1 = tok0 + pi1 * SPEC_BLOCK_SIZE + 4 * g;
+        const bool need_mask = !has1 || tok0 + (pi1 + 1) * SPEC_BLOCK_SIZE > first_masked_token;
+        f32x4 s[NT][2];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            s[nt][0] = s[nt][1] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+            if (nt > 0 && nt * 16 >= grp_rows) continue;   // a tile this request has no rows for (the same for the whole wavefront)
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                s[nt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k0[kk]), qreg[nt][kk], s[nt][0], 0, 0, 0);
+                s[nt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k1[kk]), qreg[nt][kk], s[nt][1], 0, 0, 0);
+            }
+        }
+        u32x4 v[MT];
+        then_values(v);
+        if (!has1 || tok0 + (pi1 + 1) * SPEC_BLOCK_SIZE > L) {   // slots past kv_len may hold anything: clear their V
+            const int n0 = L - tb0, n1 = has1 ? L - tb1 : 0;
+            const u32x4 keep = {n0 >= 2 ? 0xFFFFFFFFu : (n0 == 1 ? 0x0000FFFFu : 0u), n0 >= 4 ? 0xFFFFFFFFu : (n0 == 3 ? 0x0000FFFFu : 0u),
+                                n1 >= 2 ? 0xFFFFFFFFu : (n1 == 1 ? 0x0000FFFFu : 0u), n1 >= 4 ? 0xFFFFFFFFu : (n1 == 3 ? 0x0000FFFFu : 0u)};
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) v[mt] &= keep;
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if (nt > 0 && nt * 16 >= grp_rows) continue;
+            if (need_mask) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (tb0 + r > limit[nt]) s[nt][0][r] = -INFINITY;
+                    if (!has1 || tb1 + r > limit[nt]) s[nt][1][r] = -INFINITY;
+                }
+            }
+            float mx = fmaxf(fmaxf(s[nt][0][0], s[nt][0][1]), fmaxf(s[nt][0][2], s[nt][0][3]));
+            mx = fmaxf(mx, fmaxf(fmaxf(s[nt][1][0], s[nt][1][1]), fmaxf(s[nt][1][2], s[nt][1][3])));
+            raise_reference(nt, mx);
+            bf16x8 p_hi, p_lo;
+            float sum = 0.0f;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x4 pr;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) pr[r] = fast_exp2(fmaf(s[nt][h][r], p.scale_log2, -m_run[nt]));
+                sum += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+                const bf16x4 hi = __builtin_convertvector(pr, bf16x4);
+                const bf16x4 lo = __builtin_convertvector(pr - __builtin_convertvector(hi, f32x4), bf16x4);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    p_hi[4 * h + r] = hi[r];
+                    p_lo[4 * h + r] = lo[r];
+                }
+            }
+            l_run[nt] += sum;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const bf16x8 va = __builtin_bit_cast(bf16x8, v[mt]);
+                acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, p_hi, acc[nt][mt], 0, 0, 0);
+                acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, p_lo, acc[nt][mt], 0, 0, 0);
+            }
+        }
+    };
+    // Operands of a page out of LDS (token rows, padded): K as 16 bytes of a row, V through the transposing read.
+    auto k_operand = [&](const unsigned char *page, int i) { return *reinterpret_cast<const u32x4 *>(page + n16 * kVtRowBytes + i * 64 + g * 16); };
+    auto v_operands = [&](const unsigned char *page0, const unsigned char *page1, u32x4(&v)[MT]) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int at = (4 * g + (n16 >> 2)) * kVtRowBytes + (n16 & 3) * 8 + mt * 32;
+            const u32x2 v0 = read_transposed(page0 + at), v1 = read_transposed(page1 + at);
+            v[mt] = (u32x4){v0.x, v0.y, v1.x, v1.y};
+        }
+    };
+
     // Q as the B operand of S^T = K Q^T, out of LDS (the first pages are on their way)
     auto stage_q = [&] {
 #pragma unroll
@@ -1802,12 +1901,23 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
                     const int round = t + i;
                     if (grp_rows > 0) {
 #pragma unroll 1
-                        for (int slot = pw; slot < kWaves; slot += PW) {
+                        for (int slot = pw; slot < kWaves; slot += PAIRS_STAGED ? 2 * PW : PW) {
                             const int page = round * kWaves + slot;
                             if (page < w.npages) {
-                                PageRegs<D> cur;
-                                fetch_page(round & 1, slot, cur);
-                                consume(cur, page);
+                                if constexpr (PAIRS_STAGED) {
+                                    const unsigned char(*ring0)[kVtWaveBytes] = sh.ring[round & 1][slot], (*ring1)[kVtWaveBytes] = sh.ring[round & 1][slot + PW];
+                                    u32x4 k0[KK], k1[KK];
+#pragma unroll
+                                    for (int i = 0; i < KK; ++i) {
+                                        k0[i] = k_operand(ring0[0], i);
+                                        k1[i] = k_operand(ring1[0], i);
+                                    }
+                                    consume_pair(k0, k1, [&](u32x4(&v)[MT]) { v_operands(ring0[1], ring1[1], v); }, page, page + PW, page + PW < w.npages);
+                                } else {
+                                    PageRegs<D> cur;
+                                    fetch_page(round & 1, slot, cur);
+                                    consume(cur, page);
+                                }
                             }
                         }
                     }
@@ -1819,6 +1929,48 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             }
         }();
         __syncthreads();   // every wavefront is done with the ring: the epilogue reuses the memory
+    } else if constexpr (PAIR_WALK) {
+        // Two pages at a time: the next pair's K is loaded once this pair's scores are done, its V once this pair's V is
+        // in LDS, so that half a pair at least is always in flight.
+        u32x4 k0[KK], k1[KK], v0[KK], v1[KK];
+        auto load_k = [&](int it) { load_half(it, khead, K_DIRECT, k0); load_half(it + 1, khead, K_DIRECT, k1); };
+        auto load_v = [&](int it) { load_half(it, vhead, false, v0); load_half(it + 1, vhead, false, v1); };
+        load_k(0);
+        load_v(0);
+        stage_q();
+        // this wavefront's LDS region: room for two pages, K's and then V's (LDS executes a wavefront's accesses in order,
+        // so reads see the writes before them, and no write overtakes a read, without a barrier)
+        unsigned char *const lds0 = sh.vt + wave * (2 * kVtWaveBytes), *const lds1 = lds0 + kVtWaveBytes;
+        constexpr int LR = D / 8;   // lanes per token row of a 1 KB load (16 bytes each)
+        auto to_lds = [&](const u32x4(&r0)[KK], const u32x4(&r1)[KK]) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < KK; ++i) {
+                const int at = ((kWave / LR) * i + lane / LR) * kVtRowBytes + (lane % LR) * 16;
+                *reinterpret_cast<u32x4 *>(lds0 + at) = r0[i];
+                *reinterpret_cast<u32x4 *>(lds1 + at) = r1[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        for (int it = 0; it < my_pages; it += 2) {
+            if constexpr (!K_DIRECT) {
+                to_lds(k0, k1);
+#pragma unroll
+                for (int i = 0; i < KK; ++i) {
+                    k0[i] = k_operand(lds0, i);
+                    k1[i] = k_operand(lds1, i);
+                }
+            }
+            consume_pair(k0, k1, [&](u32x4(&v)[MT]) {
+                load_k(it + 2);
+                to_lds(v0, v1);
+                load_v(it + 2);
+                v_operands(lds0, lds1, v);
+            }, pw + PW * it, pw + PW * (it + 1), it + 1 < my_pages);
+        }
     } else {
         // Two register batches of P pages each.  While one batch is consumed the loads of the
         // other are in flight.  The order inside a half-step matters: first wait for the batch

@@ -111,3 +111,26 @@ def test_bad_block_table_entries_read_as_zeros_and_are_counted_once(tuning, path
         w.v_pages[p] = 0
     err = np.abs(got.astype(np.float64) - _oracle(w)).max()
     assert err <= ATTN_TOL[path[0]], err
+
+
+# walks that take two pages at a time: a last page without a partner, one page, a page that a later chunk owns, short
+# drafts that leave a tile or a group without rows, and values that are not finite past the end of a request
+@pytest.mark.parametrize("kv_len", [(9, 16, 17, 33, 48, 49, 64, 65, 100, 129, 1000), (257, 9, 271, 1000, 513, 16, 2049)], ids=["unsplit", "split"])
+@pytest.mark.parametrize("Hq,Hkv,d,k_max", [(8, 2, 64, 7), (16, 4, 64, 8), (32, 8, 64, 4), (16, 2, 64, 6), (16, 2, 64, 8), (32, 2, 64, 6), (16, 1, 64, 8),
+                                            (16, 2, 128, 6), (32, 2, 128, 6)])
+def test_pairs_of_pages(Hq, Hkv, d, k_max, kv_len):
+    from paper_2406_14066_amd.harness import DeviceStep
+    print("case pairs", Hq, Hkv, d, k_max, kv_len, flush=True)
+    k = [min(x, k_max) for x in [8, 0, 1, 8, 3, 5, 8, 0, 2, 8, 8][: len(kv_len)]]
+    w = W.make_workload("pairs", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=d, V=256, dtype="bf16", kv_len=list(kv_len), k=k,
+                        draft_std=2.0, sigma=0.8, data_seed=Hq + k_max + d, philox_seed=9)
+    inf = np.uint16(0x7F80) if w.v_pages.dtype == np.uint16 else np.inf
+    for b, n in enumerate(kv_len):
+        if n % 16:
+            w.v_pages[w.block_table[b, n // 16], :, n % 16:] = inf
+            w.k_pages[w.block_table[b, n // 16], :, n % 16:] = inf
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    got, found = _run(ds)
+    assert found == 0
+    err = np.abs(got.astype(np.float64) - _oracle(w)).max()
+    assert err <= ATTN_TOL["bf16"], err
