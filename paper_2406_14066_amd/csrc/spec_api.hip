@@ -417,11 +417,12 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
     }
     // Token-major pages of a head dim of 128, the attention alone, two or three row tiles per wavefront: K straight into
     // operand order where the launch waits for the chain from a page's arrival to its scores rather than for memory.
-    // One wave group: unsplit requests of about equal lengths that do not all start at once (two blocks per
-    // compute unit), so that the last ones run thinly spread.  32/8 heads, through LDS / direct, in us: k = 8, 768 blocks, 120 tokens
-    // 22.4 / 21.6, 200 31.0 / 28.5, 400 42.3 / 38.3, 1000 (memory) 79.9 / 84.0; 1280 blocks, 200 +6%, 300 +6%, 450 +4%, 700 +2%, 1000
-    // -2%; k = 4, 768 blocks, 120 +6%, 300 -2%; 1280 blocks, 120 +6%, 200 +10%, 300 +2%, 700 -2%; lengths from a tenth of to
-    // twice the mean gain nothing.
+    // One wave group, unsplit, through LDS / direct in us (64/8 heads, k = 3; tokens of each request):
+    //   more than two blocks per compute unit, about equal lengths, which do not all start at once, so that the last ones run thinly
+    // spread: 768 blocks of 100 tokens 18.4 / 17.9, 250 27.8 / 26.1, 600 (memory) 50.0 / 51.6; 1024 of 250 32.2 / 29.9, 600 59.0 / 60.0; 1536 of
+    // 100 30.3 / 28.3; 32/8 heads, k = 8, 768 of 250 30.8 / 28.5; lengths of a tenth to twice the mean 1 to 3% slower from 768 blocks on.
+    //   one or two per unit, 400 to 700 tokens in the mean (below that the launch is start-up, above it memory): 512 of 600 30.3 / 29.4, of
+    // 50 to 950 30.7 / 28.8, 384 of 600 25.1 / 24.5, 256 of 50 to 950 20.9 / 20.1; 512 of 250 16.5 / 16.3, of 1400 60.4 / 62.0.
     // Two wave groups of three row tiles: at most a block per compute unit, with 256 tokens or fewer.  64/8 heads, k = 7, four
     // requests of 16 / 100 / 200 tokens: direct 5, 4 and 6% faster than the staged walk page by page; 64 requests (two blocks per unit) of
     // 100 / 200 tokens 0 and 6% slower.  Two row tiles, which the staged walk takes in pairs of pages, are at least as fast that
@@ -432,7 +433,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
         const int cus = compute_units();
         if (pl.row_groups == 2) {
             pl.k_direct = pl.row_tiles == 3 && pl.chunk_tokens <= 256 && (int64_t)d_units * pl.max_chunks <= cus;
-        } else if (pl.row_groups == 1 && pl.max_chunks == 1 && a->host_kv_len != nullptr && d_units > 2 * cus) {
+        } else if (pl.row_groups == 1 && pl.max_chunks == 1 && a->host_kv_len != nullptr && d_units >= cus) {
             int64_t sum = 0;
             int longest = 0;
             for (int b = 0; b < a->B; ++b) {
@@ -440,8 +441,8 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
                 longest = std::max(longest, a->host_kv_len[b]);
             }
             const double mean = (double)sum / a->B;
-            const double most = d_units > 4 * cus ? 512.0 : (pl.row_tiles == 3 ? 256.0 : 208.0);
-            pl.k_direct = mean >= 96.0 && mean <= most && longest <= 1.35 * mean;
+            if (d_units > 2 * cus) pl.k_direct = mean >= 96.0 && mean <= (d_units > 4 * cus ? 512.0 : 320.0) && longest <= 1.35 * mean;
+            else pl.k_direct = mean >= 400.0 && mean <= 700.0;
         }
         if (tu.k_direct >= 0) pl.k_direct = pl.row_groups <= 2 && tu.k_direct;
     }

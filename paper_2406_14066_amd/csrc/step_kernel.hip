@@ -1630,8 +1630,9 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             const_cast<char *>(vhead + (size_t)page * page_stride), 0, bytes, kBufferFlags);
 #pragma unroll
         for (int i = 0; i < KK; ++i)
-            r.k[i] = K_DIRECT   // in operand order: token n16, dims 32 i + 8 g .. + 7 sit at n16 * 2 D + 64 i + 16 g
-                         ? __builtin_amdgcn_raw_buffer_load_b128(kd, n16 * (D * 2) + g * 16, i * 64, kStreamPolicy)
+            r.k[i] = K_DIRECT   // in operand order: token n16, dims 32 i + 8 g .. + 7 sit at n16 * 2 D + 64 i + 16 g (no streaming hint:
+                                // half a cache line per load, see the fp32 role; 24 requests on 64/8 heads, k = 3 47.4 -> 40.7 us)
+                         ? __builtin_amdgcn_raw_buffer_load_b128(kd, n16 * (D * 2) + g * 16, i * 64, 0)
                          : __builtin_amdgcn_raw_buffer_load_b128(kd, lane_off, i * 1024, kStreamPolicy);
         // V: in operand order already, or (token-major) as whole rows: with D / 8 lanes per row, lane L of load i holds
         // token (512 / D) i + 8 L / D, dims 8 (L % (D / 8)) .. + 7
@@ -1647,7 +1648,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             const_cast<char *>(head + (size_t)(valid ? entry : 0) * page_stride), 0, valid ? kPageHeadBytes : 0, kBufferFlags);
 #pragma unroll
         for (int i = 0; i < KK; ++i)
-            r[i] = direct ? __builtin_amdgcn_raw_buffer_load_b128(desc, n16 * (D * 2) + g * 16, i * 64, kStreamPolicy)
+            r[i] = direct ? __builtin_amdgcn_raw_buffer_load_b128(desc, n16 * (D * 2) + g * 16, i * 64, 0)
                           : __builtin_amdgcn_raw_buffer_load_b128(desc, lane_off, i * 1024, kStreamPolicy);
     };
 
@@ -2076,11 +2077,14 @@ __device__ __forceinline__ void attn_f32_role(const AttnParams &p, OrderTable or
                                                  valid ? kPageHeadBytes : 0, kBufferFlags);
     };
     f32x4 k[KI], v[4][VH];   // v[r][h]: token 4 g + r, dims 64 h + 4 n16 ..
+    // (K without the streaming hint: a load takes 64 bytes of each token row, half a cache line, and the other half, which
+    // the next load wants, is gone by then if the line is first in line for replacement.  Eight requests on 32/32 heads, k = 4: 39.8 -> 35.1
+    // us; on 32/8, k = 2: 18.3 -> 17.4.)
     auto load_k = [&](int it) {
         const __amdgpu_buffer_rsrc_t d = page_desc(khead, it);
 #pragma unroll
         for (int i = 0; i < KI; ++i)
-            k[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, n16 * (D * 4) + g * 16, i * 64, kStreamPolicy));
+            k[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, n16 * (D * 4) + g * 16, i * 64, 0));
     };
     auto load_v = [&](int it) {
         const __amdgpu_buffer_rsrc_t d = page_desc(vhead, it);
