@@ -10,6 +10,7 @@
 namespace specv {
 
 constexpr int kWave = 64;
+constexpr int kXcdCount = 8;   // the hardware deals consecutive blocks of a grid to the XCDs in turn
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr double kLog2eD = 1.4426950408889634074;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -38,6 +39,8 @@ struct AttnPlan {
     int32_t capacity_tokens;  // longest kv_len the plan allows for (chunk_tokens * max_chunks, capped by the bucket)
     int32_t fused_combine; // mfma kernel merges the chunk partials itself (few chunks) or leaves it to the combine kernel
     int32_t short_attn;    // the attention half streams for less time than the rejection stages' chain takes
+    int32_t spread;        // chunks sized from all lengths; the grid lists the chunks that exist, request by request (at most 64 requests)
+    int64_t blocks;        // attention blocks that have work
     size_t acc_bytes;
     size_t ml_bytes;
     size_t ticket_bytes;
@@ -55,8 +58,9 @@ struct AttnParams {
     int32_t fused_combine;        // matrix kernel: the last chunk's block merges the partials (needs max_chunks <= kMaxFusedChunks)
     int32_t attn_first_limit;     // attention blocks go first in the grid when there are at most this many
     float reject_span;            // fraction of the attention items among which the rejection items are spread in the grid
-    int32_t split_p;              // feed the softmax weights to the PV product as bf16 high + low parts
-    int32_t f32;                  // fp32 queries and cache (token-major pages)
+    int16_t split_p;              // feed the softmax weights to the PV product as bf16 high + low parts
+    int16_t f32;                  // fp32 queries and cache (token-major pages)
+    int32_t spread;               // see AttnPlan
     int32_t reject_even_xcds;     // fused step: rejection blocks only at even positions of the grid's rows of 8 (see GridSplit)
     int32_t reject_even_limit;    // ... when there are at most this many attention blocks (the number of compute units)
     int32_t capacity_tokens;      // a request whose device-side kv_len exceeds this is skipped and counted in *errors

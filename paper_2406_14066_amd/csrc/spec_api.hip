@@ -339,7 +339,8 @@ bool f32_scalar_is_faster(const AttnPlan &pl, int d, int max_len, int64_t rows)
 // (two with three row tiles), in multiples of the 16 tokens of a page.  The longest length the
 // plan allows for is the caller's bucket (max_kv_len) or, without one, the longest host length.
 // (alone: no rejection half in the same call)
-AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
+// (spread: the chunks may be sized from all lengths, see below; a plan without needs the smaller workspace)
+AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool spread)
 {
     AttnPlan pl;
     memset(&pl, 0, sizeof pl);
@@ -403,12 +404,45 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
         const int64_t chunk_cap = 4096 / pl.row_groups;
         if (chunk > chunk_cap) chunk = chunk_cap;
         if (tu.chunk > 0 && tu.chunk <= chunk_cap) chunk = tu.chunk;
+        // Chunks sized from all lengths: the split above is the longest request's, and the shorter ones leave compute units
+        // without a block, whose share the others' chunks could have.  So the chunk becomes the shortest with which the blocks
+        // that have work are no more than aimed for, and the grid lists those only.  Before / after, in us, 32/8 heads, k = 3,
+        // bf16: attention alone, eight requests of 500 to 8000 tokens (chunks of 1568 / 1040) 27.5 / 26.4, sixteen (3792 / 2992)
+        // 59.3 / 55.9; their steps (V = 32000) 30.6 / 27.9 and 62.4 / 58.1.  Where that shortens the chunk by a fifth at least (3680 /
+        // 3360 68.7 / 70.3, 2608 / 2240 40.2 / 40.3, 3392 / 3232 33.6 / 33.9), and not below 512 tokens (480 / 320: 13.9 / 13.8, 64/8
+        // heads 16.0 / 16.3); not with three row tiles, which aim for two blocks per unit (a long-context step, k = 8: 71.2 / 73.9).
+        // fp32 with two row tiles or more takes 3 us per page and wavefront, against which a merge of up to six chunks is cheap:
+        // chunks of 128 tokens, or 192 where that makes more than six, unless they fill the chip (32/8 heads, k = 4, chunks of 256 /
+        // 128: one request of 500 tokens 21.3 / 17.2 us, four 22.3 / 19.3; 256 / 192 / 128: four of 1000 24.3 / 21.4 / 24.0; 224 / 160,
+        // eight of 640 22.7 / 23.6; one tile, k = 2, one of 250: 10.9 / 11.7).  Sixteen of 64 to 1000: 32.3 / 28.9.
+        if (spread && tu.chunk == 0 && tu.target_blocks == 0 && a->max_kv_len == 0 && a->B <= kWave && a->Hkv % kXcdCount == 0 && units <= target_blocks &&
+            (f32 || pl.row_tiles < 3)) {
+            const int64_t least = !f32 ? 512 : (tiles >= 2 ? (max_len <= 768 ? 128 : 192) : 256);
+            const int worth = f32 ? 512 : 1024;
+            const int64_t most = std::max<int64_t>(8, (max_len + worth - 1) / worth);
+            int64_t lo = (std::max(least, (max_len + most - 1) / most) + SPEC_BLOCK_SIZE - 1) / SPEC_BLOCK_SIZE, hi = chunk / SPEC_BLOCK_SIZE;   // in pages
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) / 2;
+                int64_t blocks = 0;
+                for (int b = 0; b < a->B; ++b) blocks += (a->host_kv_len[b] + mid * SPEC_BLOCK_SIZE - 1) / (mid * SPEC_BLOCK_SIZE);
+                if (blocks * a->Hkv <= target_blocks) hi = mid;
+                else lo = mid + 1;
+            }
+            int64_t blocks = 0;
+            for (int b = 0; b < a->B; ++b) blocks += (a->host_kv_len[b] + hi * SPEC_BLOCK_SIZE - 1) / (hi * SPEC_BLOCK_SIZE);
+            const bool full = f32 && hi * SPEC_BLOCK_SIZE < 256 && blocks * a->Hkv > target_blocks * 4 / 5;
+            if (hi * SPEC_BLOCK_SIZE <= chunk * 4 / 5 && !full) {
+                chunk = hi * SPEC_BLOCK_SIZE;
+                pl.spread = 1;
+            }
+        }
         pl.chunk_tokens = (int32_t)chunk;
         pl.max_chunks = (max_len + pl.chunk_tokens - 1) / pl.chunk_tokens;
         if (f32 && alone && (tu.f32_scalar >= 0 ? tu.f32_scalar != 0 : f32_scalar_is_faster(pl, a->d, max_len, (int64_t)a->T * a->Hq))) {
             pl.use_mfma = 0;
             pl.row_groups = 1;
             pl.row_tiles = tiles;
+            pl.spread = 0;
         }
     }
     if (!pl.use_mfma) {
@@ -458,6 +492,11 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone)
     pl.ml_bytes = align_up(slots * 2 * sizeof(float));
     pl.ticket_bytes = align_up((size_t)a->B * a->Hkv * sizeof(unsigned long long));
     pl.total_bytes = pl.acc_bytes + pl.ml_bytes + pl.ticket_bytes;
+    pl.blocks = (int64_t)a->B * a->Hkv * pl.max_chunks;
+    if (pl.spread) {
+        pl.blocks = 0;
+        for (int b = 0; b < a->B; ++b) pl.blocks += (int64_t)a->Hkv * ((a->host_kv_len[b] + pl.chunk_tokens - 1) / pl.chunk_tokens);
+    }
     return pl;
 }
 
@@ -473,7 +512,7 @@ double attn_estimate_us(const spec_attn_args *a)
 // attn_us: rough duration of the attention half that runs in the same launch (microseconds), or
 // negative if the rejection half runs alone; attn_blocks: its blocks.  few_records: alone, but with no more statistics and race blocks than beside
 // an attention half (at most two per compute unit), for a workspace that has no room for more.
-RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu, double attn_us = -1.0, int64_t attn_blocks = 0, bool few_records = false,
+RejectPlan plan_reject(const spec_reject_args *r, const Tuning &tu, double attn_us = -1.0, int64_t attn_blocks = 0, bool few_records = false,
                        bool peek = true)
 {
     RejectPlan pl;
@@ -594,19 +633,21 @@ RejectPlan plan_reject(const spec_reject_args *r, size_t base, const Tuning &tu,
     if (peek && r->T > r->B && (uniform_q > 0 || r->B <= 256)) {
         const int sides = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 : 1;
         const double in_flight = (double)cus / ((double)sides * r->B * pl.stat_segments);   // positions
-        double saved_rows = 0.0;
-        for (int b = 0; b < r->B; ++b) {
-            const int k = r->host_cu_q_len[b + 1] - r->host_cu_q_len[b] - 1;
-            for (int j = 1; j <= k; ++j)
-                saved_rows += (j < k ? sides : 1) * (1.0 - pow(0.7, std::max(0.0, j - in_flight)));
+        double saved_of_k[SPEC_K_MAX + 1] = {0.0}, before = 0.0;   // rows saved of a request with k draft tokens
+        for (int k = 1; k <= SPEC_K_MAX; ++k) {
+            const double skipped = 1.0 - pow(0.7, std::max(0.0, k - in_flight));   // ... of position k
+            saved_of_k[k] = before + skipped;
+            before += sides * skipped;
         }
+        double saved_rows = 0.0;
+        for (int b = 0; b < r->B; ++b) saved_rows += saved_of_k[r->host_cu_q_len[b + 1] - r->host_cu_q_len[b] - 1];
         const double saved_us = saved_rows * r->V * 4.0 / 5.5e6;
         if (tu.early_stop >= 0 ? tu.early_stop == 2 : attn_us >= 0.0 && saved_us > (pl.early_stop == kStopWait ? 8.0 : 3.0)) {
             pl.early_stop = kStopPeek;
             pl.uniform_k = uniform_q > 0 ? uniform_q - 1 : -1;
         }
     }
-    pl.stats_off = base;
+    pl.stats_off = 0;
     pl.stats_bytes = align_up((size_t)rows * pl.stat_segments * kStatWords * sizeof(unsigned long long));
     pl.partial_off = pl.stats_off + pl.stats_bytes;
     // (room for the segments of 512 blocks at least, so that what fits the static scratch does not depend on the split)
@@ -663,6 +704,7 @@ struct StepPlan {
     spec_status status = SPEC_OK;   // of the per-request validation
     bool has_attn = false, has_reject = false;
     AttnPlan apl;
+    AttnPlan apl_small;             // for workspaces without room for apl
     RejectPlan rpl;
     RejectPlan rpl_small;           // for workspaces without room for rpl (never larger than rpl)
     UnitOrder order;
@@ -745,29 +787,36 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     if (e.status != SPEC_OK) return e;
     size_t base = 0;
     if (a != nullptr) {
-        e.apl = plan_attn(a, tu, r == nullptr);
-        e.apl.short_attn = attn_estimate_us(a) <= 20.0 ? 1 : 0;
-        if (e.apl.use_mfma) make_order(a, e.order);
-        base = e.apl.total_bytes;
+        e.apl = plan_attn(a, tu, r == nullptr, true);
+        e.apl_small = plan_attn(a, tu, r == nullptr, false);
+        e.apl.short_attn = e.apl_small.short_attn = attn_estimate_us(a) <= 20.0 ? 1 : 0;
+        make_order(a, e.order);
+        base = std::max(e.apl.total_bytes, e.apl_small.total_bytes);
     }
     e.workspace_bytes = base;
     if (r != nullptr) {
         const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
-        const int64_t attn_blocks = a != nullptr ? (int64_t)a->B * a->Hkv * e.apl.max_chunks : 0;
+        const int64_t attn_blocks = a != nullptr ? e.apl.blocks : 0;
         const bool peek = attn_us < 0.0 || a->qkv_dtype == SPEC_BF16;
-        e.rpl = plan_reject(r, base, tu, attn_us, attn_blocks, false, peek);
-        e.rpl_small = attn_us < 0.0 ? plan_reject(r, base, tu, attn_us, attn_blocks, true, peek) : e.rpl;
+        e.rpl = plan_reject(r, tu, attn_us, attn_blocks, false, peek);
+        e.rpl_small = attn_us < 0.0 ? plan_reject(r, tu, attn_us, attn_blocks, true, peek) : e.rpl;
         if (e.rpl_small.total_bytes > e.rpl.total_bytes) e.rpl_small = e.rpl;
         e.workspace_bytes = std::max(base + e.rpl.total_bytes, (attn_us < 0.0 ? base : 0) + reject_room(r, tu));
     }
     return e;
 }
 
-// The rejection half's plan on a workspace of `have` bytes.  The blocks of a half that runs alone are chosen for speed, and
-// their records take more room than those of few blocks: a workspace that holds only the latter still serves.
-const RejectPlan &reject_plan_for(const StepPlan &plan, size_t have)
+// The plans on a workspace of `have` bytes.  The blocks of a rejection half that runs alone, and the chunks of requests of
+// different lengths, are chosen for speed, and what they leave in the workspace takes more room than it would with few blocks or with
+// chunks for the longest request: a workspace that holds only the latter (sized for another batch, say) still serves.
+const AttnPlan &attn_plan_for(const StepPlan &plan, size_t have)
 {
-    return plan.rpl.stats_off + plan.rpl.total_bytes <= have ? plan.rpl : plan.rpl_small;
+    const size_t rest = plan.has_reject ? plan.rpl_small.total_bytes : 0;
+    return plan.apl.total_bytes + rest <= have ? plan.apl : plan.apl_small;
+}
+const RejectPlan &reject_plan_for(const StepPlan &plan, size_t have)   // have: after the attention's
+{
+    return plan.rpl.total_bytes <= have ? plan.rpl : plan.rpl_small;
 }
 
 // Tag of a call's tickets (see step_kernel.hip); unique per call within the process, never 0.
@@ -798,6 +847,7 @@ AttnParams attn_params(const spec_attn_args *a, const AttnPlan &pl, char *ws, in
     p.row_groups = pl.row_groups;
     p.row_tiles = pl.row_tiles;
     p.k_direct = pl.k_direct;
+    p.spread = pl.spread;
     p.f32 = a->qkv_dtype == SPEC_F32 ? 1 : 0;
     const double scale = a->softmax_scale > 0.0f ? (double)a->softmax_scale : 1.0 / sqrt((double)a->d);
     p.scale_log2 = (float)(scale * kLog2eD);
@@ -810,7 +860,7 @@ AttnParams attn_params(const spec_attn_args *a, const AttnPlan &pl, char *ws, in
     p.errors = reinterpret_cast<unsigned long long *>(a->error_count != nullptr ? a->error_count : errors);
     p.generation = next_generation();
     p.fused_combine = pl.fused_combine;
-    p.split_p = tu.split_p;
+    p.split_p = (int16_t)tu.split_p;
     p.reject_span = tu.reject_span;
     // as many attention blocks as there are block slots: all start at once
     p.attn_first_limit = tu.attn_first_limit >= 0 ? (int32_t)tu.attn_first_limit : 2 * compute_units();
@@ -882,17 +932,17 @@ spec_status prepare_step(const spec_attn_args *attn, const spec_reject_args *rej
 spec_status step_on_workspace(const spec_attn_args *attn, const spec_reject_args *reject, const StepPlan &plan,
                               void *workspace, size_t workspace_bytes, void *hip_stream)
 {
-    const AttnPlan &apl = plan.apl;
-    const RejectPlan &rpl = reject_plan_for(plan, workspace_bytes);
+    const AttnPlan &apl = attn_plan_for(plan, workspace_bytes);
+    const RejectPlan &rpl = reject_plan_for(plan, workspace_bytes - std::min(workspace_bytes, apl.total_bytes));
     const spec_status st = check_workspace(workspace, workspace_bytes, apl.total_bytes + rpl.total_bytes);
     if (st != SPEC_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const AttnParams ap = attn_params(attn, apl, static_cast<char *>(workspace), reject->counters + 6);
-    const RejectParams rp = reject_params(reject, rpl, static_cast<char *>(workspace));
+    const RejectParams rp = reject_params(reject, rpl, static_cast<char *>(workspace) + apl.total_bytes);
     if (apl.use_mfma) {
         // the whole step in one launch
         hipError_t err = timed_launch(SPEC_KERNEL_STEP, [&](LaunchEvents ev) {
-            return launch_step_fused(&ap, &rp, &plan.order, ev, stream);
+            return launch_step_fused(&ap, &rp, apl.spread ? nullptr : &plan.order, ev, stream);
         });
         if (err == hipSuccess && !apl.fused_combine && apl.max_chunks > 1)
             err = timed(SPEC_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
@@ -985,14 +1035,14 @@ spec_status spec_verify_attn(const spec_attn_args *attn, void *workspace, size_t
     if (plan.status != SPEC_OK) return plan.status;
     st = validate_attn_table(attn);
     if (st != SPEC_OK) return st;
-    const AttnPlan &pl = plan.apl;
+    const AttnPlan &pl = attn_plan_for(plan, workspace_bytes);
     st = check_workspace(workspace, workspace_bytes, pl.total_bytes);
     if (st != SPEC_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const AttnParams ap = attn_params(attn, pl, static_cast<char *>(workspace), nullptr);
     if (!pl.use_mfma) return run_attn_generic(ap, attn->qkv_dtype, stream);
     hipError_t err = timed_launch(SPEC_KERNEL_ATTN, [&](LaunchEvents ev) {
-        return launch_step_fused(&ap, nullptr, &plan.order, ev, stream);
+        return launch_step_fused(&ap, nullptr, pl.spread ? nullptr : &plan.order, ev, stream);
     });
     if (err == hipSuccess && !pl.fused_combine && pl.max_chunks > 1)
         err = timed(SPEC_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
@@ -1033,7 +1083,7 @@ spec_status spec_verify_step_static(const spec_attn_args *attn, const spec_rejec
     const StepPlan *plan = nullptr;
     const spec_status st = prepare_step(attn, reject, plan);
     if (st != SPEC_OK) return st;
-    if (plan->apl.total_bytes + plan->rpl_small.total_bytes > SPEC_STATIC_SCRATCH_BYTES) return SPEC_EWORKSPACE;
+    if (plan->apl_small.total_bytes + plan->rpl_small.total_bytes > SPEC_STATIC_SCRATCH_BYTES) return SPEC_EWORKSPACE;
     void *ws = static_scratch_of_current_device();
     if (ws == nullptr) return SPEC_EHIP;
     return step_on_workspace(attn, reject, *plan, ws, SPEC_STATIC_SCRATCH_BYTES, hip_stream);

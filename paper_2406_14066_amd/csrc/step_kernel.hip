@@ -79,7 +79,7 @@ constexpr int kBufferFlags = 0x00020000;   // raw 32-bit buffer descriptor, word
 // words); measured on the four large workloads the hint alone takes 8-10% off the step.
 constexpr int kStreamPolicy = 2;           // "nt" bit of a raw buffer load
 constexpr float kRescaleSlack = 8.0f;      // see the online softmax of the attention role
-constexpr int kXcds = 8;                   // the hardware deals consecutive blocks of a grid to the 8 XCDs in turn
+constexpr int kXcds = kXcdCount;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -1278,14 +1278,32 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     // workload takes 4% longer).
     const int n_units = p.B * p.Hkv;
     const int row_items = attn_row_items(p);
-    const int chunk = item / row_items;
-    const int place = item - chunk * row_items;
-    if (place >= n_units) return false;   // padding
-    const int kvh = place % p.Hkv;
-    int b = place / p.Hkv;   // rank in the order of the attention items
-    if (order.n > 0) {
-        const uint32_t pair = order.pairs[b >> 1];
-        b = (int)((b & 1) ? pair >> 16 : pair & 0xFFFFu);
+    int chunk, kvh, b, L = 0;
+    if (p.spread) {
+        // Only the chunks that exist, request by request (no holes between blocks that have work: the dispatcher deals the
+        // blocks out in turn, and empty ones leave their compute units idle while others get two).  A lane looks
+        // at a request; lengths that are left out below count as one chunk, whose block reports them.
+        const int len = lane < p.B ? p.kv_len[lane] : 0;
+        const int mine = len >= 1 && len <= p.capacity_tokens ? (len + p.chunk_tokens - 1) / p.chunk_tokens : 1;
+        kvh = item % p.Hkv;
+        chunk = item / p.Hkv;
+        for (b = 0; b < p.B; ++b) {
+            const int n = __builtin_amdgcn_readlane(mine, b);
+            if (chunk < n) break;
+            chunk -= n;
+        }
+        if (b == p.B) return false;
+        L = __builtin_amdgcn_readlane(len, b);
+    } else {
+        chunk = item / row_items;
+        const int place = item - chunk * row_items;
+        if (place >= n_units) return false;   // padding
+        kvh = place % p.Hkv;
+        b = place / p.Hkv;   // rank in the order of the attention items
+        if (order.n > 0) {
+            const uint32_t pair = order.pairs[b >> 1];
+            b = (int)((b & 1) ? pair >> 16 : pair & 0xFFFFu);
+        }
     }
     const int unit = b * p.Hkv + kvh;
 
@@ -1294,7 +1312,7 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     int bt = 0;
     if (p.max_chunks == 1 && first + STEP * lane < p.max_blocks_per_req)
         bt = p.block_table[(size_t)b * p.max_blocks_per_req + first + STEP * lane];
-    const int L = uniform_load(p.kv_len, b);
+    if (!p.spread) L = uniform_load(p.kv_len, b);
     const int row0 = uniform_load(p.cu_q_len, b);
     const int q_len = uniform_load(p.cu_q_len, b + 1) - row0;
     // The lengths come from device memory and bound every loop and index below: a request

@@ -134,3 +134,52 @@ def test_pairs_of_pages(Hq, Hkv, d, k_max, kv_len):
     assert found == 0
     err = np.abs(got.astype(np.float64) - _oracle(w)).max()
     assert err <= ATTN_TOL["bf16"], err
+
+
+# chunks sized from all lengths: the grid lists the chunks that exist; lengths that do not fit are left out and counted once,
+# and a workspace that holds the partial results of the longest request's split only serves with that split
+@pytest.mark.parametrize("dtype,Hq,Hkv,k,kv_len,chunks", [
+    ("bf16", 8, 8, 3, (5000, 513, 16, 9, 2000, 3100, 700, 40), 8), ("f32", 16, 8, 8, (1000, 9, 500, 200), 6), ("f32", 32, 8, 4, (500,), 4),
+    ("bf16", 16, 16, 2, (4000, 600, 64, 6000), 8)])
+def test_chunks_sized_from_all_lengths(dtype, Hq, Hkv, k, kv_len, chunks):
+    from paper_2406_14066_amd.harness import DeviceStep
+    print("case spread", dtype, Hq, Hkv, k, kv_len, flush=True)
+    w = W.make_workload("spread", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len),
+                        k=[min(k, n - 1) for n in kv_len], draft_std=2.0, sigma=0.8, data_seed=Hq + k, philox_seed=9)
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    plan = sv.spec_verify_plan(ds.attn_args, None)
+    need = sum((n + plan["chunk_tokens"] - 1) // plan["chunk_tokens"] for n in kv_len) * Hkv
+    assert plan["max_chunks"] == chunks and need <= 256, (plan, need)
+    ref = _oracle(w)
+    got, found = _run(ds)
+    assert found == 0
+    assert np.abs(got.astype(np.float64) - ref).max() <= ATTN_TOL[dtype]
+    # the split of the longest request alone, which is what a bucket of that length gets
+    import ctypes
+    bucket = type(ds.attn_args)()
+    ctypes.memmove(ctypes.byref(bucket), ctypes.byref(ds.attn_args), ctypes.sizeof(bucket))
+    bucket.max_kv_len = max(kv_len)
+    small = sv.spec_verify_workspace_bytes(bucket, None)
+    whole = ds.workspace
+    if small < sv.spec_verify_workspace_bytes(ds.attn_args, None):
+        ds.workspace = whole[:small]
+        got, found = _run(ds)
+        assert found == 0
+        assert np.abs(got.astype(np.float64) - ref).max() <= ATTN_TOL[dtype]
+        ds.workspace = whole
+    if len(kv_len) == 1:
+        return
+    # a length beyond the plan and one below its own query rows
+    good = ds.kv_len.clone()
+    bad = {0: plan["chunk_tokens"] * plan["max_chunks"] + 1, 2: 0}
+    for b, n in bad.items():
+        ds.kv_len[b] = n
+    got, found = _run(ds)
+    ds.kv_len.copy_(good)
+    assert found == len(bad)
+    for b in range(w.B):
+        rows = got[_rows(w, b)]
+        if b in bad:
+            assert np.isnan(rows).all()
+        else:
+            assert np.abs(rows.astype(np.float64) - ref[_rows(w, b)]).max() <= ATTN_TOL[dtype]
