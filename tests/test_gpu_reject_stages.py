@@ -115,7 +115,7 @@ def test_early_stop_that_looks_at_earlier_positions(harness, tuning, B, V, unifo
         w.draft_tokens = np.where(hit, w.target_logits[rows].argmax(1), w.draft_tokens).astype(np.int32)
     tuning("SPEC_VERIFY_EARLY_STOP", 2)
     ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=mode)
-    assert ds.plan()["early_stop"] == (1 if w.T > B and (uniform or B <= 256) else 0)
+    assert sv.spec_verify_plan(None, ds.reject_args)["early_stop"] == (1 if w.T > B and (uniform or B <= 256) else 0)
     for _ in range(2):   # the second call finds the first one's records cleared or out of date
         ds.counters.zero_()
         ds.out_tokens.fill_(-7)
