@@ -797,7 +797,7 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     if (r != nullptr) {
         const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
         const int64_t attn_blocks = a != nullptr ? e.apl.blocks : 0;
-        const bool peek = attn_us < 0.0 || a->qkv_dtype == SPEC_BF16;
+        const bool peek = attn_us >= 0.0 && a->qkv_dtype == SPEC_BF16;
         e.rpl = plan_reject(r, tu, attn_us, attn_blocks, false, peek);
         e.rpl_small = attn_us < 0.0 ? plan_reject(r, tu, attn_us, attn_blocks, true, peek) : e.rpl;
         if (e.rpl_small.total_bytes > e.rpl.total_bytes) e.rpl_small = e.rpl;

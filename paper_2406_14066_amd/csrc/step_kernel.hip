@@ -253,7 +253,9 @@ constexpr float kLog2eLo = 1.9259629911266175e-8f;  // log2 e - kLog2eHi
 struct RejectShared {
     float red_f[kWaves];
     double red_d[kWaves];
-    double lse2[2 * SPEC_K_MAX + 1];  // log2-sum-exp: target rows 0..k, then draft rows 0..k-1
+    // target rows 0..k, then draft rows 0..k-1: sum_v 2^(x_v * log2(e) - row_off), row_off a whole number
+    double row_sum[2 * SPEC_K_MAX + 1];
+    float row_off[2 * SPEC_K_MAX + 1];
     double u[SPEC_K_MAX], ratio[SPEC_K_MAX];
     int accept[SPEC_K_MAX];
     int m, near;
@@ -476,8 +478,8 @@ struct RaceRows {
 // One part (vectors g0 .. of [g0, g_end)): the thread's best (score, id) so far is carried along.
 // drow == nullptr: weights are the target probabilities (bonus token), with `exclude` left out (point-mass
 // draft: the rejected token; -1: none); otherwise the positive part of p - q.
-//   p_v = corr_t * 2^(x_v * log2e + off_t), off_t = fp32(-log2-sum-exp), corr_t the
-//   factor lost by rounding off_t.  Ties keep the lowest id; weights <= 0 never win.
+//   p_v = corr_t * 2^(x_v * log2e + off_t), off_t = -(the row's offset, a whole number), corr_t =
+//   1 / (its sum).  Ties keep the lowest id; weights <= 0 never win.
 __device__ __forceinline__ void race_part(const RaceRows &rr, int g0, int g_end, const RejectShared &sh, float &best_score, int &best_id)
 {
     // The loads run kRaceDepth vectors ahead.  Descriptors end with the part (past it the loads read zeros
@@ -545,7 +547,9 @@ __device__ __forceinline__ void race_winner(float &best_score, int &best_id, Rej
 
 // Bounded wait until `ready` holds for every thread of the block (block-wide AND).
 // `probe` re-evaluates the condition; returns false if the limit ran out.
-template <typename F>
+// FEW: few blocks wait like this (the final stage's, at the very end), so that their polls cost the streams nothing: naps stay short
+// (rejection alone, one request 12.7 -> 12.2 us, 32 at k = 4 19.4 -> 18.9; the smallest fp32 step 12.7 -> 12.1).
+template <bool FEW = false, typename F>
 __device__ __forceinline__ bool wait_all(const RejectParams &p, F probe)
 {
     for (int spin = 0; spin < p.spin_limit; ++spin) {
@@ -554,7 +558,7 @@ __device__ __forceinline__ bool wait_all(const RejectParams &p, F probe)
         // short naps first.  In a large one many blocks wait at once and their polls compete with the
         // streams (short naps there: the 7B- and 70B-shaped steps 0.5 to 0.8% slower).
         if (p.short_naps && spin < 4) __builtin_amdgcn_s_sleep(2);
-        else if (p.short_naps && spin < 8) __builtin_amdgcn_s_sleep(8);
+        else if (FEW || (p.short_naps && spin < 8)) __builtin_amdgcn_s_sleep(8);
         else __builtin_amdgcn_s_sleep(32);
     }
     return false;
@@ -563,7 +567,7 @@ __device__ __forceinline__ bool wait_all(const RejectParams &p, F probe)
 // Accept chain of request b from the published row statistics.  Cheap (a few
 // hundred loads and fp64 operations), so every block that needs its result just
 // recomputes it.  Waits (bounded) until all of the request's statistics carry this
-// call's tag.  Leaves log2-sum-exp per row in sh.lse2, m in sh.m, the near-tie count
+// call's tag.  Leaves the rows' offsets and sums in sh.row_off and sh.row_sum, m in sh.m, the near-tie count
 // in sh.near.  Returns false if the statistics never arrived.
 __device__ __forceinline__ bool accept_phase(const RejectParams &p, int b, RejectShared &sh, bool write_debug, int npos = -1)
 {
@@ -624,15 +628,21 @@ __device__ __forceinline__ bool accept_phase(const RejectParams &p, int b, Rejec
             // instead of a call in a chain of as many calls as there are segments (this, the series below and the
             // uniforms drawn before the wait: tiny fp32 step 13.05 -> 12.64 us, 48 requests of V = 128256 alone 47.2 -> 46.4)
             total += ldexp(sh.seg_sum[tid][sg], (int)fmaxf(sh.seg_off[tid][sg] - mx, -4000.0f));
-        sh.lse2[tid] = (double)mx + log2(total);
+        sh.row_sum[tid] = total;
+        sh.row_off[tid] = mx;
     }
     __syncthreads();
 
     // accept tests, all evaluated in parallel; the chain is resolved below
     if (tid < npos_eval) {
-        const double log2_p = (double)tx * kLog2eD - sh.lse2[tid];
-        const double log2_q = has_draft_rows ? (double)dx * kLog2eD - sh.lse2[k + 1 + tid] : 0.0;   // point mass: q(x) = 1
-        const double ratio = exp2(log2_p - log2_q);  // p = 0 -> 0, q = 0 < p -> inf, both 0 -> NaN (rejects)
+        // p/q = 2^(difference of the exponents) * (ratio of the sums): no logarithm in the chain (rejection alone, 48 requests,
+        // V = 128256 46.5 -> 46.0 us; 128 at k = 3, V = 4096 17.0 -> 16.4)
+        double e = (double)tx * kLog2eD - (double)sh.row_off[tid], ratio = 1.0 / sh.row_sum[tid];
+        if (has_draft_rows) {   // (a point mass: q(x) = 1)
+            e -= (double)dx * kLog2eD - (double)sh.row_off[k + 1 + tid];
+            ratio = sh.row_sum[k + 1 + tid] / sh.row_sum[tid];
+        }
+        ratio *= exp2(e);   // p = 0 -> 0, q = 0 < p -> inf, both 0 -> NaN (rejects)
         sh.u[tid] = u;
         sh.ratio[tid] = ratio;
         sh.accept[tid] = (u < ratio) ? 1 : 0;
@@ -924,14 +934,6 @@ __device__ __forceinline__ void stats_role(const RejectParams &p, int item, Reje
     stats_block<DEPTH>(p, row, seg, sh);
 }
 
-// 2^d in fp32 for what rounding an offset to fp32 lost (a few 1e-6 for any ordinary offset: three terms are exact).
-__device__ __forceinline__ float pow2_of_residue(double d)
-{
-    const double x = d * 0.6931471805599453094;
-    if (fabs(x) < 1e-4) return (float)(1.0 + x * (1.0 + 0.5 * x));
-    return (float)exp2(d);
-}
-
 __device__ __forceinline__ RaceRows race_rows(const RejectParams &p, int b, const RejectShared &sh)
 {
     RaceRows rr;
@@ -939,9 +941,8 @@ __device__ __forceinline__ RaceRows race_rows(const RejectParams &p, int b, cons
     const int k = uniform_load(p.cu_q_len, b + 1) - row_t0 - 1;
     const int row_d0 = row_t0 - b;
     rr.m = sh.m;
-    const double off_t_exact = -sh.lse2[rr.m];
-    rr.off_t = (float)off_t_exact;
-    rr.corr_t = pow2_of_residue(off_t_exact - (double)rr.off_t);
+    rr.off_t = -sh.row_off[rr.m];
+    rr.corr_t = (float)(1.0 / sh.row_sum[rr.m]);
     rr.off_d = 0.0f;
     rr.corr_d = 0.0f;
     rr.trow = p.target_logits + (size_t)(row_t0 + rr.m) * p.V;
@@ -949,9 +950,8 @@ __device__ __forceinline__ RaceRows race_rows(const RejectParams &p, int b, cons
     rr.exclude = -1;
     if (rr.m < k && p.mode == SPEC_ACCEPT_POINT_DRAFT) rr.exclude = p.draft_tokens[row_d0 + rr.m];
     if (rr.m < k && p.mode == SPEC_ACCEPT_SAMPLE) {
-        const double off_d_exact = -sh.lse2[k + 1 + rr.m];
-        rr.off_d = (float)off_d_exact;
-        rr.corr_d = pow2_of_residue(off_d_exact - (double)rr.off_d);
+        rr.off_d = -sh.row_off[k + 1 + rr.m];
+        rr.corr_d = (float)(1.0 / sh.row_sum[k + 1 + rr.m]);
         rr.drow = p.draft_logits + (size_t)(row_d0 + rr.m) * p.V;
     }
     return rr;
@@ -1033,7 +1033,7 @@ __device__ __forceinline__ void final_role(const RejectParams &p, int item, Reje
     float *rec_value = &sh.seg_off[0][0] + local * (SPEC_K_MAX + 1) * segs;   // (2^final_shift * segs <= kMaxStatSegments)
     double *rec_id = &sh.seg_sum[0][0] + local * (SPEC_K_MAX + 1) * segs;
     bool mine = true;
-    const bool ok = wait_all(p, [&] {
+    const bool ok = wait_all<true>(p, [&] {
         mine = true;
         if (!valid) return true;
         if (greedy) {
@@ -1128,25 +1128,28 @@ __device__ __forceinline__ void final_role(const RejectParams &p, int item, Reje
         }
     }
 
+    // the counters' sums first: a barrier after the outputs would wait for their stores
     const bool ready = sh.fin_ready[local] != 0;
+    if (valid && ready && li <= SPEC_K_MAX) {
+        if (li < k && (unsigned)token >= (unsigned)p.V) atomicAdd(&sh.fin_count[1], 1u << 8);   // an input error
+        if (li == 0) {   // four sums of at most 16 * 8 in one word
+            atomicAdd(&sh.fin_count[0], (uint32_t)k | (uint32_t)m << 8 | (uint32_t)(m + 1 < k ? m + 1 : k) << 16 | (uint32_t)near << 24);
+            atomicAdd(&sh.fin_count[1], 1u);
+        }
+    }
+    __syncthreads();
     if (valid && li <= SPEC_K_MAX) {
         if (p.out_tokens != nullptr)
             p.out_tokens[(size_t)b * (SPEC_K_MAX + 1) + li] = !ready ? -1 : (li < m ? token : (li == m ? win_id : -1));
-        if (ready && li < k && (unsigned)token >= (unsigned)p.V) atomicAdd(&sh.fin_count[1], 1u << 8);   // an input error
         if (li == 0) {
             p.accepted_len[b] = ready ? m : -1;
             p.next_token[b] = ready ? win_id : -1;
             if (p.new_kv_len != nullptr) p.new_kv_len[b] = ready ? kv_len - (k - m) : -1;
             if (p.draft_next_len != nullptr) p.draft_next_len[b] = !ready ? -1 : ((k > 0 && m == k) ? 2 : 1);
-            if (ready) {   // four sums of at most 16 * 8 in one word
-                atomicAdd(&sh.fin_count[0], (uint32_t)k | (uint32_t)m << 8 | (uint32_t)(m + 1 < k ? m + 1 : k) << 16 | (uint32_t)near << 24);
-                atomicAdd(&sh.fin_count[1], 1u);
-            } else {       // a wait ran out (never in a healthy launch): the request is counted here only
-                atomicAdd(&p.counters[7], 1ull);
-            }
+            // a wait ran out (never in a healthy launch): the request is counted here only
+            if (!ready) atomicAdd(&p.counters[7], 1ull);
         }
     }
-    __syncthreads();
     if (tid < 7) {
         const uint32_t sums = sh.fin_count[0], n = sh.fin_count[1] & 0xFFu;
         uint32_t add = tid == 5 ? n : sh.fin_count[1] >> 8;
@@ -2325,8 +2328,8 @@ __device__ __forceinline__ bool grid_item(const GridSplit &gs, int &item, bool &
     return true;
 }
 
-// (PEEK: the kernel knows kStopPeek.  The fp32 kernel does not: its code beside the stages costs the smallest steps
-// 0.9 of 12.7 us.)
+// (PEEK: the kernel knows kStopPeek.  The fp32 kernel and the rejection half's do not: all code beside the stages costs the smallest
+// launches, this one 0.9 of the smallest fp32 step's 12.7 us.)
 template <int DEPTH, bool PEEK>
 __device__ __forceinline__ void reject_item(const RejectParams &p, int n_stat, int item, RejectShared &sh)
 {
@@ -2372,7 +2375,7 @@ __global__ __launch_bounds__(kThreads, (kMinBlocks<NT, HAS_ATTN, VAR>)) void spe
     if constexpr (HAS_REJECT) {
         if (!is_attn) {
             // a whole 32000-entry row per round trip where the registers allow it
-            reject_item<(HAS_ATTN && NT >= 2) ? 8 : 4, true>(rp, args.gs.n_stat, item, *reinterpret_cast<RejectShared *>(shared));
+            reject_item<(HAS_ATTN && NT >= 2) ? 8 : 4, HAS_ATTN>(rp, args.gs.n_stat, item, *reinterpret_cast<RejectShared *>(shared));
             return;
         }
     }

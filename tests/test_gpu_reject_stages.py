@@ -108,18 +108,19 @@ def test_requests_grouped_in_the_final_stage(harness, B, mode):
 def test_early_stop_that_looks_at_earlier_positions(harness, tuning, B, V, uniform, mode):
     print("case look", B, V, uniform, mode, flush=True)
     rng = np.random.default_rng(B + V)
-    w = _logits_only(B, V, [6] * B if uniform else rng.integers(0, 9, size=B), seed=B)
+    w = W.make_workload("look", B=B, Hq=1, Hkv=1, d=64, V=V, dtype="bf16", kv_len=[16] * B, k=[6] * B if uniform else rng.integers(0, 9, size=B),
+                        draft_std=3.0, sigma=0.8, data_seed=B, philox_seed=99 + B)
     if mode == sv.ACCEPT_GREEDY:
         hit = rng.random(w.T - B) < 0.7
         rows = np.concatenate([np.arange(w.cu_q_len[b], w.cu_q_len[b + 1] - 1) for b in range(B)])
         w.draft_tokens = np.where(hit, w.target_logits[rows].argmax(1), w.draft_tokens).astype(np.int32)
     tuning("SPEC_VERIFY_EARLY_STOP", 2)
     ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=mode)
-    assert sv.spec_verify_plan(None, ds.reject_args)["early_stop"] == (1 if w.T > B and (uniform or B <= 256) else 0)
+    assert ds.plan()["early_stop"] == (1 if w.T > B and (uniform or B <= 256) else 0)
     for _ in range(2):   # the second call finds the first one's records cleared or out of date
         ds.counters.zero_()
         ds.out_tokens.fill_(-7)
-        ds.run_reject()
+        ds.run_step()
         res = ds.results()
         if mode == sv.ACCEPT_GREEDY:
             ref = oracle.reject_greedy(w.target_logits, w.draft_tokens, w.cu_q_len)
