@@ -627,7 +627,7 @@ RejectPlan plan_reject(const spec_reject_args *r, const Tuning &tu, double attn_
     // and races that start later.  All rows read or waiting as chosen above / looking, in us: 64/8 heads, token-major, B=96 k=7 99 / 87,
     // tiles, B=48 k=8 88.4 / 80.9; 32/8 heads, B=86 k=7 L=1326 126 / 112; 64/4 heads, B=65 k=8 L=690 117 / 107; drafts of 1..k: 64/8
     // heads, B=200 k=3 93.7 / 90.0, B=64 k=5 (nothing is saved) 49.9 / 52.8.  Over 138 steps (24 to 256 requests, all modes, rates of
-    // 0.5, 0.7 and 0.9) the rule takes a sixth of them, 15% faster to 5% slower, 5% faster in the mean.  Not where the
+    // 0.5, 0.7 and 0.9) the rule takes a sixth of them, 15% faster to 5% slower.  Not where the
     // rejection half runs alone: its blocks fill the chip at once (four per unit) and start together; 120 such calls -7 to +29%.
     // (peek: the kernel that takes the launch can.)
     if (peek && r->T > r->B && (uniform_q > 0 || r->B <= 256)) {
@@ -642,7 +642,10 @@ RejectPlan plan_reject(const spec_reject_args *r, const Tuning &tu, double attn_
         double saved_rows = 0.0;
         for (int b = 0; b < r->B; ++b) saved_rows += saved_of_k[r->host_cu_q_len[b + 1] - r->host_cu_q_len[b] - 1];
         const double saved_us = saved_rows * r->V * 4.0 / 5.5e6;
-        if (tu.early_stop >= 0 ? tu.early_stop == 2 : attn_us >= 0.0 && saved_us > (pl.early_stop == kStopWait ? 8.0 : 3.0)) {
+        // (a row's segment has to be worth the look at it, and the search for the item where draft lengths differ: V = 8016, drafts of
+        // 1..8, 64/4 heads, B=255 65.8 / 72.3; V = 4736, k = 7, 32/8 heads of 64, B=194 52.8 / 55.2; V = 13792, k = 7, B=123 42.8 / 40.2)
+        const bool long_enough = pl.stat_seg_len >= (uniform_q > 0 ? 8192 : 16384);
+        if (tu.early_stop >= 0 ? tu.early_stop == 2 : attn_us >= 0.0 && long_enough && saved_us > (pl.early_stop == kStopWait ? 8.0 : 3.0)) {
             pl.early_stop = kStopPeek;
             pl.uniform_k = uniform_q > 0 ? uniform_q - 1 : -1;
         }

@@ -53,8 +53,8 @@ def test_few_race_blocks_beside_a_long_attention_half(B, k, length, V, segments)
 
 # beside an attention half, long drafts and draft lengths of their own stop early where that saves enough rows; not alone, nor
 # with draft lengths of more requests than a block has threads
-@pytest.mark.parametrize("B,k,length,V,ragged,stops", [(96, 7, 640, 32000, False, 1), (200, 3, 400, 32000, True, 1), (256, 8, 200, 8192, True, 1),
-                                                       (257, 8, 200, 8192, True, 0), (64, 5, 580, 32000, True, 0), (8, 4, 2048, 32000, False, 0)])
+@pytest.mark.parametrize("B,k,length,V,ragged,stops", [(96, 7, 640, 32000, False, 1), (200, 3, 400, 32000, True, 1), (256, 8, 200, 17000, True, 1), (255, 8, 52, 8016, True, 0),
+                                                       (257, 8, 200, 17000, True, 0), (64, 5, 580, 32000, True, 0), (8, 4, 2048, 32000, False, 0)])
 def test_early_stop_beside_an_attention_half(B, k, length, V, ragged, stops):
     q_len = [1 + (1 + b % k) for b in range(B)] if ragged else None
     r = reject_args(B, k, V, q_len=q_len)
