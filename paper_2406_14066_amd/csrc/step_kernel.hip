@@ -1361,11 +1361,88 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     return true;
 }
 
+// The merge of a request's chunks, in chunk order: half a wavefront takes RB query rows at a time (four head dims per lane) and
+// GROUP chunks of each per pass.
+template <int GROUP, int RB, int D>
+__device__ __forceinline__ void merge_chunks(const AttnParams &p, const AttnWork &w)
+{
+    const int lane = w.lane, wave = w.wave, rows = w.rows, group = w.group, row0 = w.row0, kvh = w.kvh, nchunks = w.nchunks;
+    const int half = lane >> 5, l32 = lane & 31;
+    const bool dims_on = 4 * l32 < D;   // (a head dim of 64 keeps half of the lanes busy)
+    for (int r0 = 2 * wave + half; r0 < rows; r0 += 2 * kWaves * RB) {
+        bool rv[RB];
+        size_t rh[RB];
+        const unsigned long long *ml[RB], *pa[RB];
+        float mx[RB], denom[RB];
+        f32x4 o[RB];
+#pragma unroll
+        for (int j = 0; j < RB; ++j) {
+            const int r = r0 + 2 * kWaves * j;
+            rv[j] = r < rows;
+            const int rr = rv[j] ? r : 0;
+            rh[j] = (size_t)(row0 + rr / group) * p.Hq + kvh * group + rr % group;
+            const size_t base = rh[j] * p.max_chunks;
+            ml[j] = reinterpret_cast<const unsigned long long *>(p.ws_ml) + base;
+            pa[j] = reinterpret_cast<const unsigned long long *>(p.ws_acc) + base * (D / 2) + 2 * (l32 % (D / 4));
+            mx[j] = kEmptyMax;
+            denom[j] = 0.0f;
+            o[j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        for (int c0 = 0; c0 < nchunks; c0 += GROUP) {
+            unsigned long long mlv[RB][GROUP], a0[RB][GROUP], a1[RB][GROUP];
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+#pragma unroll
+                for (int c = 0; c < GROUP; ++c) {
+                    const unsigned long long *al = pa[j] + (size_t)(c0 + c) * (D / 2);
+                    if constexpr (RB == 1 || D < 4 * 32) {
+                        mlv[j][c] = pack_f32x2(kEmptyMax, 0.0f);
+                        a0[j][c] = a1[j][c] = 0ull;
+                        // the same for the whole wavefront: one branch for the three
+                        if (c0 + c < nchunks && (RB == 1 || __builtin_amdgcn_readfirstlane(r0) + 2 * kWaves * j < rows)) {
+                            mlv[j][c] = fetch_u64(ml[j] + c0 + c);
+                            a0[j][c] = fetch_u64(al);
+                            a1[j][c] = fetch_u64(al + 1);
+                        }
+                    } else {
+                        const bool on = rv[j] && c0 + c < nchunks;
+                        mlv[j][c] = on ? fetch_u64(ml[j] + c0 + c) : pack_f32x2(kEmptyMax, 0.0f);
+                        a0[j][c] = on ? fetch_u64(al) : 0ull;
+                        a1[j][c] = on ? fetch_u64(al + 1) : 0ull;
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < RB; ++j) {
+                float gmx = mx[j];
+#pragma unroll
+                for (int c = 0; c < GROUP; ++c) gmx = fmaxf(gmx, __uint_as_float((uint32_t)mlv[j][c]));
+                const float keep = fast_exp2(mx[j] - gmx);   // rescale of what earlier passes summed
+                denom[j] *= keep;
+                o[j] *= keep;
+                mx[j] = gmx;
+#pragma unroll
+                for (int c = 0; c < GROUP; ++c) {
+                    const float w = fast_exp2(__uint_as_float((uint32_t)mlv[j][c]) - gmx);
+                    denom[j] = fmaf(w, __uint_as_float((uint32_t)(mlv[j][c] >> 32)), denom[j]);
+                    o[j][0] = fmaf(w, __uint_as_float((uint32_t)a0[j][c]), o[j][0]);
+                    o[j][1] = fmaf(w, __uint_as_float((uint32_t)(a0[j][c] >> 32)), o[j][1]);
+                    o[j][2] = fmaf(w, __uint_as_float((uint32_t)a1[j][c]), o[j][2]);
+                    o[j][3] = fmaf(w, __uint_as_float((uint32_t)(a1[j][c] >> 32)), o[j][3]);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < RB; ++j)
+            if (rv[j] && dims_on) *reinterpret_cast<f32x4 *>(p.out + rh[j] * D + 4 * l32) = o[j] * (1.0f / denom[j]);
+    }
+}
+
 // The end of an attention block: merges its wavefronts, and writes the output rows (a request that is not
 // split) or publishes the chunk's partial results and, as the last chunk to finish, merges all of them.
 // acc[nt][mt] holds, per lane, four consecutive head dims of query row n16 of tile nt, the first of which
 // is dim_base(mt, g).
-template <int NT, int WG, int D, typename Shared, typename DimBase>
+template <int NT, int WG, int D, bool FEW_CHUNKS, typename Shared, typename DimBase>
 __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w, f32x4 (&acc)[NT][D / 16], float (&m_run)[NT],
                                          float (&l_run)[NT], const int (&out_row)[NT], DimBase dim_base, Shared &sh)
 {
@@ -1497,77 +1574,18 @@ __device__ __forceinline__ void attn_end(const AttnParams &p, const AttnWork &w,
     // 64/8 heads of 128, k = 1, two chunks: 10.94 -> 10.75 us; 16 on 32/8 heads of 64, k = 8: 15.8 -> 14.7.  With two
     // rows in flight of 128 dims, where those loads are too many, it costs 2%: 75.1 / 77.3 us for four of 6000
     // tokens on 64/4 heads, k = 8.)
+    // FEW_CHUNKS: with four chunks or fewer, half as many chunks and twice as many rows per pass, so that 17 to 32 rows take one
+    // pass (attention alone, 64/8 heads, k = 7, one request of 1000 tokens 19.5 -> 18.5 us; fp32, 32/8 heads, k = 4, four of 500 19.5 -> 19.0, eight
+    // of 256 to 1024 24.45 -> 24.0).  For two row tiles of 128 dims in wave groups or fp32 only: three tiles spill.
+    if constexpr (FEW_CHUNKS && NT == 2 && D == 128) {
+        if (nchunks <= 4) {
+            merge_chunks<4, 4, D>(p, w);
+            return;
+        }
+    }
     constexpr int GROUP = 8;   // chunks merged per pass (16 per pass spill 200 to 340 bytes per lane)
     constexpr int RB = NT >= 2 ? 2 : 1;   // rows in flight per half wavefront (one row tile: at most two passes anyway, and registers are tight)
-    const int half = lane >> 5, l32 = lane & 31;
-    const bool dims_on = 4 * l32 < D;   // (a head dim of 64 keeps half of the lanes busy)
-    for (int r0 = 2 * wave + half; r0 < rows; r0 += 2 * kWaves * RB) {
-        bool rv[RB];
-        size_t rh[RB];
-        const unsigned long long *ml[RB], *pa[RB];
-        float mx[RB], denom[RB];
-        f32x4 o[RB];
-#pragma unroll
-        for (int j = 0; j < RB; ++j) {
-            const int r = r0 + 2 * kWaves * j;
-            rv[j] = r < rows;
-            const int rr = rv[j] ? r : 0;
-            rh[j] = (size_t)(row0 + rr / group) * p.Hq + kvh * group + rr % group;
-            const size_t base = rh[j] * p.max_chunks;
-            ml[j] = reinterpret_cast<const unsigned long long *>(p.ws_ml) + base;
-            pa[j] = reinterpret_cast<const unsigned long long *>(p.ws_acc) + base * (D / 2) + 2 * (l32 % (D / 4));
-            mx[j] = kEmptyMax;
-            denom[j] = 0.0f;
-            o[j] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        for (int c0 = 0; c0 < nchunks; c0 += GROUP) {
-            unsigned long long mlv[RB][GROUP], a0[RB][GROUP], a1[RB][GROUP];
-#pragma unroll
-            for (int j = 0; j < RB; ++j) {
-#pragma unroll
-                for (int c = 0; c < GROUP; ++c) {
-                    const unsigned long long *al = pa[j] + (size_t)(c0 + c) * (D / 2);
-                    if constexpr (RB == 1 || D < 4 * 32) {
-                        mlv[j][c] = pack_f32x2(kEmptyMax, 0.0f);
-                        a0[j][c] = a1[j][c] = 0ull;
-                        // the same for the whole wavefront: one branch for the three
-                        if (c0 + c < nchunks && (RB == 1 || __builtin_amdgcn_readfirstlane(r0) + 2 * kWaves * j < rows)) {
-                            mlv[j][c] = fetch_u64(ml[j] + c0 + c);
-                            a0[j][c] = fetch_u64(al);
-                            a1[j][c] = fetch_u64(al + 1);
-                        }
-                    } else {
-                        const bool on = rv[j] && c0 + c < nchunks;
-                        mlv[j][c] = on ? fetch_u64(ml[j] + c0 + c) : pack_f32x2(kEmptyMax, 0.0f);
-                        a0[j][c] = on ? fetch_u64(al) : 0ull;
-                        a1[j][c] = on ? fetch_u64(al + 1) : 0ull;
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < RB; ++j) {
-                float gmx = mx[j];
-#pragma unroll
-                for (int c = 0; c < GROUP; ++c) gmx = fmaxf(gmx, __uint_as_float((uint32_t)mlv[j][c]));
-                const float keep = fast_exp2(mx[j] - gmx);   // rescale of what earlier passes summed
-                denom[j] *= keep;
-                o[j] *= keep;
-                mx[j] = gmx;
-#pragma unroll
-                for (int c = 0; c < GROUP; ++c) {
-                    const float w = fast_exp2(__uint_as_float((uint32_t)mlv[j][c]) - gmx);
-                    denom[j] = fmaf(w, __uint_as_float((uint32_t)(mlv[j][c] >> 32)), denom[j]);
-                    o[j][0] = fmaf(w, __uint_as_float((uint32_t)a0[j][c]), o[j][0]);
-                    o[j][1] = fmaf(w, __uint_as_float((uint32_t)(a0[j][c] >> 32)), o[j][1]);
-                    o[j][2] = fmaf(w, __uint_as_float((uint32_t)a1[j][c]), o[j][2]);
-                    o[j][3] = fmaf(w, __uint_as_float((uint32_t)(a1[j][c] >> 32)), o[j][3]);
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < RB; ++j)
-            if (rv[j] && dims_on) *reinterpret_cast<f32x4 *>(p.out + rh[j] * D + 4 * l32) = o[j] * (1.0f / denom[j]);
-    }
+    merge_chunks<GROUP, RB, D>(p, w);
 }
 
 // (K_DIRECT: see attn_k_direct_kernel)
@@ -2036,7 +2054,7 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     }
 
     if constexpr (TM && !STAGED) __syncthreads();   // every wavefront is done with its staging region: the epilogue reuses the memory
-    attn_end<NT, WG, D>(p, w, acc, m_run, l_run, out_row, [](int mt, int gg) { return mt * 16 + 4 * gg; }, sh);
+    attn_end<NT, WG, D, (WG > 1)>(p, w, acc, m_run, l_run, out_row, [](int mt, int gg) { return mt * 16 + 4 * gg; }, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -2245,7 +2263,7 @@ __device__ __forceinline__ void attn_f32_role(const AttnParams &p, OrderTable or
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int e = 0; e < 4; ++e) out[nt][mt][e] = acc[nt][mt / 4 * 4 + e][mt % 4];
-    attn_end<NT, WG, D>(p, w, out, m_run, l_run, out_row, [](int mt, int gg) { return mt / 4 * 64 + 16 * gg + mt % 4 * 4; }, sh);
+    attn_end<NT, WG, D, true>(p, w, out, m_run, l_run, out_row, [](int mt, int gg) { return mt / 4 * 64 + 16 * gg + mt % 4 * 4; }, sh);
 }
 
 // ===========================================================================

@@ -183,3 +183,19 @@ def test_chunks_sized_from_all_lengths(dtype, Hq, Hkv, k, kv_len, chunks):
             assert np.isnan(rows).all()
         else:
             assert np.abs(rows.astype(np.float64) - ref[_rows(w, b)]).max() <= ATTN_TOL[dtype]
+
+
+# requests of two to four chunks, whose merge takes four rows of four chunks per half wavefront and pass: 17 to 64 rows
+@pytest.mark.parametrize("dtype,Hq,Hkv,k_max", [("bf16", 16, 2, 6), ("bf16", 16, 2, 7), ("f32", 8, 2, 7), ("f32", 9, 1, 1), ("f32", 16, 2, 6), ("f32", 32, 2, 7)])
+def test_merge_of_few_chunks(tuning, dtype, Hq, Hkv, k_max):
+    from paper_2406_14066_amd.harness import DeviceStep
+    print("case few chunks", dtype, Hq, Hkv, k_max, flush=True)
+    tuning("SPEC_VERIFY_F32_SCALAR", 0)
+    kv_len = (1000, 257, 513, 40, 769)
+    w = W.make_workload("merge", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len),
+                        k=[min(x, k_max) for x in (8, 0, 8, 3, 2)], draft_std=2.0, sigma=0.8, data_seed=Hq + k_max, philox_seed=9)
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    assert ds.plan()["max_chunks"] == 4, ds.plan()
+    got, found = _run(ds)
+    assert found == 0
+    assert np.abs(got.astype(np.float64) - _oracle(w)).max() <= ATTN_TOL[dtype]
