@@ -39,7 +39,7 @@ struct AttnPlan {
     int32_t capacity_tokens;  // longest kv_len the plan allows for (chunk_tokens * max_chunks, capped by the bucket)
     int32_t fused_combine; // mfma kernel merges the chunk partials itself (few chunks) or leaves it to the combine kernel
     int32_t short_attn;    // the attention half streams for less time than the rejection stages' chain takes
-    int32_t spread;        // chunks sized from all lengths; the grid lists the chunks that exist, request by request (at most 64 requests)
+    int32_t spread;        // chunks sized from all lengths; the grid lists the chunks that exist, request by request (at most kMaxListedChunks of each)
     int64_t blocks;        // attention blocks that have work
     size_t acc_bytes;
     size_t ml_bytes;
@@ -59,8 +59,9 @@ struct AttnParams {
     int32_t attn_first_limit;     // attention blocks go first in the grid when there are at most this many
     float reject_span;            // fraction of the attention items among which the rejection items are spread in the grid
     int16_t split_p;              // feed the softmax weights to the PV product as bf16 high + low parts
-    int16_t f32;                  // fp32 queries and cache (token-major pages)
-    int32_t spread;               // see AttnPlan
+    int8_t f32;                   // fp32 queries and cache (token-major pages)
+    int8_t spread;                // see AttnPlan: the order table lists chunks
+    int32_t ranks;                // attention items per KV head and chunk index: the requests, or all chunks if the order table lists them
     int32_t reject_even_xcds;     // fused step: rejection blocks only at even positions of the grid's rows of 8 (see GridSplit)
     int32_t reject_even_limit;    // ... when there are at most this many attention blocks (the number of compute units)
     int32_t capacity_tokens;      // a request whose device-side kv_len exceeds this is skipped and counted in *errors
@@ -142,8 +143,12 @@ static_assert(sizeof(RejectParams) == 18 * 4 + 16 * 8, "RejectParams has padding
 inline int final_items(const RejectParams &p) { return (p.B + (1 << p.final_shift) - 1) >> p.final_shift; }
 
 // Order in which the attention items take the requests (longest first), passed as a
-// kernel argument.  n == 0: the given order.
+// kernel argument.  n == 0: the given order.  With chunks sized from all lengths it lists the chunks that
+// exist: an entry is a request, above it the chunk's index, and a flag at the request's last chunk.
 constexpr int kMaxOrdered = 1024;
+constexpr int kListChunkShift = 10, kMaxListedChunks = 32;
+constexpr uint32_t kListLast = 1u << 15;
+static_assert(kMaxOrdered <= 1 << kListChunkShift && kMaxListedChunks << kListChunkShift <= (int)kListLast, "an entry has 16 bits");
 struct UnitOrder {
     int32_t n;
     alignas(4) uint16_t request[kMaxOrdered];
@@ -160,10 +165,11 @@ struct LaunchEvents {
 // matrix-instruction path (bf16 with either page layout or fp32, d = 128 or 64; row_tiles tiles per wave
 // group, ap.row_groups wave groups per block).  `order` may be null.
 int step_attn_items(const AttnParams &ap);   // attention blocks of the launch
-// attention items per chunk index: one per (request, KV head), padded to whole rows of 8 blocks (one per XCD) when requests are split
+// attention items per chunk index (listed chunks: all of them): one per (rank, KV head), padded to whole rows of 8 blocks (one per
+// XCD) when requests are split
 __host__ __device__ inline int attn_row_items(const AttnParams &ap)
 {
-    const int units = ap.B * ap.Hkv;
+    const int units = ap.ranks * ap.Hkv;
     return ap.max_chunks > 1 ? (units + 7) / 8 * 8 : units;
 }
 hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject, const UnitOrder *order,

@@ -406,7 +406,9 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool s
         if (tu.chunk > 0 && tu.chunk <= chunk_cap) chunk = tu.chunk;
         // Chunks sized from all lengths: the split above is the longest request's, and the shorter ones leave compute units
         // without a block, whose share the others' chunks could have.  So the chunk becomes the shortest with which the blocks
-        // that have work are no more than aimed for, and the grid lists those only.  Before / after, in us, 32/8 heads, k = 3,
+        // that have work are no more than aimed for, and the grid lists those only (empty blocks behind them, which the order of the
+        // grid's halves then counts: three requests of 8000 and thirteen of 1000 tokens 34.6 -> 39.9 us, two of 16000 and fourteen
+        // of 500 39.8 -> 42.5; steps, 32/8 heads, k = 3, V = 32000).  Before / after, in us, 32/8 heads, k = 3,
         // bf16: attention alone, eight requests of 500 to 8000 tokens (chunks of 1568 / 1040) 27.5 / 26.4, sixteen (3792 / 2992)
         // 59.3 / 55.9; their steps (V = 32000) 30.6 / 27.9 and 62.4 / 58.1.  Where that shortens the chunk by a fifth at least (3680 /
         // 3360 68.7 / 70.3, 2608 / 2240 40.2 / 40.3, 3392 / 3232 33.6 / 33.9), and not below 512 tokens (480 / 320: 13.9 / 13.8, 64/8
@@ -431,7 +433,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool s
             int64_t blocks = 0;
             for (int b = 0; b < a->B; ++b) blocks += (a->host_kv_len[b] + hi * SPEC_BLOCK_SIZE - 1) / (hi * SPEC_BLOCK_SIZE);
             const bool full = f32 && hi * SPEC_BLOCK_SIZE < 256 && blocks * a->Hkv > target_blocks * 4 / 5;
-            if (hi * SPEC_BLOCK_SIZE <= chunk * 4 / 5 && !full) {
+            if (hi * SPEC_BLOCK_SIZE <= chunk * 4 / 5 && !full && max_len <= hi * SPEC_BLOCK_SIZE * kMaxListedChunks) {
                 chunk = hi * SPEC_BLOCK_SIZE;
                 pl.spread = 1;
             }
@@ -697,6 +699,17 @@ void make_order(const spec_attn_args *a, UnitOrder &order)
     order.n = a->B;
 }
 
+// The chunks that exist, request by request, for a plan whose chunks are sized from all lengths.
+void list_chunks(const spec_attn_args *a, const AttnPlan &pl, UnitOrder &list)
+{
+    list.n = 0;
+    for (int b = 0; b < a->B; ++b) {
+        const int chunks = (a->host_kv_len[b] + pl.chunk_tokens - 1) / pl.chunk_tokens;
+        for (int c = 0; c < chunks; ++c)
+            list.request[list.n++] = (uint16_t)((uint32_t)b | (uint32_t)c << kListChunkShift | (c == chunks - 1 ? kListLast : 0u));
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Plan cache: what one shape needs beyond the scalar checks, keyed by a hash of everything the
 // plan depends on.  Per thread, sixteen entries (one per draft length and then some), replaced in turn.
@@ -710,7 +723,7 @@ struct StepPlan {
     AttnPlan apl_small;             // for workspaces without room for apl
     RejectPlan rpl;
     RejectPlan rpl_small;           // for workspaces without room for rpl (never larger than rpl)
-    UnitOrder order;
+    UnitOrder order, listed;        // apl's if its chunks are listed, apl_small's (and apl's otherwise)
     size_t workspace_bytes = 0;     // what callers are told: enough for this call, and for its rejection half alone at this batch or a smaller one
     // (for telling a hash collision from a hit)
     int32_t B = 0, T = 0, V = 0;
@@ -794,6 +807,7 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
         e.apl_small = plan_attn(a, tu, r == nullptr, false);
         e.apl.short_attn = e.apl_small.short_attn = attn_estimate_us(a) <= 20.0 ? 1 : 0;
         make_order(a, e.order);
+        if (e.apl.spread) list_chunks(a, e.apl, e.listed);
         base = std::max(e.apl.total_bytes, e.apl_small.total_bytes);
     }
     e.workspace_bytes = base;
@@ -850,7 +864,8 @@ AttnParams attn_params(const spec_attn_args *a, const AttnPlan &pl, char *ws, in
     p.row_groups = pl.row_groups;
     p.row_tiles = pl.row_tiles;
     p.k_direct = pl.k_direct;
-    p.spread = pl.spread;
+    p.spread = (int8_t)pl.spread;
+    p.ranks = pl.spread ? (int32_t)(pl.blocks / a->Hkv) : a->B;
     p.f32 = a->qkv_dtype == SPEC_F32 ? 1 : 0;
     const double scale = a->softmax_scale > 0.0f ? (double)a->softmax_scale : 1.0 / sqrt((double)a->d);
     p.scale_log2 = (float)(scale * kLog2eD);
@@ -945,7 +960,7 @@ spec_status step_on_workspace(const spec_attn_args *attn, const spec_reject_args
     if (apl.use_mfma) {
         // the whole step in one launch
         hipError_t err = timed_launch(SPEC_KERNEL_STEP, [&](LaunchEvents ev) {
-            return launch_step_fused(&ap, &rp, apl.spread ? nullptr : &plan.order, ev, stream);
+            return launch_step_fused(&ap, &rp, apl.spread ? &plan.listed : &plan.order, ev, stream);
         });
         if (err == hipSuccess && !apl.fused_combine && apl.max_chunks > 1)
             err = timed(SPEC_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });
@@ -1008,7 +1023,8 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
         if (pl.use_mfma) {
             AttnParams ap;
             memset(&ap, 0, sizeof ap);
-            ap.B = attn->B; ap.Hkv = attn->Hkv; ap.max_chunks = pl.max_chunks; ap.row_groups = pl.row_groups;
+            ap.Hkv = attn->Hkv; ap.max_chunks = pl.max_chunks; ap.spread = (int8_t)pl.spread;
+            ap.ranks = pl.spread ? (int32_t)(pl.blocks / attn->Hkv) : attn->B;
             info->attn_blocks = step_attn_items(ap);
             info->launches = 1 + ((!pl.fused_combine && pl.max_chunks > 1) ? 1 : 0);
         } else {
@@ -1045,7 +1061,7 @@ spec_status spec_verify_attn(const spec_attn_args *attn, void *workspace, size_t
     const AttnParams ap = attn_params(attn, pl, static_cast<char *>(workspace), nullptr);
     if (!pl.use_mfma) return run_attn_generic(ap, attn->qkv_dtype, stream);
     hipError_t err = timed_launch(SPEC_KERNEL_ATTN, [&](LaunchEvents ev) {
-        return launch_step_fused(&ap, nullptr, pl.spread ? nullptr : &plan.order, ev, stream);
+        return launch_step_fused(&ap, nullptr, pl.spread ? &plan.listed : &plan.order, ev, stream);
     });
     if (err == hipSuccess && !pl.fused_combine && pl.max_chunks > 1)
         err = timed(SPEC_KERNEL_ATTN_COMBINE, stream, [&] { return launch_attn_combine(ap, stream); });

@@ -1279,34 +1279,22 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     // that all chunks of a (request, KV head) run on one XCD and find its query rows, table entries,
     // partial results and ticket in that XCD's L2 (spread over the XCDs the ragged long-context
     // workload takes 4% longer).
-    const int n_units = p.B * p.Hkv;
+    // Where the order table lists chunks there is one such row: only the chunks that exist, request by request (no
+    // holes between blocks that have work: the dispatcher deals the blocks out in turn, and empty ones leave their compute
+    // units idle while others get two).
+    const int n_units = p.ranks * p.Hkv;
     const int row_items = attn_row_items(p);
-    int chunk, kvh, b, L = 0;
-    if (p.spread) {
-        // Only the chunks that exist, request by request (no holes between blocks that have work: the dispatcher deals the
-        // blocks out in turn, and empty ones leave their compute units idle while others get two).  A lane looks
-        // at a request; lengths that are left out below count as one chunk, whose block reports them.
-        const int len = lane < p.B ? p.kv_len[lane] : 0;
-        const int mine = len >= 1 && len <= p.capacity_tokens ? (len + p.chunk_tokens - 1) / p.chunk_tokens : 1;
-        kvh = item % p.Hkv;
-        chunk = item / p.Hkv;
-        for (b = 0; b < p.B; ++b) {
-            const int n = __builtin_amdgcn_readlane(mine, b);
-            if (chunk < n) break;
-            chunk -= n;
-        }
-        if (b == p.B) return false;
-        L = __builtin_amdgcn_readlane(len, b);
-    } else {
-        chunk = item / row_items;
-        const int place = item - chunk * row_items;
-        if (place >= n_units) return false;   // padding
-        kvh = place % p.Hkv;
-        b = place / p.Hkv;   // rank in the order of the attention items
-        if (order.n > 0) {
-            const uint32_t pair = order.pairs[b >> 1];
-            b = (int)((b & 1) ? pair >> 16 : pair & 0xFFFFu);
-        }
+    int chunk = item / row_items;
+    const int place = item - chunk * row_items;
+    if (place >= n_units) return false;   // padding
+    const int kvh = place % p.Hkv;
+    int b = place / p.Hkv;   // rank in the order of the attention items
+    uint32_t entry = 0;
+    if (order.n > 0) {
+        const uint32_t pair = order.pairs[b >> 1];
+        entry = (b & 1) ? pair >> 16 : pair & 0xFFFFu;
+        b = (int)(entry & ((1u << kListChunkShift) - 1u));
+        chunk += (int)(entry >> kListChunkShift) & (kMaxListedChunks - 1);
     }
     const int unit = b * p.Hkv + kvh;
 
@@ -1315,7 +1303,7 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     int bt = 0;
     if (p.max_chunks == 1 && first + STEP * lane < p.max_blocks_per_req)
         bt = p.block_table[(size_t)b * p.max_blocks_per_req + first + STEP * lane];
-    if (!p.spread) L = uniform_load(p.kv_len, b);
+    const int L = uniform_load(p.kv_len, b);
     const int row0 = uniform_load(p.cu_q_len, b);
     const int q_len = uniform_load(p.cu_q_len, b + 1) - row0;
     // The lengths come from device memory and bound every loop and index below: a request
@@ -1327,6 +1315,8 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     }
     const int nchunks = (L + p.chunk_tokens - 1) / p.chunk_tokens;   // <= max_chunks, since L <= capacity_tokens
     if (chunk >= nchunks) return false;
+    // a request that has outgrown its listed chunks: the merge waits for a chunk that no block has, so its rows are left out
+    if ((entry & kListLast) != 0 && chunk + 1 < nchunks && kvh == 0 && tid == 0 && p.errors != nullptr) atomicAdd(p.errors, 1ull);
     // even chunks per request, page aligned (never longer than chunk_tokens)
     const int C = ((L + nchunks - 1) / nchunks + SPEC_BLOCK_SIZE - 1) & ~(SPEC_BLOCK_SIZE - 1);
     const int group = p.Hq / p.Hkv;
@@ -2579,7 +2569,7 @@ SPEC_STEP_LAUNCHER(launch_step_f32)
 #if SPEC_STEP_HAS_PART(0)
 int step_attn_items(const AttnParams &ap)
 {
-    return attn_row_items(ap) * ap.max_chunks;
+    return attn_row_items(ap) * (ap.spread ? 1 : ap.max_chunks);
 }
 
 hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject, const UnitOrder *order,
@@ -2609,7 +2599,11 @@ hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject,
         const bool dim_ok = ap.d == kD || ap.d == 64;
         if (!dim_ok || !shape_ok || ap.chunk_tokens > 4096 / ap.row_groups || ap.chunk_tokens % SPEC_BLOCK_SIZE != 0 ||
             ap.capacity_tokens > ap.chunk_tokens * ap.max_chunks ||
-            (ap.f32 && ap.kv_layout != SPEC_KV_TOKEN_MAJOR) || (ap.fused_combine && ap.max_chunks > kMaxFusedChunks) || (order != nullptr && order->n != 0 && order->n != ap.B))
+            (ap.f32 && ap.kv_layout != SPEC_KV_TOKEN_MAJOR) || (ap.fused_combine && ap.max_chunks > kMaxFusedChunks) || (order != nullptr && order->n != 0 && order->n != ap.ranks))
+            return hipErrorInvalidValue;
+        // listed chunks: a table with all of them, whole rows of blocks, and a merge inside the launch
+        if (ap.spread ? (order == nullptr || order->n != ap.ranks || ap.max_chunks > kMaxListedChunks || ap.Hkv % kXcds != 0 || !ap.fused_combine)
+                      : ap.ranks != ap.B)
             return hipErrorInvalidValue;
         n_attn = step_attn_items(ap);
     }

@@ -169,6 +169,7 @@ def test_chunks_sized_from_all_lengths(dtype, Hq, Hkv, k, kv_len, chunks):
         ds.workspace = whole
     if len(kv_len) == 1:
         return
+    assert plan["attn_blocks"] == need, plan
     # a length beyond the plan and one below its own query rows
     good = ds.kv_len.clone()
     bad = {0: plan["chunk_tokens"] * plan["max_chunks"] + 1, 2: 0}
@@ -199,3 +200,36 @@ def test_merge_of_few_chunks(tuning, dtype, Hq, Hkv, k_max):
     got, found = _run(ds)
     assert found == 0
     assert np.abs(got.astype(np.float64) - _oracle(w)).max() <= ATTN_TOL[dtype]
+
+
+# the listed chunks are the host lengths': a request that has grown or shrunk on the device within its last chunk's room is served,
+# one that needs a chunk more is left out and counted once
+@pytest.mark.parametrize("dtype,Hq,Hkv", [("bf16", 16, 16), ("f32", 16, 8)])
+def test_lengths_that_outgrow_their_listed_chunks(dtype, Hq, Hkv):
+    from paper_2406_14066_amd.harness import DeviceStep
+    print("case outgrown", dtype, Hq, Hkv, flush=True)
+    kv_len = (4000, 600, 64, 6000)
+    w = W.make_workload("outgrown", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len), k=[2] * 4, draft_std=2.0, sigma=0.8,
+                        data_seed=Hq, philox_seed=9)
+    w.block_table = np.concatenate([w.block_table, w.block_table], axis=1)   # room for the longer lengths (any pages will do)
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    plan = sv.spec_verify_plan(ds.attn_args, None)
+    C = plan["chunk_tokens"]
+    chunks = [(n + C - 1) // C for n in kv_len]
+    assert plan["attn_blocks"] == Hkv * sum(chunks), plan
+    room = chunks[0] * C
+    pages = -(-room // 16) + 1
+    w.block_table[0, :pages] = w.block_table[3, np.arange(pages) % (6000 // 16)]
+    ds.block_table.copy_(ds.block_table.new_tensor(w.block_table))
+    for lens, out in (([room, 500, 40, 3000], ()), ([room + 1, 500, 64, 6000], (0,)), ([4000, chunks[1] * C + 16, 64, 6000], (1,))):
+        w.kv_len = np.asarray(lens, dtype=np.int32)
+        ds.kv_len.copy_(ds.kv_len.new_tensor(w.kv_len))
+        got, found = _run(ds)
+        assert found == len(out), (lens, found)
+        ref = _oracle(w)
+        for b in range(w.B):
+            rows = got[_rows(w, b)]
+            if b in out:
+                assert np.isnan(rows).all()
+            else:
+                assert np.abs(rows.astype(np.float64) - ref[_rows(w, b)]).max() <= ATTN_TOL[dtype]

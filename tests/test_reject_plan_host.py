@@ -63,6 +63,17 @@ def test_early_stop_beside_an_attention_half(B, k, length, V, ragged, stops):
         assert sv.spec_verify_plan(None, r)["early_stop"] == 0
 
 
+# chunks sized from all lengths: the launch has the blocks that the rejection half's plan counts on, one per chunk that exists
+@pytest.mark.parametrize("lens,V", [([8000] * 3 + [1000] * 13, 32000), ([16000] * 2 + [500] * 14, 32000), ([32000] + [800] * 7, 32000),
+                                    ([8000] * 2 + [300] * 14, None), ([12000] + [400] * 15, None)])
+def test_listed_chunks_are_the_blocks_of_the_launch(lens, V):
+    a = attn_args(len(lens), 3, max(lens), Hq=32)
+    hk = np.asarray(lens, dtype=np.int32)
+    a.host_kv_len, a._keep = hk.ctypes.data, a._keep + (hk,)
+    plan = sv.spec_verify_plan(a, None if V is None else reject_args(len(lens), 3, V))
+    assert plan["attn_blocks"] == 8 * sum((n + plan["chunk_tokens"] - 1) // plan["chunk_tokens"] for n in lens) <= 256
+
+
 def small_records(B, k, V, mode=sv.ACCEPT_SAMPLE):
     """Bytes of the rejection half's records with about 256 statistics and 512 race blocks: the least that
     the half alone works with."""
