@@ -107,7 +107,7 @@ struct Tuning {
     int k_direct = -1;            // SPEC_VERIFY_K_DIRECT=0/1: the attention alone on token-major pages, K through LDS or straight into
                                   // operand order where there is a kernel for it (-1: automatic)
     int f32_scalar = -1;          // SPEC_VERIFY_F32_SCALAR=0/1: fp32 attention alone on the matrix-instruction / scalar kernel (-1: automatic)
-    int spin_limit = 1 << 20;     // SPEC_VERIFY_SPIN_LIMIT: polls of a bounded wait (about a second at the default)
+    int spin_limit = 1 << 20;     // SPEC_VERIFY_SPIN_LIMIT: polls of a bounded wait (about two seconds at the default)
     uint32_t epoch = 1;           // changes with every reload: part of the plan cache's key
 };
 Tuning g_tuning;

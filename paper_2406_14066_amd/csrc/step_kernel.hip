@@ -54,6 +54,7 @@
 // per decision (segment sums, log-sum-exp, p/q of the draft token, the comparison
 // with u) is fp64.
 #include "common.h"
+#include "bounded_wait.h"
 #include "grid_split.h"
 
 #include <hip/hip_ext.h>
@@ -547,19 +548,17 @@ __device__ __forceinline__ void race_winner(float &best_score, int &best_id, Rej
 
 // Bounded wait until `ready` holds for every thread of the block (block-wide AND).
 // `probe` re-evaluates the condition; returns false if the limit ran out.
-// FEW: few blocks wait like this (the final stage's, at the very end), so that their polls cost the streams nothing: naps stay short
-// (rejection alone, one request 12.7 -> 12.2 us, 32 at k = 4 19.4 -> 18.9; the smallest fp32 step 12.7 -> 12.1).
+// FEW: see nap_length.
 template <bool FEW = false, typename F>
 __device__ __forceinline__ bool wait_all(const RejectParams &p, F probe)
 {
     for (int spin = 0; spin < p.spin_limit; ++spin) {
         if (__syncthreads_and(probe() ? 1 : 0)) return true;
-        // In a small launch the data is a poll or two away and a long nap would be most of the wait:
-        // short naps first.  In a large one many blocks wait at once and their polls compete with the
-        // streams (short naps there: the 7B- and 70B-shaped steps 0.5 to 0.8% slower).
-        if (p.short_naps && spin < 4) __builtin_amdgcn_s_sleep(2);
-        else if (FEW || (p.short_naps && spin < 8)) __builtin_amdgcn_s_sleep(8);
-        else __builtin_amdgcn_s_sleep(32);
+        switch (nap_length(spin, FEW, p.short_naps != 0)) {   // (the instruction takes a constant)
+            case 2: __builtin_amdgcn_s_sleep(2); break;
+            case 8: __builtin_amdgcn_s_sleep(8); break;
+            default: __builtin_amdgcn_s_sleep(32); break;
+        }
     }
     return false;
 }
