@@ -459,16 +459,17 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool s
     // 100 30.3 / 28.3; 32/8 heads, k = 8, 768 of 250 30.8 / 28.5; lengths of a tenth to twice the mean 1 to 3% slower from 768 blocks on.
     //   one or two per unit, 400 to 700 tokens in the mean (below that the launch is start-up, above it memory): 512 of 600 30.3 / 29.4, of
     // 50 to 950 30.7 / 28.8, 384 of 600 25.1 / 24.5, 256 of 50 to 950 20.9 / 20.1; 512 of 250 16.5 / 16.3, of 1400 60.4 / 62.0.
-    // Two wave groups of three row tiles: at most a block per compute unit, with 256 tokens or fewer.  64/8 heads, k = 7, four
-    // requests of 16 / 100 / 200 tokens: direct 5, 4 and 6% faster than the staged walk page by page; 64 requests (two blocks per unit) of
-    // 100 / 200 tokens 0 and 6% slower.  Two row tiles, which the staged walk takes in pairs of pages, are at least as fast that
-    // way (32 requests of 100 / 256 tokens, staged / direct 10.0 / 10.4, 13.2 / 14.5 us).
+    // Two wave groups: at most a block per compute unit, with 256 tokens or fewer.  Staged / direct, two row tiles (both in pairs of
+    // pages): 64/8 heads, k = 7, 32 requests of 16 / 90 to 128 / 200 to 256 tokens 8.0 / 7.8, 10.45 / 9.7, 13.5 / 12.5 us; 64/4 heads,
+    // k = 3, one of 256 10.9 / 10.6, eight of 500 to 2000 in chunks of 256 25.0 / 24.2.  More blocks: 48 requests on 64/8
+    // heads, 90 to 128 tokens 13.6 / 14.8, 64 of 150 to 200 18.4 / 20.6; chunks of more tokens, 32 of 500 to 2000 46.0 / 47.4.  Three tiles:
+    // 64/8 heads, four requests of 16 / 100 / 200 tokens direct 5, 4 and 6% faster; 64 requests of 100 / 200 tokens 0 and 6% slower.
     const int d_units = a->B * a->Hkv;
     pl.k_direct = 0;
     if (a->qkv_dtype == SPEC_BF16 && a->kv_layout == SPEC_KV_TOKEN_MAJOR && a->d == 128 && pl.use_mfma && pl.row_tiles >= 2) {
         const int cus = compute_units();
         if (pl.row_groups == 2) {
-            pl.k_direct = pl.row_tiles == 3 && pl.chunk_tokens <= 256 && (int64_t)d_units * pl.max_chunks <= cus;
+            pl.k_direct = pl.chunk_tokens <= 256 && (int64_t)d_units * pl.max_chunks <= cus;
         } else if (pl.row_groups == 1 && pl.max_chunks == 1 && a->host_kv_len != nullptr && d_units >= cus) {
             int64_t sum = 0;
             int longest = 0;

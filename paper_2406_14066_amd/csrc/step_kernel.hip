@@ -1593,7 +1593,8 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
     // 200 to 1900 tokens, k = 7 / 8 31.0 -> 30.0 / 33.0 -> 31.4; four of 9000 to 18000, k = 8 37.5 -> 34.4; 128 of 100, k = 5 14.9 -> 14.2.
     // (Not elsewhere: one row tile of 64 dims 28.5 -> 28.3 and, 256 short requests, 38.5 -> 38.8; tiled pages of 64 dims 28.0 ->
     // 28.4; 128 dims, one tile, 43.9 -> 50.5 at an occupancy step less, two tiles 41.1 -> 42.9.  With K straight into operand
-    // order it takes the staged walk's pairs, whose sums it has to equal.)
+    // order, two groups of two tiles take the staged walk's pairs, whose sums they have to equal.  Staged, requests of one
+    // page or two lose: 130 of 9 to 16 tokens on 64/8 heads, k = 7 22.5 -> 23.8 us, of 33 to 48 25.05 -> 24.5.)
     constexpr bool PAIRS_STAGED = STAGED && (NT <= 2 || D == 64);
     constexpr bool PAIR_WALK = !STAGED && TM && ((D == 64 && NT >= 2) || (K_DIRECT && NT == 2 && WG == 2));
     constexpr int KK = D / 32;                        // 32-dim steps of the score product = 1 KB loads per K or V page
@@ -1984,7 +1985,11 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         };
-        for (int it = 0; it < my_pages; it += 2) {
+        // (A last page without a partner goes by itself, at half the work of a pair: 130 requests of 9 to 16 / 49 to 64 / 300 to 900
+        // tokens on 32/8 heads, k = 7 15.8 -> 14.4 / 16.8 -> 15.1 / 39.2 -> 37.7 us.  Not with K straight into operand order,
+        // whose sums have to equal the staged walk's, and there code for both spills or is slower: 25.2 -> 26.2 at 64 dims.)
+        int it = 0;
+        for (; it < (K_DIRECT ? my_pages : my_pages - 1); it += 2) {
             if constexpr (!K_DIRECT) {
                 to_lds(k0, k1);
 #pragma unroll
@@ -1998,7 +2003,16 @@ __device__ __forceinline__ void attn_role(const AttnParams &p, OrderTable order,
                 to_lds(v0, v1);
                 load_v(it + 2);
                 v_operands(lds0, lds1, v);
-            }, pw + PW * it, pw + PW * (it + 1), it + 1 < my_pages);
+            }, pw + PW * it, pw + PW * (it + 1), !K_DIRECT || it + 1 < my_pages);
+        }
+        if (!K_DIRECT && it < my_pages) {
+            PageRegs<D> last;
+#pragma unroll
+            for (int i = 0; i < KK; ++i) {
+                last.k[i] = k0[i];
+                last.v[i] = v0[i];
+            }
+            consume(last, pw + PW * it);
         }
     } else {
         // Two register batches of P pages each.  While one batch is consumed the loads of the
