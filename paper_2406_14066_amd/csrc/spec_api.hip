@@ -339,8 +339,9 @@ bool f32_scalar_is_faster(const AttnPlan &pl, int d, int max_len, int64_t rows)
 // (two with three row tiles), in multiples of the 16 tokens of a page.  The longest length the
 // plan allows for is the caller's bucket (max_kv_len) or, without one, the longest host length.
 // (alone: no rejection half in the same call)
-// (spread: the chunks may be sized from all lengths, see below; a plan without needs the smaller workspace)
-AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool spread)
+// (spread: the chunks may be sized from all lengths, see below, for this share of the blocks aimed for; 0: they may not, which needs
+// the smaller workspace)
+AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, double spread)
 {
     AttnPlan pl;
     memset(&pl, 0, sizeof pl);
@@ -417,7 +418,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool s
         // chunks of 128 tokens, or 192 where that makes more than six, unless they fill the chip (32/8 heads, k = 4, chunks of 256 /
         // 128: one request of 500 tokens 21.3 / 17.2 us, four 22.3 / 19.3; 256 / 192 / 128: four of 1000 24.3 / 21.4 / 24.0; 224 / 160,
         // eight of 640 22.7 / 23.6; one tile, k = 2, one of 250: 10.9 / 11.7).  Sixteen of 64 to 1000: 32.3 / 28.9.
-        if (spread && tu.chunk == 0 && tu.target_blocks == 0 && a->max_kv_len == 0 && a->B <= kWave && a->Hkv % kXcdCount == 0 && units <= target_blocks &&
+        if (spread > 0.0 && tu.chunk == 0 && tu.target_blocks == 0 && a->max_kv_len == 0 && a->B <= kWave && a->Hkv % kXcdCount == 0 && units <= target_blocks &&
             (f32 || pl.row_tiles < 3)) {
             const int64_t least = !f32 ? 512 : (tiles >= 2 ? (max_len <= 768 ? 128 : 192) : 256);
             const int worth = f32 ? 512 : 1024;
@@ -427,7 +428,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, bool s
                 const int64_t mid = (lo + hi) / 2;
                 int64_t blocks = 0;
                 for (int b = 0; b < a->B; ++b) blocks += (a->host_kv_len[b] + mid * SPEC_BLOCK_SIZE - 1) / (mid * SPEC_BLOCK_SIZE);
-                if (blocks * a->Hkv <= target_blocks) hi = mid;
+                if (blocks * a->Hkv <= target_blocks * spread) hi = mid;
                 else lo = mid + 1;
             }
             int64_t blocks = 0;
@@ -629,8 +630,10 @@ RejectPlan plan_reject(const spec_reject_args *r, const Tuning &tu, double attn_
     // those, at an acceptance rate of 0.7, in us of logits at 5.5 TB/s, has to repay a look (3 us of a block's time) per row
     // and races that start later.  All rows read or waiting as chosen above / looking, in us: 64/8 heads, token-major, B=96 k=7 99 / 87,
     // tiles, B=48 k=8 88.4 / 80.9; 32/8 heads, B=86 k=7 L=1326 126 / 112; 64/4 heads, B=65 k=8 L=690 117 / 107; drafts of 1..k: 64/8
-    // heads, B=200 k=3 93.7 / 90.0, B=64 k=5 (nothing is saved) 49.9 / 52.8.  Over 138 steps (24 to 256 requests, all modes, rates of
-    // 0.5, 0.7 and 0.9) the rule takes a sixth of them, 15% faster to 5% slower.  Not where the
+    // heads, B=200 k=3 93.7 / 90.0, B=64 k=5 (nothing is saved) 49.9 / 52.8.  Over 70 steps that stop early in either form (24 to
+    // 256 requests, k = 2 to 8, V = 16000 to 128256, 60 to 2000 tokens, all modes) the time against all rows read is 0.98 at an acceptance
+    // rate of 0.9, 0.94 at 0.7 and 0.90 at 0.45; best 0.78, 0.78 and 0.70; worst 1.15, 1.08 and 1.04 (64/4 heads, B=64 k=7,
+    // V=16000, 16 to 97 tokens: the rate is not known here, nor how long a short launch takes to dispatch).  Not where the
     // rejection half runs alone: its blocks fill the chip at once (four per unit) and start together; 120 such calls -7 to +29%.
     // (peek: the kernel that takes the launch can.)
     if (peek && r->T > r->B && (uniform_q > 0 || r->B <= 256)) {
@@ -662,6 +665,14 @@ RejectPlan plan_reject(const spec_reject_args *r, const Tuning &tu, double attn_
     pl.partial_bytes = align_up(((size_t)r->B * std::max(pl.race_segments, room) * 2 + r->B) * sizeof(unsigned long long));
     pl.total_bytes = pl.stats_bytes + pl.partial_bytes;
     return pl;
+}
+
+// Blocks of the rejection half: statistics, race, final stage.
+int64_t reject_blocks(const spec_reject_args *r, const RejectPlan &pl)
+{
+    const int64_t rows = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * (int64_t)r->T - r->B : r->T;
+    const int64_t race = r->accept_mode == SPEC_ACCEPT_GREEDY ? 0 : (int64_t)r->B * pl.race_segments;
+    return rows * pl.stat_segments + race + ((r->B + (1 << pl.final_shift) - 1) >> pl.final_shift);
 }
 
 // The most that the rejection half alone takes with this vocabulary, at this batch or any smaller one (fewer rows get more
@@ -804,20 +815,35 @@ const StepPlan &plan_for(const spec_attn_args *a, const spec_reject_args *r)
     if (e.status != SPEC_OK) return e;
     size_t base = 0;
     if (a != nullptr) {
-        e.apl = plan_attn(a, tu, r == nullptr, true);
-        e.apl_small = plan_attn(a, tu, r == nullptr, false);
+        e.apl = plan_attn(a, tu, r == nullptr, 1.0);
+        e.apl_small = plan_attn(a, tu, r == nullptr, 0.0);
         e.apl.short_attn = e.apl_small.short_attn = attn_estimate_us(a) <= 20.0 ? 1 : 0;
         make_order(a, e.order);
+    }
+    const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
+    const bool peek = attn_us >= 0.0 && a->qkv_dtype == SPEC_BF16;
+    if (r != nullptr) {
+        e.rpl = plan_reject(r, tu, attn_us, a != nullptr ? e.apl.blocks : 0, false, peek);
+        // Rejection blocks that fill the chip and go first in the grid (see fill_args): the attention's get the slots that the statistics
+        // leave, and the race's blocks, about one per compute unit, hold theirs to the end.  With a chunk's block for every compute
+        // unit the last of them start when the race ends, so the split aims for an eighth less.  256 / 224 blocks, in us: 64/8
+        // heads, k = 2, V = 128256, eight requests of 60 to 6000 tokens 41.3 / 36.2; 32/8, k = 1, twelve 33.8 / 28.9; fp32, 64/8, k = 3,
+        // V = 32000, twelve of 60 to 3000 58.4 / 45.6.  With fewer rejection blocks (32/8, k = 1, V = 8192, 17 of 60 to 4000 26.6 / 28.4)
+        // or a longer attention half (32/8, k = 4, V = 32000, eleven of 200 to 6000 31.7 / 38.2 with fewer) not.
+        const int64_t n_reject = reject_blocks(r, e.rpl);
+        if (a != nullptr && e.apl.spread && e.apl.short_attn && n_reject >= 2 * compute_units() && n_reject <= tu.reject_first_limit) {
+            e.apl = plan_attn(a, tu, false, 0.875);
+            e.apl.short_attn = 1;
+            e.rpl = plan_reject(r, tu, attn_us, e.apl.blocks, false, peek);
+        }
+    }
+    if (a != nullptr) {
         if (e.apl.spread) list_chunks(a, e.apl, e.listed);
         base = std::max(e.apl.total_bytes, e.apl_small.total_bytes);
     }
     e.workspace_bytes = base;
     if (r != nullptr) {
-        const double attn_us = (a != nullptr && e.apl.use_mfma) ? attn_estimate_us(a) : -1.0;
-        const int64_t attn_blocks = a != nullptr ? e.apl.blocks : 0;
-        const bool peek = attn_us >= 0.0 && a->qkv_dtype == SPEC_BF16;
-        e.rpl = plan_reject(r, tu, attn_us, attn_blocks, false, peek);
-        e.rpl_small = attn_us < 0.0 ? plan_reject(r, tu, attn_us, attn_blocks, true, peek) : e.rpl;
+        e.rpl_small = attn_us < 0.0 ? plan_reject(r, tu, attn_us, a != nullptr ? e.apl.blocks : 0, true, peek) : e.rpl;
         if (e.rpl_small.total_bytes > e.rpl.total_bytes) e.rpl_small = e.rpl;
         e.workspace_bytes = std::max(base + e.rpl.total_bytes, (attn_us < 0.0 ? base : 0) + reject_room(r, tu));
     }
@@ -1038,9 +1064,7 @@ spec_status spec_verify_plan(const spec_attn_args *attn, const spec_reject_args 
         info->early_stop = pl.early_stop != kReadAll ? 1 : 0;
         info->stat_segments = pl.stat_segments;
         info->race_segments = reject->accept_mode == SPEC_ACCEPT_GREEDY ? 0 : pl.race_segments;
-        const int rows = reject->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 * reject->T - reject->B : reject->T;
-        info->reject_blocks = rows * pl.stat_segments + reject->B * info->race_segments +
-                              ((reject->B + (1 << pl.final_shift) - 1) >> pl.final_shift);
+        info->reject_blocks = (int32_t)reject_blocks(reject, pl);
         if (attn == nullptr || !plan.apl.use_mfma) info->launches += 1;
     }
     info->workspace_bytes = plan.workspace_bytes;

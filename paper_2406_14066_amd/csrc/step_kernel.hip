@@ -2466,8 +2466,10 @@ dim3 fill_args(StepArgs &args, const AttnParams &ap, const RejectParams &rp, int
     // beside them), the rejection blocks, which slow down the attention block they share a compute
     // unit with, go to the even XCDs only: even positions of a row of 8 blocks; the odd positions
     // of such rows exit at once.  (With more attention blocks it does not pay: measured 1% slower
-    // with two per compute unit, 15% slower where the rejection half is a fifth of the step.)
-    gs.reject_cols = (HAS_ATTN && HAS_REJECT && ap.reject_even_xcds && n_attn <= ap.reject_even_limit && !reject_first) ? kXcds / 2 : kXcds;
+    // with two per compute unit, 15% slower where the rejection half is a fifth of the step.  Nor where the
+    // order table lists the chunks, whose blocks are all about equally long: even / all XCDs, 32/8 heads, ten requests of 500 to 8000
+    // tokens, k = 4, V = 32000 38.1 / 33.0 us; 64/8, nine, k = 3, V = 128256 47.8 / 40.4; at best 2% faster.)
+    gs.reject_cols = (HAS_ATTN && HAS_REJECT && ap.reject_even_xcds && !ap.spread && n_attn <= ap.reject_even_limit && !reject_first) ? kXcds / 2 : kXcds;
     const int rows_reject = (n_reject + gs.reject_cols - 1) / gs.reject_cols;
     gs.rows_attn_mixed = reject_first ? 0 : attention_rows_mixed(rows_attn_all, rows_reject, ap.reject_span);
     return dim3(mixed ? (rows_attn_all + rows_reject) * kXcds

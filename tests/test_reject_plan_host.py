@@ -74,6 +74,18 @@ def test_listed_chunks_are_the_blocks_of_the_launch(lens, V):
     assert plan["attn_blocks"] == 8 * sum((n + plan["chunk_tokens"] - 1) // plan["chunk_tokens"] for n in lens) <= 256
 
 
+# beside a short attention half whose rejection blocks fill the chip and go first, an eighth of the units is left to them
+@pytest.mark.parametrize("lens,k,V,Hq,blocks", [([60 + 850 * i for i in range(8)], 2, 128256, 64, 224), ([6000] * 3 + [900] * 9, 1, 128256, 32, 224),
+                                                ([200 + 300 * i for i in range(17)], 1, 8192, 32, 256), ([200 + 1000 * i for i in range(11)], 4, 32000, 32, 256)])
+def test_listed_chunks_beside_rejection_blocks_that_go_first(lens, k, V, Hq, blocks):
+    a = attn_args(len(lens), k, max(lens), Hq=Hq)
+    hk = np.asarray(lens, dtype=np.int32)
+    a.host_kv_len, a._keep = hk.ctypes.data, a._keep + (hk,)
+    plan = sv.spec_verify_plan(a, reject_args(len(lens), k, V))
+    assert plan["attn_blocks"] == 8 * sum((n + plan["chunk_tokens"] - 1) // plan["chunk_tokens"] for n in lens)
+    assert blocks - 32 < plan["attn_blocks"] <= blocks, plan
+
+
 def small_records(B, k, V, mode=sv.ACCEPT_SAMPLE):
     """Bytes of the rejection half's records with about 256 statistics and 512 race blocks: the least that
     the half alone works with."""
