@@ -39,7 +39,7 @@ struct AttnPlan {
     int32_t capacity_tokens;  // longest kv_len the plan allows for (chunk_tokens * max_chunks, capped by the bucket)
     int32_t fused_combine; // mfma kernel merges the chunk partials itself (few chunks) or leaves it to the combine kernel
     int32_t short_attn;    // the attention half streams for less time than the rejection stages' chain takes
-    int32_t spread;        // chunks sized from all lengths; the grid lists the chunks that exist, request by request (at most kMaxListedChunks of each)
+    int32_t spread;        // chunks sized from all lengths; the grid lists the chunks that exist, request by request (at most kMaxListedRequests, kMaxListedChunks of each)
     int64_t blocks;        // attention blocks that have work
     size_t acc_bytes;
     size_t ml_bytes;
@@ -144,11 +144,11 @@ inline int final_items(const RejectParams &p) { return (p.B + (1 << p.final_shif
 
 // Order in which the attention items take the requests (longest first), passed as a
 // kernel argument.  n == 0: the given order.  With chunks sized from all lengths it lists the chunks that
-// exist: an entry is a request, above it the chunk's index, and a flag at the request's last chunk.
+// exist: an entry is a request, above it the chunk's index and the index of the request's last chunk.
 constexpr int kMaxOrdered = 1024;
-constexpr int kListChunkShift = 10, kMaxListedChunks = 32;
-constexpr uint32_t kListLast = 1u << 15;
-static_assert(kMaxOrdered <= 1 << kListChunkShift && kMaxListedChunks << kListChunkShift <= (int)kListLast, "an entry has 16 bits");
+constexpr int kListRequestBits = 6, kListChunkBits = 5;
+constexpr int kMaxListedRequests = 1 << kListRequestBits, kMaxListedChunks = 1 << kListChunkBits;
+static_assert(kListRequestBits + 2 * kListChunkBits <= 16, "an entry has 16 bits");
 struct UnitOrder {
     int32_t n;
     alignas(4) uint16_t request[kMaxOrdered];

@@ -418,7 +418,7 @@ AttnPlan plan_attn(const spec_attn_args *a, const Tuning &tu, bool alone, double
         // chunks of 128 tokens, or 192 where that makes more than six, unless they fill the chip (32/8 heads, k = 4, chunks of 256 /
         // 128: one request of 500 tokens 21.3 / 17.2 us, four 22.3 / 19.3; 256 / 192 / 128: four of 1000 24.3 / 21.4 / 24.0; 224 / 160,
         // eight of 640 22.7 / 23.6; one tile, k = 2, one of 250: 10.9 / 11.7).  Sixteen of 64 to 1000: 32.3 / 28.9.
-        if (spread > 0.0 && tu.chunk == 0 && tu.target_blocks == 0 && a->max_kv_len == 0 && a->B <= kWave && a->Hkv % kXcdCount == 0 && units <= target_blocks &&
+        if (spread > 0.0 && tu.chunk == 0 && tu.target_blocks == 0 && a->max_kv_len == 0 && a->B <= kMaxListedRequests && a->Hkv % kXcdCount == 0 && units <= target_blocks &&
             (f32 || pl.row_tiles < 3)) {
             const int64_t least = !f32 ? 512 : (tiles >= 2 ? (max_len <= 768 ? 128 : 192) : 256);
             const int worth = f32 ? 512 : 1024;
@@ -718,7 +718,7 @@ void list_chunks(const spec_attn_args *a, const AttnPlan &pl, UnitOrder &list)
     for (int b = 0; b < a->B; ++b) {
         const int chunks = (a->host_kv_len[b] + pl.chunk_tokens - 1) / pl.chunk_tokens;
         for (int c = 0; c < chunks; ++c)
-            list.request[list.n++] = (uint16_t)((uint32_t)b | (uint32_t)c << kListChunkShift | (c == chunks - 1 ? kListLast : 0u));
+            list.request[list.n++] = (uint16_t)(b | c << kListRequestBits | (chunks - 1) << (kListRequestBits + kListChunkBits));
     }
 }
 

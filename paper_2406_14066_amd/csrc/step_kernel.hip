@@ -1288,12 +1288,17 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     if (place >= n_units) return false;   // padding
     const int kvh = place % p.Hkv;
     int b = place / p.Hkv;   // rank in the order of the attention items
-    uint32_t entry = 0;
+    int capacity = p.capacity_tokens;
     if (order.n > 0) {
         const uint32_t pair = order.pairs[b >> 1];
-        entry = (b & 1) ? pair >> 16 : pair & 0xFFFFu;
-        b = (int)(entry & ((1u << kListChunkShift) - 1u));
-        chunk += (int)(entry >> kListChunkShift) & (kMaxListedChunks - 1);
+        b = (int)((b & 1) ? pair >> 16 : pair & 0xFFFFu);
+        if (p.spread) {
+            // (a request that has outgrown its listed chunks is left out by all of its blocks: a ticket taken for a merge that
+            // no block makes would still be there in the next replay of the launch)
+            capacity = min(capacity, ((b >> (kListRequestBits + kListChunkBits)) + 1) * p.chunk_tokens);
+            chunk = b >> kListRequestBits & (kMaxListedChunks - 1);
+            b &= kMaxListedRequests - 1;
+        }
     }
     const int unit = b * p.Hkv + kvh;
 
@@ -1308,14 +1313,12 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     // The lengths come from device memory and bound every loop and index below: a request
     // whose lengths do not fit the launch (longer than planned for, beyond its block-table row,
     // shorter than its own query rows) is left out and reported.
-    if (!request_lengths_ok(L, q_len, p.capacity_tokens, p.max_blocks_per_req)) {
+    if (!request_lengths_ok(L, q_len, capacity, p.max_blocks_per_req)) {
         if (chunk == 0 && kvh == 0 && tid == 0 && p.errors != nullptr) atomicAdd(p.errors, 1ull);
         return false;
     }
     const int nchunks = (L + p.chunk_tokens - 1) / p.chunk_tokens;   // <= max_chunks, since L <= capacity_tokens
     if (chunk >= nchunks) return false;
-    // a request that has outgrown its listed chunks: the merge waits for a chunk that no block has, so its rows are left out
-    if ((entry & kListLast) != 0 && chunk + 1 < nchunks && kvh == 0 && tid == 0 && p.errors != nullptr) atomicAdd(p.errors, 1ull);
     // even chunks per request, page aligned (never longer than chunk_tokens)
     const int C = ((L + nchunks - 1) / nchunks + SPEC_BLOCK_SIZE - 1) & ~(SPEC_BLOCK_SIZE - 1);
     const int group = p.Hq / p.Hkv;
@@ -2617,7 +2620,7 @@ hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject,
             (ap.f32 && ap.kv_layout != SPEC_KV_TOKEN_MAJOR) || (ap.fused_combine && ap.max_chunks > kMaxFusedChunks) || (order != nullptr && order->n != 0 && order->n != ap.ranks))
             return hipErrorInvalidValue;
         // listed chunks: a table with all of them, whole rows of blocks, and a merge inside the launch
-        if (ap.spread ? (order == nullptr || order->n != ap.ranks || ap.max_chunks > kMaxListedChunks || ap.Hkv % kXcds != 0 || !ap.fused_combine)
+        if (ap.spread ? (order == nullptr || order->n != ap.ranks || ap.B > kMaxListedRequests || ap.max_chunks > kMaxListedChunks || ap.Hkv % kXcds != 0 || !ap.fused_combine)
                       : ap.ranks != ap.B)
             return hipErrorInvalidValue;
         n_attn = step_attn_items(ap);

@@ -60,3 +60,48 @@ def test_step_replays_from_a_graph(tuning, name, kw, early_stop):
         np.testing.assert_array_equal(got["next_token"], eager["next_token"])
         np.testing.assert_array_equal(got["out_tokens"], eager["out_tokens"])
         np.testing.assert_array_equal(got["counters"], eager["counters"])
+
+
+# a replayed launch reuses its tickets' tag: a replay in which a request has outgrown the chunks that the launch lists leaves nothing behind
+# that the next one, with lengths that fit again, would take for its own
+def test_replay_after_one_whose_lengths_did_not_fit(tuning):
+    import torch
+    from paper_2406_14066_amd.harness import DeviceStep
+    print("case graph outgrown", flush=True)
+    kv_len = (4000, 600, 64, 6000)
+    w = W.make_workload("outgrown", B=len(kv_len), Hq=16, Hkv=16, d=128, V=256, dtype="bf16", kv_len=list(kv_len), k=[2] * 4, draft_std=2.0,
+                        sigma=0.8, data_seed=3, philox_seed=9)
+    w.block_table = np.concatenate([w.block_table, w.block_table], axis=1)   # room for the longer lengths (any pages will do)
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    plan = sv.spec_verify_plan(ds.attn_args, None)
+    C = plan["chunk_tokens"]
+    assert plan["attn_blocks"] == 16 * sum(-(-n // C) for n in kv_len) < 16 * len(kv_len) * plan["max_chunks"], plan
+    errors = torch.zeros(1, dtype=torch.int64, device="cuda")
+    ds.attn_args.error_count = errors.data_ptr()
+    good = ds.kv_len.clone()
+    long = good.clone()
+    long[1] = -(-kv_len[1] // C) * C + 1      # one chunk more than listed
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ds.run_attn(side)
+    torch.cuda.synchronize()
+    eager = ds.out.cpu().numpy()
+    check_attn(w, eager)
+    with torch.cuda.graph(graph, stream=side):
+        ds.run_attn(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for lens, found in ((good, 0), (long, 1), (good, 0), (long, 1), (long, 1), (good, 0), (good, 0)):
+        ds.kv_len.copy_(lens)
+        ds.out.fill_(float("nan"))
+        errors.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(errors.item()) == found
+        got = ds.out.cpu().numpy()
+        rows = slice(int(w.cu_q_len[1]), int(w.cu_q_len[2]))
+        if found:
+            assert np.isnan(got[rows]).all()
+            got[rows] = eager[rows]
+        np.testing.assert_array_equal(got, eager)
