@@ -100,8 +100,9 @@ constexpr int kStatWords = 3;
 enum : int32_t {
     kReadAll = 0,    // takes the rows request by request and reads them all
     kStopWait = 1,   // takes them in position order; a block waits for the request's earlier positions and skips its row after a rejection
-    kStopPeek = 2,   // the same, but it only looks at what has been published by then
+    kStopPeek = 2,   // the same, but it only looks at what has been published by then (bf16, beside an attention half)
 };
+constexpr int kMaxOwnLengths = 256;   // requests up to which kStopPeek takes draft lengths of their own (a thread of the block looks at one)
 
 struct RejectPlan {
     int32_t stat_segments, stat_seg_len;   // vocabulary segments per row in the statistics pass
@@ -124,7 +125,7 @@ struct RejectParams {
     int32_t spin_limit;                  // polls a consumer block spends waiting for its producers
     uint32_t generation;
     int32_t early_stop;                  // one of the above
-    int32_t uniform_k;                   // with early stop: every request's draft length, or -1 (they differ; at most 256 requests)
+    int32_t uniform_k;                   // with early stop: every request's draft length, or -1 (they differ; kStopPeek, at most kMaxOwnLengths requests)
     int32_t short_naps;                  // a small launch: the bounded waits poll at short intervals at first
     int32_t final_shift;                 // log2 of the requests per item of the final stage (0..kMaxFinalShift)
     const float *target_logits, *draft_logits;

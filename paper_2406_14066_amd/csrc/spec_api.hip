@@ -636,7 +636,7 @@ RejectPlan plan_reject(const spec_reject_args *r, const Tuning &tu, double attn_
     // V=16000, 16 to 97 tokens: the rate is not known here, nor how long a short launch takes to dispatch).  Not where the
     // rejection half runs alone: its blocks fill the chip at once (four per unit) and start together; 120 such calls -7 to +29%.
     // (peek: the kernel that takes the launch can.)
-    if (peek && r->T > r->B && (uniform_q > 0 || r->B <= 256)) {
+    if (peek && r->T > r->B && (uniform_q > 0 || r->B <= kMaxOwnLengths)) {
         const int sides = r->accept_mode == SPEC_ACCEPT_SAMPLE ? 2 : 1;
         const double in_flight = (double)cus / ((double)sides * r->B * pl.stat_segments);   // positions
         double saved_of_k[SPEC_K_MAX + 1] = {0.0}, before = 0.0;   // rows saved of a request with k draft tokens

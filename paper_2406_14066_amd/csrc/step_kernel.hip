@@ -715,6 +715,7 @@ __device__ __forceinline__ bool greedy_prefix(const RejectParams &p, int b, int 
 struct PositionItem {
     int j, b, row;
 };
+static_assert(kMaxOwnLengths <= kThreads, "a thread per request");
 template <bool PEEK>
 __device__ __forceinline__ bool position_item(const RejectParams &p, int rec, RejectShared &sh, PositionItem &at)
 {
@@ -736,7 +737,7 @@ __device__ __forceinline__ bool position_item(const RejectParams &p, int rec, Re
         at.row = is_draft ? p.T + (row_t0 - at.b) + at.j : row_t0 + at.j;
         return true;
     }
-    // Draft lengths of their own (up to kThreads requests): thread t looks at request t, and the counts of requests with
+    // Draft lengths of their own (up to kMaxOwnLengths requests): thread t looks at request t, and the counts of requests with
     // k >= 0, 1, ... say which position the item is in and which of its requests it belongs to.
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int row_t0 = tid < p.B ? p.cu_q_len[tid] : 0;
@@ -2600,6 +2601,12 @@ hipError_t launch_step_fused(const AttnParams *attn, const RejectParams *reject,
         rp = *reject;
         if (rp.stat_segments > kMaxStatSegments || rp.race_segments > kWave || rp.spin_limit < 1 ||
             rp.final_shift < 0 || rp.final_shift > kMaxFinalShift || (rp.stat_segments << rp.final_shift) > kMaxStatSegments)
+            return hipErrorInvalidValue;
+        // early stop: a form that the kernel has, and one draft length unless each block finds its row from the lengths
+        const bool can_peek = attn != nullptr && !attn->f32;
+        if (rp.early_stop != kReadAll &&
+            ((rp.early_stop == kStopPeek ? !can_peek : rp.early_stop != kStopWait) ||
+             (rp.uniform_k >= 0 ? rp.T != rp.B * (rp.uniform_k + 1) : rp.early_stop != kStopPeek || rp.B > kMaxOwnLengths)))
             return hipErrorInvalidValue;
         if (rp.mode == SPEC_ACCEPT_GREEDY) rp.race_segments = 0;   // no race stage
         n_stat = (rp.mode == SPEC_ACCEPT_SAMPLE ? 2 * rp.T - rp.B : rp.T) * rp.stat_segments;
