@@ -105,3 +105,49 @@ def test_replay_after_one_whose_lengths_did_not_fit(tuning):
             assert np.isnan(got[rows]).all()
             got[rows] = eager[rows]
         np.testing.assert_array_equal(got, eager)
+
+
+# the early stop that looks at what its request's earlier positions have published, replayed: every replay draws other random numbers, so that
+# a record left from the one before would show another rejection.  One row tile, the rejection half first; two row tiles and wave
+# groups in the mixed order of the grid (more blocks of each half than go first).
+@pytest.mark.parametrize("ragged", [False, True], ids=["uniform", "ragged"])
+@pytest.mark.parametrize("B,Hq,Hkv,k,V,mixed", [(64, 2, 1, 6, 2052, False), (80, 32, 8, 7, 8192, True), (80, 64, 8, 7, 8192, True)])
+def test_looking_early_stop_replays_from_a_graph(tuning, B, Hq, Hkv, k, V, mixed, ragged):
+    import torch
+    from paper_2406_14066_amd.harness import DeviceStep
+    print("case graph look", B, Hq, Hkv, k, V, ragged, flush=True)
+    tuning("SPEC_VERIFY_EARLY_STOP", 2)
+    ks = np.random.default_rng(B).integers(2, k + 1, size=B) if ragged else np.full(B, k)
+    ks[0] = k
+    w = W.make_workload("look_graph", B=B, Hq=Hq, Hkv=Hkv, d=128, V=V, dtype="bf16", kv_len=[40 + b for b in range(B)], k=ks, draft_std=3.0,
+                        sigma=0.8, data_seed=B, philox_seed=5)
+    ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
+    step = torch.zeros(1, dtype=torch.int64, device="cuda")
+    ds.reject_args.philox_step_device = step.data_ptr()
+    plan = ds.plan()
+    assert plan["early_stop"] == 1 and mixed == (plan["attn_blocks"] > 512 and plan["reject_blocks"] > 1024), plan
+    assert (plan["row_tiles"], plan["row_groups"]) == {2: (1, 1), 32: (2, 1), 64: (2, 2)}[Hq], plan
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ds.run_step(side)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        ds.run_step(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    out = None
+    for replay in range(4):
+        w.philox_step = 1000 + replay
+        step.fill_(w.philox_step)
+        ds.out.fill_(float("nan"))
+        for t in (ds.accepted_len, ds.next_token, ds.out_tokens):
+            t.fill_(-9)
+        ds.counters.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        got = ds.results()
+        check_reject(w, got, max_excluded=1)
+        if out is None:
+            check_attn(w, got["out"])
+            out = got["out"]
+        np.testing.assert_array_equal(got["out"], out)

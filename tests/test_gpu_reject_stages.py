@@ -133,6 +133,45 @@ def test_early_stop_that_looks_at_earlier_positions(harness, tuning, B, V, unifo
             check_reject(w, res, ref=ref, max_excluded=1)
 
 
+# ... and rows are skipped, none but those after a request's first rejection.  The final stage clears the records of the requests that it
+# serves; with one poll per wait it abandons most of them, and theirs stay behind in the workspace.
+@pytest.mark.parametrize("mode", [sv.ACCEPT_SAMPLE, sv.ACCEPT_GREEDY, sv.ACCEPT_POINT_DRAFT], ids=["sample", "greedy", "point"])
+@pytest.mark.parametrize("B,uniform", [(300, True), (256, False)], ids=["uniform", "ragged"])
+def test_early_stop_that_looks_skips_rows(harness, tuning, B, uniform, mode):
+    print("case skipped rows", B, uniform, mode, flush=True)
+    rng = np.random.default_rng(B)
+    w = W.make_workload("skip", B=B, Hq=1, Hkv=1, d=64, V=1024, dtype="bf16", kv_len=[16] * B, k=[8] * B if uniform else rng.integers(4, 9, size=B),
+                        draft_std=3.0, sigma=0.8, data_seed=B, philox_seed=7)
+    if mode == sv.ACCEPT_SAMPLE:
+        ref = oracle.reject_sample(w.target_logits, w.draft_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
+    elif mode == sv.ACCEPT_GREEDY:
+        ref = oracle.reject_greedy(w.target_logits, w.draft_tokens, w.cu_q_len)
+    else:
+        ref = oracle.reject_onehot(w.target_logits, w.draft_tokens, w.cu_q_len, w.philox_seed, w.philox_step)
+    after = np.zeros(2 * w.T - w.B, dtype=bool)       # rows after a first rejection: target rows, then draft rows
+    for b in range(B):
+        t0, t1, m = int(w.cu_q_len[b]), int(w.cu_q_len[b + 1]), int(ref.accepted_len[b])
+        after[t0 + m + 1: t1] = True
+        after[w.T + t0 - b + m + 1: w.T + t1 - b - 1] = True
+    tuning("SPEC_VERIFY_EARLY_STOP", 2)
+    tuning("SPEC_VERIFY_SPIN_LIMIT", 1)
+    ds = harness.DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR, accept_mode=mode)
+    plan = ds.plan()
+    assert plan["early_stop"] == 1 and plan["stat_segments"] == 1, plan
+    ds.workspace.zero_()
+    ds.run_step()
+    gone = ds.results()["accepted_len"] < 0
+    base = sv.spec_verify_workspace_bytes(ds.attn_args, None)
+    rows = w.T if mode != sv.ACCEPT_SAMPLE else len(after)
+    rec = ds.workspace.cpu().numpy().view(np.uint8)[base: base + rows * 24].view(np.uint32).reshape(rows, 3, 2)   # (value, tag) of three words
+    # a skipped row's record: the largest logit of nothing, or a sum of 1 at offset 0
+    value = (0xFF800000, 0x7FFFFFFF) if mode == sv.ACCEPT_GREEDY else (0, 0x3FF00000, 0)
+    skipped = (rec[:, 0, 1] != 0) & np.all(rec[:, : len(value), 0] == np.array(value, dtype=np.uint32), axis=1)
+    print("abandoned %d of %d requests, rows after a rejection %d, skipped among what is left %d" % (gone.sum(), B, after[:rows].sum(), skipped.sum()),
+          flush=True)
+    assert gone.any() and skipped.any() and not (skipped & ~after[:rows]).any()
+
+
 def test_offsets_far_apart_and_segments_of_nothing(harness):
     """Row statistics whose segments differ by thousands of powers of two, and segments of nothing but -inf: the
     accept chain rescales them exactly (a segment far below the row's maximum adds nothing)."""
