@@ -124,9 +124,8 @@ typedef struct {
                                    page in use must be in [0, num_blocks), else SPEC_EINVAL */
     const int32_t *host_block_table; /* optional HOST copy of block_table, read only when validate == 1 */
     int64_t *error_count;       /* optional DEVICE counter [1], ADDED to: findings of the device-side checks
-                                   (a request whose kv_len is below its q_len, above the planned bound (without a
-                                   bucket: host_kv_len's chunks) or beyond its block-table row; a block-table
-                                   entry outside [0, num_blocks)).
+                                   (a request whose kv_len is below its q_len, above the planned bound or
+                                   beyond its block-table row; a block-table entry outside [0, num_blocks)).
                                    Such a request's output rows are not written; a bad page reads as zeros.
                                    In spec_verify_step a NULL here means &reject->counters[6]. */
 } spec_attn_args;

@@ -1289,14 +1289,16 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
     if (place >= n_units) return false;   // padding
     const int kvh = place % p.Hkv;
     int b = place / p.Hkv;   // rank in the order of the attention items
-    int capacity = p.capacity_tokens;
+    int capacity = p.capacity_tokens, listed = p.max_chunks;
     if (order.n > 0) {
         const uint32_t pair = order.pairs[b >> 1];
         b = (int)((b & 1) ? pair >> 16 : pair & 0xFFFFu);
         if (p.spread) {
-            // (a request that has outgrown its listed chunks is left out by all of its blocks: a ticket taken for a merge that
-            // no block makes would still be there in the next replay of the launch)
-            capacity = min(capacity, ((b >> (kListRequestBits + kListChunkBits)) + 1) * p.chunk_tokens);
+            // A request that has grown on the device past its listed chunks takes longer ones, as far as a wavefront's table
+            // entries go.  (Beyond that it is left out by all of its blocks: a ticket taken for a merge that no block
+            // makes would still be there in the next replay of the launch.)
+            listed = (b >> (kListRequestBits + kListChunkBits)) + 1;
+            capacity = min(capacity, listed * (kWave * PW * SPEC_BLOCK_SIZE));
             chunk = b >> kListRequestBits & (kMaxListedChunks - 1);
             b &= kMaxListedRequests - 1;
         }
@@ -1318,9 +1320,9 @@ __device__ __forceinline__ bool attn_begin(const AttnParams &p, OrderTable order
         if (chunk == 0 && kvh == 0 && tid == 0 && p.errors != nullptr) atomicAdd(p.errors, 1ull);
         return false;
     }
-    const int nchunks = (L + p.chunk_tokens - 1) / p.chunk_tokens;   // <= max_chunks, since L <= capacity_tokens
+    const int nchunks = min((L + p.chunk_tokens - 1) / p.chunk_tokens, listed);   // (<= max_chunks in any case, since L <= capacity_tokens)
     if (chunk >= nchunks) return false;
-    // even chunks per request, page aligned (never longer than chunk_tokens)
+    // even chunks per request, page aligned (never longer than chunk_tokens, unless there are too few listed)
     const int C = ((L + nchunks - 1) / nchunks + SPEC_BLOCK_SIZE - 1) & ~(SPEC_BLOCK_SIZE - 1);
     const int group = p.Hq / p.Hkv;
     // (the plan sized WG and NT for the longest draft of the host copy of cu_q_len; should the device

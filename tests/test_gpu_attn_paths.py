@@ -202,27 +202,32 @@ def test_merge_of_few_chunks(tuning, dtype, Hq, Hkv, k_max):
     assert np.abs(got.astype(np.float64) - _oracle(w)).max() <= ATTN_TOL[dtype]
 
 
-# the listed chunks are the host lengths': a request that has grown or shrunk on the device within its last chunk's room is served,
-# one that needs a chunk more is left out and counted once
-@pytest.mark.parametrize("dtype,Hq,Hkv", [("bf16", 16, 16), ("f32", 16, 8)])
-def test_lengths_that_outgrow_their_listed_chunks(dtype, Hq, Hkv):
+# the listed chunks are the host lengths': a request that has grown or shrunk on the device is served with them, in longer ones if
+# they are too few, up to 64 pages per wavefront; one that does not fit those is left out and counted once
+@pytest.mark.parametrize("dtype,Hq,Hkv,k,groups", [("bf16", 16, 16, 2, 1), ("f32", 16, 8, 2, 1), ("bf16", 64, 8, 7, 2), ("f32", 64, 8, 7, 2)])
+def test_lengths_that_outgrow_their_listed_chunks(dtype, Hq, Hkv, k, groups):
     from paper_2406_14066_amd.harness import DeviceStep
-    print("case outgrown", dtype, Hq, Hkv, flush=True)
-    kv_len = (4000, 600, 64, 6000)
-    w = W.make_workload("outgrown", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len), k=[2] * 4, draft_std=2.0, sigma=0.8,
+    print("case outgrown", dtype, Hq, Hkv, k, flush=True)
+    kv_len = (4000, 600, 64, 6000) + (100,) * (4 if groups == 2 else 0)
+    w = W.make_workload("outgrown", B=len(kv_len), Hq=Hq, Hkv=Hkv, d=128, V=256, dtype=dtype, kv_len=list(kv_len), k=[k] * len(kv_len), draft_std=2.0, sigma=0.8,
                         data_seed=Hq, philox_seed=9)
     w.block_table = np.concatenate([w.block_table, w.block_table], axis=1)   # room for the longer lengths (any pages will do)
     ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
     plan = sv.spec_verify_plan(ds.attn_args, None)
     C = plan["chunk_tokens"]
     chunks = [(n + C - 1) // C for n in kv_len]
-    assert plan["attn_blocks"] == Hkv * sum(chunks), plan
-    room = chunks[0] * C
-    pages = -(-room // 16) + 1
-    w.block_table[0, :pages] = w.block_table[3, np.arange(pages) % (6000 // 16)]
+    assert plan["attn_blocks"] == Hkv * sum(chunks) < Hkv * len(kv_len) * plan["max_chunks"] and plan["row_groups"] == groups, plan
+    most, bound = 4096 // groups, C * plan["max_chunks"]    # tokens of a chunk, of a request
+    for b in (0, 1, 2):
+        w.block_table[b] = np.resize(w.block_table[3, : 6000 // 16], w.block_table.shape[1])
     ds.block_table.copy_(ds.block_table.new_tensor(w.block_table))
-    for lens, out in (([room, 500, 40, 3000], ()), ([room + 1, 500, 64, 6000], (0,)), ([4000, chunks[1] * C + 16, 64, 6000], (1,))):
-        w.kv_len = np.asarray(lens, dtype=np.int32)
+    one, two = min(chunks[2] * most, bound), min(chunks[1] * most, bound)    # (what a request of one chunk and one of some can grow to)
+    cases = [([chunks[0] * C, 500, 40, 3000], ()), ([chunks[0] * C + 1, 500, 64, 6000], ()), ([4000, chunks[1] * C + 16, C + 1, 6000], ()),
+             ([4000, two, one, 17], ())]
+    if chunks[2] * most < bound:
+        cases.append(([4000, 600, chunks[2] * most + 1, 6000], (2,)))
+    for lens, out in cases:
+        w.kv_len = np.asarray(tuple(lens) + kv_len[4:], dtype=np.int32)
         ds.kv_len.copy_(ds.kv_len.new_tensor(w.kv_len))
         got, found = _run(ds)
         assert found == len(out), (lens, found)
@@ -232,4 +237,4 @@ def test_lengths_that_outgrow_their_listed_chunks(dtype, Hq, Hkv):
             if b in out:
                 assert np.isnan(rows).all()
             else:
-                assert np.abs(rows.astype(np.float64) - ref[_rows(w, b)]).max() <= ATTN_TOL[dtype]
+                assert np.abs(rows.astype(np.float64) - ref[_rows(w, b)]).max() <= ATTN_TOL[dtype], (lens, b)

@@ -62,7 +62,7 @@ def test_step_replays_from_a_graph(tuning, name, kw, early_stop):
         np.testing.assert_array_equal(got["counters"], eager["counters"])
 
 
-# a replayed launch reuses its tickets' tag: a replay in which a request has outgrown the chunks that the launch lists leaves nothing behind
+# a replayed launch reuses its tickets' tag: a replay in which a request has outgrown what the chunks that the launch lists can hold leaves nothing behind
 # that the next one, with lengths that fit again, would take for its own
 def test_replay_after_one_whose_lengths_did_not_fit(tuning):
     import torch
@@ -75,12 +75,12 @@ def test_replay_after_one_whose_lengths_did_not_fit(tuning):
     ds = DeviceStep(w, kv_layout=sv.KV_TOKEN_MAJOR)
     plan = sv.spec_verify_plan(ds.attn_args, None)
     C = plan["chunk_tokens"]
-    assert plan["attn_blocks"] == 16 * sum(-(-n // C) for n in kv_len) < 16 * len(kv_len) * plan["max_chunks"], plan
+    assert plan["attn_blocks"] == 16 * sum(-(-n // C) for n in kv_len) < 16 * len(kv_len) * plan["max_chunks"] and C < 4096 < C * plan["max_chunks"], plan
     errors = torch.zeros(1, dtype=torch.int64, device="cuda")
     ds.attn_args.error_count = errors.data_ptr()
     good = ds.kv_len.clone()
     long = good.clone()
-    long[1] = -(-kv_len[1] // C) * C + 1      # one chunk more than listed
+    long[2] = 4097      # one chunk is listed, and no chunk has more than 4096 tokens
     graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
@@ -100,7 +100,7 @@ def test_replay_after_one_whose_lengths_did_not_fit(tuning):
         torch.cuda.synchronize()
         assert int(errors.item()) == found
         got = ds.out.cpu().numpy()
-        rows = slice(int(w.cu_q_len[1]), int(w.cu_q_len[2]))
+        rows = slice(int(w.cu_q_len[2]), int(w.cu_q_len[3]))
         if found:
             assert np.isnan(got[rows]).all()
             got[rows] = eager[rows]
