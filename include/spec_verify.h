@@ -216,9 +216,10 @@ typedef struct {
 /* Host-only: bytes of workspace the three calls below need for these shapes
  * (either argument may be NULL).  Returns 0 if the arguments are malformed.
  * The workspace must be 256-byte aligned device memory; its contents need no
- * initialisation and are undefined afterwards.  A workspace asked for the largest
- * batch and draft length serves the rejection half of smaller calls with that vocabulary too: where its
- * records would not fit, the half runs with fewer blocks. */
+ * initialisation and are undefined afterwards.  Where a call's own size is not there, a smaller one may still
+ * serve (SPEC_EWORKSPACE if not): the rejection half alone then runs with fewer blocks, so that a workspace asked for
+ * the largest batch and draft length serves smaller calls with that vocabulary too, and attention planned
+ * without a bucket splits the requests as the longest one needs it and not by all lengths. */
 size_t spec_verify_workspace_bytes(const spec_attn_args *attn, const spec_reject_args *reject);
 
 /* (a) only: writes attn->out. */
@@ -240,8 +241,10 @@ spec_status spec_verify_step(const spec_attn_args *attn, const spec_reject_args 
  * results and errors as spec_verify_step, but the workspace is a device array inside the
  * library (SPEC_STATIC_SCRATCH_BYTES per GPU, held by every GPU the library runs on until the
  * process ends).  The call allocates and frees nothing.
- *   - A step whose workspace (spec_verify_workspace_bytes) exceeds SPEC_STATIC_SCRATCH_BYTES is
- *     refused with SPEC_EWORKSPACE before anything is launched; use spec_verify_step then.
+ *   - A step that needs more than SPEC_STATIC_SCRATCH_BYTES is refused with SPEC_EWORKSPACE before anything is
+ *     launched; use spec_verify_step then.  What counts is the smaller workspace with which spec_verify_step would
+ *     still serve (see above), so a step whose spec_verify_workspace_bytes fits always runs, and one whose
+ *     does not may.
  *   - The first call on a GPU resolves the array's device address (one runtime query, no
  *     allocation); make that call outside stream capture.
  *   - All calls on one GPU share that GPU's array, which keeps the previous call's contents
@@ -253,8 +256,8 @@ spec_status spec_verify_step(const spec_attn_args *attn, const spec_reject_args 
 spec_status spec_verify_step_static(const spec_attn_args *attn, const spec_reject_args *reject, void *hip_stream);
 
 /*
- * Host-only: how the library would run this step (either argument may be NULL), for
- * callers and tests that want to know which kernel a shape takes.
+ * Host-only: how the library would run this step (either argument may be NULL) on a workspace of the reported
+ * size, for callers and tests that want to know which kernel a shape takes.
  */
 #define SPEC_PATH_NONE 0
 #define SPEC_PATH_MFMA 1     /* bf16: matrix-instruction attention inside the one-launch step kernel */
