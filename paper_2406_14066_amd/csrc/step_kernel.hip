@@ -2101,7 +2101,8 @@ struct AttnF32Shared {
     int last;
 };
 
-template <int NT, int WG, int D>
+// (K_POLICY: cache policy of the K loads)
+template <int NT, int WG, int D, int K_POLICY>
 __device__ __forceinline__ void attn_f32_role(const AttnParams &p, OrderTable order, int item, AttnF32Shared<NT, WG, D> &sh)
 {
     constexpr int KI = D / 16;                        // 16-byte K loads per lane and page
@@ -2127,12 +2128,12 @@ __device__ __forceinline__ void attn_f32_role(const AttnParams &p, OrderTable or
     f32x4 k[KI], v[4][VH];   // v[r][h]: token 4 g + r, dims 64 h + 4 n16 ..
     // (K without the streaming hint: a load takes 64 bytes of each token row, half a cache line, and the other half, which
     // the next load wants, is gone by then if the line is first in line for replacement.  Eight requests on 32/32 heads, k = 4: 39.8 -> 35.1
-    // us; on 32/8, k = 2: 18.3 -> 17.4.)
+    // us; on 32/8, k = 2: 18.3 -> 17.4.  With it beside many rejection blocks, see launch_f32.)
     auto load_k = [&](int it) {
         const __amdgpu_buffer_rsrc_t d = page_desc(khead, it);
 #pragma unroll
         for (int i = 0; i < KI; ++i)
-            k[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, n16 * (D * 4) + g * 16, i * 64, 0));
+            k[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, n16 * (D * 4) + g * 16, i * 64, K_POLICY));
     };
     auto load_v = [&](int it) {
         const __amdgpu_buffer_rsrc_t d = page_desc(vhead, it);
@@ -2427,7 +2428,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_k_direct_kernel(StepArgs arg
 // The step in fp32: the same grid and roles.  A launch of the attention alone has no rejection items.
 // (Three row tiles take over 256 registers at a head dim of 128: 33 to 48 rows run as two wave groups of two
 // tiles, and only the widest shapes, 129 to 144 rows, as four groups of three with one block per compute unit.)
-template <int NT, int WG, int D>
+template <int NT, int WG, int D, int K_POLICY = 0>
 __global__ __launch_bounds__(kThreads, (NT == 3 ? 1 : 2)) void f32_step_kernel(StepArgs args)
 {
     int item;
@@ -2435,7 +2436,7 @@ __global__ __launch_bounds__(kThreads, (NT == 3 ? 1 : 2)) void f32_step_kernel(S
     if (!grid_item(args.gs, item, is_attn)) return;
     typedef AttnF32Shared<NT, WG, D> AttnSh;
     __shared__ alignas(16) unsigned char shared[sizeof(RejectShared) > sizeof(AttnSh) ? sizeof(RejectShared) : sizeof(AttnSh)];
-    if (is_attn) attn_f32_role<NT, WG, D>(args.ap, order_table(args.order.n), item, *reinterpret_cast<AttnSh *>(shared));
+    if (is_attn) attn_f32_role<NT, WG, D, K_POLICY>(args.ap, order_table(args.order.n), item, *reinterpret_cast<AttnSh *>(shared));
     else reject_item<NT >= 2 ? 8 : 4, false>(args.rp, args.gs.n_stat, item, *reinterpret_cast<RejectShared *>(shared));
 }
 
@@ -2520,6 +2521,16 @@ hipError_t launch_f32(const AttnParams &ap, const RejectParams &rp, int n_stat, 
 {
     StepArgs args;
     const dim3 grid = fill_args<true, true>(args, ap, rp, n_stat, n_attn, n_race, order);
+    // 64 dims, one wave group: K takes the streaming hint beside a race and more rejection blocks than the chip has slots, whose logits, part
+    // of them read twice, then pass through the caches for most of the launch, and contexts that do not outlast them.  Without
+    // / with it, steps in us: 16/16 heads, 243 requests of 10 to 199 tokens, k = 7, V = 16032 84.5 / 80.5, 173 of 60 to 113, k = 7 47.4 / 44.7,
+    // 189 of 517, k = 2 147.8 / 146.0; 32/8, 164 of 212 to 395, k = 3 73.9 / 70.1, 97 of 662 to 1229, k = 4 109.4 / 107.9; longer ones, 73 of 1026 to
+    // 1907, k = 6 154.1 / 163.9; fewer rejection blocks, 20 of 475 to 882, k = 0 24.3 / 28.4, 77 of 98 to 1863, k = 6 116.2 / 126.1.  Worst
+    // for it, 148 of 57, k = 5, point-mass draft 43.5 / 44.4.  (128 dims: 55 of 44 to 853 on 32/8 heads, k = 8 90.3 / 104.1, 200 of 148 on 32/32,
+    // k = 5 207.6 / 220.3, 57 of 233 on 64/8, k = 6 84.0 / 80.3, 133 of 6 to 127, k = 1 58.0 / 56.5: no size was found that tells them apart.)
+    if constexpr (WG == 1)
+        if (ap.d == 64 && rp.race_segments > 0 && args.gs.n_reject > 4 * ap.reject_even_limit && ap.capacity_tokens <= 1536)
+            return launch_kernel(f32_step_kernel<NT, WG, 64, kStreamPolicy>, grid, args, ev, stream);
     if (ap.d == 64) return launch_kernel(f32_step_kernel<NT, WG, 64>, grid, args, ev, stream);
     return launch_kernel(f32_step_kernel<NT, WG, 128>, grid, args, ev, stream);
 }

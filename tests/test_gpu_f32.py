@@ -43,6 +43,29 @@ def test_rows_and_lengths(harness, Hq, Hkv, kmax, d):
     np.testing.assert_array_equal(ds.results()["out"], res["out"])
 
 
+# 64 dims beside a race and more rejection blocks than block slots: K with the streaming hint up to a longest request of 1536 tokens.  The hint
+# changes no result: the attention alone, which runs without it, gives the same bits
+@pytest.mark.parametrize("longest", [1536, 1537])
+@pytest.mark.parametrize("Hq,Hkv,k,tiles", [(4, 2, 6, 1), (8, 2, 7, 2)])
+def test_k_with_the_streaming_hint(harness, tuning, Hq, Hkv, k, tiles, longest):
+    print("case f32 K hint", Hq, Hkv, k, longest, flush=True)
+    tuning("SPEC_VERIFY_F32_SCALAR", 0)
+    B = 150
+    kv_len = [longest if b == 70 else k + 1 + (37 * b) % 90 for b in range(B)]
+    w = _workload(Hq, Hkv, 64, kv_len, [k] * B, seed=tiles)
+    ds = harness.DeviceStep(w)
+    plan = ds.plan()
+    assert plan["reject_blocks"] > 1024 and (plan["row_tiles"], plan["row_groups"]) == (tiles, 1), plan
+    ds.run_step()
+    res = ds.results()
+    check_attn(w, res["out"])
+    check_reject(w, res, max_excluded=1)
+    if sv.spec_verify_plan(ds.attn_args, None)["chunk_tokens"] == plan["chunk_tokens"]:
+        ds.out.zero_()
+        ds.run_attn()
+        np.testing.assert_array_equal(ds.results()["out"], res["out"])
+
+
 @pytest.mark.parametrize("bucket", [0, 2048])
 @pytest.mark.parametrize("chunk", [16, 48, 1024])
 def test_split_requests(harness, tuning, chunk, bucket):
