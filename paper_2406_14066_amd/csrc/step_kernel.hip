@@ -2526,8 +2526,9 @@ hipError_t launch_f32(const AttnParams &ap, const RejectParams &rp, int n_stat, 
     // / with it, steps in us: 16/16 heads, 243 requests of 10 to 199 tokens, k = 7, V = 16032 84.5 / 80.5, 173 of 60 to 113, k = 7 47.4 / 44.7,
     // 189 of 517, k = 2 147.8 / 146.0; 32/8, 164 of 212 to 395, k = 3 73.9 / 70.1, 97 of 662 to 1229, k = 4 109.4 / 107.9; longer ones, 73 of 1026 to
     // 1907, k = 6 154.1 / 163.9; fewer rejection blocks, 20 of 475 to 882, k = 0 24.3 / 28.4, 77 of 98 to 1863, k = 6 116.2 / 126.1.  Worst
-    // for it, 148 of 57, k = 5, point-mass draft 43.5 / 44.4.  (128 dims: 55 of 44 to 853 on 32/8 heads, k = 8 90.3 / 104.1, 200 of 148 on 32/32,
-    // k = 5 207.6 / 220.3, 57 of 233 on 64/8, k = 6 84.0 / 80.3, 133 of 6 to 127, k = 1 58.0 / 56.5: no size was found that tells them apart.)
+    // for it, 148 of 57, k = 5, point-mass draft 43.5 / 44.4.  (128 dims: over 74 steps with more than 800 rejection blocks without it takes 0.86
+    // to 1.05 of the time with it, 0.98 in the mean: 55 of 44 to 853 on 32/8 heads, k = 8 90.3 / 104.1, 57 of 233 on 64/8, k = 6 84.0 / 80.3, 133 of 6
+    // to 127, k = 1 58.0 / 56.5; neither sizes nor blocks tell them apart.)
     if constexpr (WG == 1)
         if (ap.d == 64 && rp.race_segments > 0 && args.gs.n_reject > 4 * ap.reject_even_limit && ap.capacity_tokens <= 1536)
             return launch_kernel(f32_step_kernel<NT, WG, 64, kStreamPolicy>, grid, args, ev, stream);
